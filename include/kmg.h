@@ -120,14 +120,12 @@ int32_t kmg_version(void);
  * its stream).  Not thread-safe: for single-threaded profiling runs.
  * kmg_timing_enable(0) stops timing.  Returns 0, or -1 if events could not
  * be created.  kmg_timing_read copies up to n stage totals (milliseconds and
- * number of bracketed launches; match_topk is the candidate tile launch of
- * the first matching direction, match_image the whole matching back) and
+ * number of bracketed launches; match_topk is the sample and sweep launches of
+ * the first matching phase, match_image the whole matching back) and
  * returns the number of stages; kmg_stage_name(i) names stage i (static
  * storage).  kmg_timing_work copies up to n per-stage work counts of the
- * stage's last timed launch (for match_topk and match_image with the norm
- * bands: query-row products the tiles evaluated, each 16-query tile over its
- * own chunk range; 0 where a stage counts
- * none, -1 if the count could not be read) and returns the number of stages;
+ * stage's last timed launch (for match_topk: query-row products of the
+ * matching's first phase; 0 where a stage counts none, -1 if the count could not be read) and returns the number of stages;
  * it reads device memory of the last call's workspace, which must still be
  * allocated.
  */
@@ -155,10 +153,9 @@ const char* kmg_stage_name(int32_t stage);
  *                   rows read from LDS per step where two J points share a
  *                   wavefront (3H <= 64), rows in flight per lane otherwise;
  *                   1, 2 (default), 4, 8 or 16.
- *   band_tile       partner chunks per distance tile of matching (a length
- *                   of the planner's candidate set: 1..64, then four per
- *                   octave up to 4096), used whenever its tiles fit; 0
- *                   (default) = the planner's modelled choice.
+ *   band_tile       accepted (1..64, then four per octave up to 4096; 0 =
+ *                   default) and without effect: the matching plans its tiles
+ *                   from the sizes of the sets.
  *   fuse_features   1: SPFH and FPFH (Eq. A2-A5) in one persistent launch
  *                   that takes work items from a queue, the FPFH of a cloud
  *                   starting once every SPFH of that cloud is written
@@ -170,13 +167,12 @@ const char* kmg_stage_name(int32_t stage);
  *                   eighth's neighbourhood) rather than in turn; 0..3,
  *                   default 2 (measured: the FPFH gather reads its
  *                   neighbours' rows and gains, the SPFH pass loses).
- *   match_form      FP64 matching (Section III-C reciprocity test) of a batch
- *                   that fits the one-sided form: 0 (default) matches the
- *                   smaller set of each pair against the larger, then only
- *                   the rows that are some query's nearest neighbour back;
- *                   1 matches both directions in full in one band pass (more
- *                   distance tiles, fewer launches).  The same
- *                   correspondences, d1 and d2 either way.
+ *   match_form      matching (Section III-C reciprocity test): 0 (default)
+ *                   large sets one-sided (the smaller set of each pair against
+ *                   the larger, then only the rows that are some query's
+ *                   nearest neighbour back), small ones in both directions at
+ *                   once; 1 both directions always.  The same correspondences,
+ *                   d1 and d2 either way.
  *   search_form     radius search (Eq. A1) of a batch (kmg_batch_run):
  *                   0 a count pass, the offsets, then the fill pass;
  *                   1 (default) one search pass that writes |N(q)| and each list
@@ -294,20 +290,22 @@ kmg_status kmg_fpfh(const float* xyz, const float* normals, uint8_t* flags, cons
  * Distance D(i, j) = sum_t ((double)x_it - (double)y_jt)^2 in dimension
  * order (squared L2).  NN_Q(i) = argmin_j D(i, j), ties to the smaller j;
  * NN_P(j) likewise.  (i, j) is a correspondence iff NN_Q(i) = j and
- * NN_P(j) = i.  Candidates are found on matrix cores (precision `prec`)
- * and every reported decision is re-scored exactly in FP64; rows whose
- * candidate set cannot be certified are re-scanned exactly.
+ * NN_P(j) = i.  Candidates are the rows whose distance in 16-bit integer
+ * coordinates (exact sums on matrix cores, with a rigorous bound of what
+ * rounding moved) may be among the two smallest; they are scored exactly in
+ * FP64, and queries that the integers cannot serve are scanned exactly.
  *   desc_p    [in]  float32 row-major, rows addressed through rows_p.
  *   rows_p    [in]  int32[np]: row of desc_p for each P entry, or NULL for
  *                   rows 0..np-1.  The same for desc_q / rows_q / nq.
  *   dim       [in]  descriptor length (1 <= dim <= 64).
- *   prec      [in]  KMG_FP32 (KMG_BF16 / KMG_FP16: candidate generation in
- *                   16-bit with FP32 accumulation; same exact result).
+ *   prec      [in]  KMG_FP32, KMG_BF16 or KMG_FP16: the same exact result,
+ *                   from the same 16-bit candidates.
  *   pairs     [out] int32[cap * 2]: (rows_p[i], rows_q[j]) sorted by i.
  *   d1, d2    [out] float32[cap]: sqrt of the smallest and second-smallest
  *                   D over row i (d2 = +inf if nq < 2).
  *   n_pairs   [out, HOST] number of correspondences.
- *   n_fallback[out, optional HOST] rows (both directions) re-scanned exactly.
+ *   n_fallback[out, optional HOST] queries (both directions) that took more
+ *                   than four exact scores (a work statistic).
  * Descriptors must be finite and non-negative (FPFH rows are).
  */
 kmg_status kmg_match(const float* desc_p, const int32_t* rows_p, int64_t np, const float* desc_q,
@@ -330,8 +328,8 @@ kmg_status kmg_match(const float* desc_p, const int32_t* rows_p, int64_t np, con
  *
  * counts [out, DEVICE] int64[8 * n_pairs]: per pair, 0 correspondences,
  * 1 kept source points, 2 kept target points, 3 |J| source, 4 |J| target,
- * 5 queries re-scanned exactly (a work statistic: it depends on the matching
- * form of the launch tuning, the other entries do not), 6 status (a kmg_status; KMG_ERR_WORKSPACE
+ * 5 queries that took more than four exact scores (a work statistic: it
+ * depends on the matching form of the launch tuning, the other entries do not), 6 status (a kmg_status; KMG_ERR_WORKSPACE
  * when the batch's neighbour entries exceed nnz_cap, KMG_ERR_CAPACITY when
  * outs[i].cap is too small, KMG_ERR_DEVICE if a bounded wait between the
  * blocks of a kernel gave up, which is never expected), 7 neighbour entries

@@ -195,7 +195,7 @@ kmg_status batch_run(int n_pairs, int64_t raw_cap, int64_t nnz_cap, int H, int p
                            w.nrm, raw_cap, w.flags, nullptr, w.fpfh, w.jlist, w.cs, s, true, w.sets,
                            w.scan_status + w.n_vox_status + w.n_search_status));
     // the pair counts and statuses come with the correspondences
-    KMG_TRY(match_batch(w.sets, C, D, prec, w.st, w.match, w.outs, counts, kCountsStride, s, w.cs, nnz_cap));
+    KMG_TRY(match_batch(w.sets, C, D, w.st, w.match, w.outs, counts, kCountsStride, s, w.cs, nnz_cap));
     timer_collect();  // waits for the stream only while timing is enabled
     return KMG_OK;
 }

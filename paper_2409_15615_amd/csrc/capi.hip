@@ -171,8 +171,8 @@ KMG_EXPORT kmg_status kmg_match(const float* desc_p, const int32_t* rows_p, int6
     if ((np > 0 && !desc_p) || (nq > 0 && !desc_q)) return KMG_ERR_ARG;
     if (cap > 0 && (!pairs || !d1 || !d2)) return KMG_ERR_ARG;
     if (ws_bytes < kmg::match_ws(np, nq, dim)) return KMG_ERR_WORKSPACE;
-    return kmg::match(desc_p, rows_p, np, desc_q, rows_q, nq, dim, prec, pairs, d1, d2, cap, n_pairs, n_fallback,
-                      ws, ws_bytes, as_stream(stream));
+    return kmg::match(desc_p, rows_p, np, desc_q, rows_q, nq, dim, pairs, d1, d2, cap, n_pairs, n_fallback, ws,
+                      ws_bytes, as_stream(stream));
 }
 
 }  // extern "C"

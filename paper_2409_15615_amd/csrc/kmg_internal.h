@@ -27,7 +27,6 @@ constexpr int kListSmall = 1024;                             // LDS neighbour li
 constexpr int kMaxDegree = 8192;                             // largest |N(q)| accepted
 constexpr int kMaxBins = 32;                                 // largest H (3H <= 96 descriptor values)
 constexpr int kMaxMatchDim = 64;                             // longest descriptor the matcher takes
-constexpr int kTopK = 4;                                     // candidates kept per query before re-scoring
 constexpr int kPersistBlocks = 2048;                         // grid of the grid-stride kernels
 
 // Strict radius test d2 < r^2: an FP32 screen decides everything farther than
@@ -74,25 +73,35 @@ struct MatchSet {
     const int32_t* rows;  // nullable
     const int32_t* n;     // device count
     int32_t row_base;     // subtracted from rows[i] in the output
-    int32_t flags;        // kSetRowsOnly: rows for the partner only, no queries
+    int32_t flags;        // reserved
 };
-constexpr int32_t kSetRowsOnly = 1;
 
-// Per-set plan written by the device planner.
+// Per-set plan written by the device planner of the matching.
 struct SetPlan {
-    int32_t n;          // rows
-    int32_t q_off;      // first query slot in the flattened query space
-    int32_t chunk_off;  // first packed 16-row chunk
-    int32_t chunks;
-    int32_t tile_off;   // first tile of this set as the query side (norm bands: first sorted tile)
-    int32_t cblocks;    // 256-query column blocks
-    int32_t segs;       // segments of the partner's rows
-    int32_t n_fb;       // queries of this set re-scanned exactly
-    int64_t part_off;   // first partial entry
-    unsigned long long max_norm_bits;  // max squared norm (FP64 bits, non-negative)
-    int32_t wave_off;   // norm-band matching: first query wave of the set
-    int32_t rank_off;   // norm-band matching: first tile pair of the set's cross ranking
-    int32_t n_img;      // one-sided form: rows of this set listed for the matching back
+    int32_t n;           // rows
+    int32_t base;        // first slot (slots of a set start on a 16-row chunk)
+    int32_t s_base;      // first row of the set's sample
+    int32_t nq;          // queries of the phase (all rows, the image rows, or none)
+    int32_t groups;      // 64-query groups of the phase
+    int32_t grp_off;     // first of them
+    int32_t s_tile_off;  // first tile of the sample pass with this set as queries
+    int32_t tile_off;    // first tile of the sweep
+    int32_t emit_off;    // first tile of the mutual test (even sets)
+    int32_t n_out;       // rows out of the integer range
+    int32_t n_open;      // queries of the phase listed for the exact scan
+    int32_t n_img;       // one-sided form: rows listed for the matching back
+    int32_t pad[2];
+};
+
+// Counts of the matching's passes, on the device.
+struct MatchCtl {
+    int32_t slots, groups, s_tiles, tiles;
+    int32_t s_segs;      // sample segments per group (partials per query)
+    int32_t depth;       // chunks per tile of the sweep
+    int32_t cap;         // listed rows per query
+    int32_t open;        // queries listed for the exact scan
+    int32_t emit_tiles;
+    int32_t n_long;      // queries whose lists go to whole wavefronts
 };
 
 // Matching output of one pair (device buffers).
@@ -118,19 +127,8 @@ struct DevStatus {
     uint32_t amb_orientation; // |n . (vp - a_q)| tiny (FP64)
     uint32_t feat_fp64;       // pair features recomputed in FP64
     uint32_t feat_edge;       // FP64 features within 1e-9 of a bin edge
-    uint32_t n_fallback;      // queries re-scanned exactly
-    int32_t total_tiles;      // matching tiles
-    uint32_t tile_next;       // persistent tile queue
-    int32_t total_queries;
-    int64_t total_chunks;
-    int64_t pairs_total;      // correspondences over the batch
-    int32_t total_waves;      // norm-band matching: query waves
-    int32_t band_step;        // norm-band matching: chunks per tile
-    int32_t rank_items;       // norm-band matching: tile pairs of the cross ranking
-    int32_t sort_items;       // norm-band matching: sorted tiles
-    int64_t band_pairs;       // norm-band matching: query-row products evaluated by the tiles
-    int32_t err_sync;         // a bounded wait inside a persistent kernel gave up (never expected)
-    int32_t pad1;
+    int32_t err_sync;         // a bounded wait inside a kernel gave up (never expected)
+    int64_t match_products;   // query-row products of the matching's first phase
 };
 
 // Linear workspace allocator; with base == nullptr it only measures.
@@ -388,75 +386,55 @@ kmg_status fpfh_batch(int n_clouds, const float* xyz, int64_t stride, int64_t m_
                       uint64_t* j_scan_status = nullptr);
 
 // ---- match.hip ------------------------------------------------------------
-constexpr int kLpMaxDim = 64;  // descriptor length of the FP16 / BF16 tiles (two K = 32 steps)
-// Per pair of the reduced-precision form: the centre of both sets' rows and a
-// power-of-two scale (max |x - mu| * scale <= 2^14).
-struct PairLp {
-    double mu[kLpMaxDim];
-    double scale;
-    double inv_s2;
-    unsigned long long maxabs_bits;  // max |x - mu| over both sets (FP64 bits)
+// Centre and scale of a pair's integer rows.
+struct PairScale {
+    double mu[kMaxMatchDim];
+    double scale, inv;
 };
-// Re-run of the queries the reduced-precision certificate left open: their
-// own sets (query rows listed through f_row) against the full partner sets
-// (rows only), through the FP64 form with its own status block and its own
-// workspace region (carved on the host when used).
-struct RerunWs {
-    DevStatus* st;
-    MatchSet* sets;      // 2 per main set
-    int32_t* f_slot;     // main query slot of each listed query
-    int32_t* f_row;      // its descriptor row
-    int32_t* f_count;    // listed queries per main set
-    int64_t* f_total;
-    char* region;        // nullptr when not carved
-    size_t region_bytes;
+// The two sets of kmg_match, by value (on = 0: the sets are on the device).
+struct SinglePair {
+    int32_t on, na, nb, pad;
+    MatchSet a, b;
+    int32_t* counts;
+    PairOutDev out;
+    PairOutDev* out_dev;
 };
 struct MatchWs {
+    MatchCtl* ctl;
     SetPlan* plan;
-    double* pk;           // packed rows
-    double* n2;           // exact squared norms per query slot
-    double* part;         // per-segment top-4 lists of encoded scores
-    double* lp_nx;        // reduced-precision form: ||x - mu|| per query slot
-    PairLp* lp_pairs;     // reduced-precision form: per pair centre and scale
-    RerunWs rr;           // FP64 re-runs: uncertified queries, the one-sided form's matching back
-    MatchSet* one_sided;  // the sets of the one-sided form's first direction (null: both in full)
-    int32_t* rank;        // norm-band matching: packed position of every query slot in its set
-    int32_t* perm;        // norm-band matching: local row of every packed position
-    double* r2;           // norm-band matching: seed bound R^2 per query slot
-    uint32_t* skey;       // norm-band matching: sort key of every packed partner position
-    int32_t* wave_c0;     // norm-band matching: first partner chunk of every query wave's band
-    int32_t* wave_len;    // norm-band matching: chunks in the band
-    int2* wave_sub;       // norm-band matching: chunk range of each 16-query tile of every wave
-    int32_t* chist;       // norm-band matching, both directions: class histogram of every query sort tile
-    int32_t* wave_tile;   // norm-band matching: first tile of every wave (wave_cap + 1 entries)
-    int4* tinfo;          // norm-band matching: per tile {wave, set, first chunk, end chunk}
-    int64_t wave_cap;
-    int64_t tile_cap;
-    int32_t* nn;
+    PairScale* pp;
+    unsigned char* rows;   // packed integer rows, 128 bytes per slot
+    int* half;             // per slot: minus half the squared norm, less one (INT_MIN: not in the sweep)
+    unsigned char* s_rows; // the samples, packed the same way
+    int* s_half;
+    int2* s_best;          // best and second raw score of every query over a sample segment
+    float* err;            // per slot: rounding error in units of the scale (< 0: not in the sweep)
+    int32_t* cnt;          // per slot: listed rows
+    uint2* pool;           // the lists: ctl->cap entries (row, raw score) per slot
+    int32_t* out_list;     // rows out of range, in their set's slots
+    int32_t* fb_list;      // queries of the exact scan, in their set's slots
+    int32_t* long_list;    // queries with long lists
+    double* part;          // partial results of the exact scans
+    int32_t* img_list;     // one-sided form: rows of the matching back, in their set's slots
+    int32_t* nn;           // per slot: nearest neighbour, and the two smallest squared distances
     double* best;
     double* second;
-    int32_t* fb_list;     // queries left to the exact scan (slot order, or any order from the band re-score)
-    int64_t* fb_total;
-    int32_t* grp_done;    // exact scan: finished segments per 64-entry group (the planners zero them)
-    int64_t n_grp;
-    int32_t* flag;
-    int32_t* pos;
-    int64_t* scan_tmp;
-    int64_t q_cap;        // total query slots
-    int64_t chunk_cap;    // packed chunks
-    int64_t part_cap;     // partial entries
-    int kp;
+    int32_t* fb_part;      // queries decided on more than four exact scores, partial counts per set
+    int32_t* grp_done;     // exact scan: finished segments per 64-entry group
+    uint64_t* emit_status; // look-back words of the mutual test
+    int64_t q_cap, slot_cap, pool_cap, part_cap;
+    int32_t n_sets;
 };
-MatchWs carve_match(Carver& c, int n_sets, int64_t q_cap, int dim, bool rerun = true);
+MatchWs carve_match(Carver& c, int n_sets, int64_t q_cap, int dim);
 // Matches sets 2i and 2i+1 for every pair i (both directions, mutual check).
 // counts[i * counts_stride + 0] receives the number of correspondences of
-// pair i and [.. + 5] the number of exact re-scans of its queries.
-// With cs (the batch form), counts also receive per pair the kept points and
-// |J| of both clouds (from cs), the neighbour entries and the pair's status
-// (nnz_cap: the neighbour-list capacity the status is judged against).
-kmg_status match_batch(const MatchSet* sets, int n_sets, int dim, int prec, DevStatus* st, const MatchWs& w,
-                       const PairOutDev* outs, int64_t* counts, int counts_stride, hipStream_t s,
-                       const CloudState* cs = nullptr, int64_t nnz_cap = 0);
+// pair i and [.. + 5] the number of queries decided on more than four exact
+// scores.  With cs (the batch form), counts also receive per pair the kept
+// points and |J| of both clouds (from cs), the neighbour entries and the
+// pair's status (nnz_cap: the neighbour-list capacity it is judged against).
+kmg_status match_batch(MatchSet* sets, int n_sets, int dim, DevStatus* st, const MatchWs& w, const PairOutDev* outs,
+                       int64_t* counts, int counts_stride, hipStream_t s, const CloudState* cs = nullptr,
+                       int64_t nnz_cap = 0);
 
 // ---- graph.hip: ratio filter, Eq. (3) graph, max k-core ----------------------
 size_t graph_ws(int64_t n_corr, int32_t n_tau);
@@ -482,7 +460,7 @@ kmg_status fpfh(const float* xyz, const float* nrm, uint8_t* flags, const int32_
                 int64_t* stats_host, void* ws, size_t ws_bytes, hipStream_t s);
 size_t match_ws(int64_t np, int64_t nq, int dim);
 kmg_status match(const float* dp, const int32_t* rp, int64_t np, const float* dq, const int32_t* rq, int64_t nq,
-                 int dim, int prec, int32_t* pairs, float* d1, float* d2, int64_t cap, int64_t* n_pairs_host,
+                 int dim, int32_t* pairs, float* d1, float* d2, int64_t cap, int64_t* n_pairs_host,
                  int64_t* n_fallback_host, void* ws, size_t ws_bytes, hipStream_t s);
 
 // ---- tuning.hip -----------------------------------------------------------
@@ -494,7 +472,7 @@ struct Tuning {
     int count_queries = 2;    // queries per wavefront in the count pass (1, 2, 4)
     int spfh_pair_mean = 24;  // mean list length up to which SPFH takes two points per wavefront
     int fpfh_rows = 2;        // SPFH rows per unrolled step of the FPFH sum (1, 2, 4, 8, 16)
-    int band_tile = 0;        // partner chunks per band tile; 0 = the tile-length model's choice
+    int band_tile = 0;        // accepted, without effect
     int fuse_features = 0;    // 1: SPFH and FPFH in one persistent launch (per-cloud readiness counters)
     int xcd_split = 2;        // bit 0 SPFH, bit 1 FPFH: XCD-aware split of the points over the wavefronts
     int match_form = 0;       // 0: one-sided matching then the image back; 1: both directions in one pass
@@ -502,7 +480,7 @@ struct Tuning {
 };
 const Tuning& tuning();
 bool set_tuning(const Tuning& t);
-bool band_tile_candidate(int T);  // T is one of the band planner's candidate lengths
+bool band_tile_candidate(int T);  // lengths the band_tile field accepts
 
 // ---- batch.hip ------------------------------------------------------------
 size_t batch_ws(int n_pairs, int64_t raw_cap, int64_t nnz_cap, int H);
