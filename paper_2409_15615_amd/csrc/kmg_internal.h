@@ -80,7 +80,6 @@ struct MatchSet {
 struct SetPlan {
     int32_t n;           // rows
     int32_t base;        // first slot (slots of a set start on a 16-row chunk)
-    int32_t s_base;      // first row of the set's sample
     int32_t nq;          // queries of the phase (all rows, the image rows, or none)
     int32_t groups;      // 64-query groups of the phase
     int32_t grp_off;     // first of them
@@ -405,8 +404,10 @@ struct MatchWs {
     PairScale* pp;
     unsigned char* rows;   // packed integer rows, 128 bytes per slot
     int* half;             // per slot: minus half the squared norm, less one (INT_MIN: not in the sweep)
-    unsigned char* s_rows; // the samples, packed the same way
-    int* s_half;
+    float* nu;             // per slot: norm
+    float2* c_norm;        // per chunk: least and largest norm
+    int32_t* perm;         // per slot: the row (a set's slots are in norm order within 1,024-row tiles)
+    int32_t* inv;          // per row: its place in the set's slots
     int2* s_best;          // best and second raw score of every query over a sample segment
     float* err;            // per slot: rounding error in units of the scale (< 0: not in the sweep)
     int32_t* cnt;          // per slot: listed rows
@@ -416,7 +417,7 @@ struct MatchWs {
     int32_t* long_list;    // queries with long lists
     double* part;          // partial results of the exact scans
     int32_t* img_list;     // one-sided form: rows of the matching back, in their set's slots
-    int32_t* nn;           // per slot: nearest neighbour, and the two smallest squared distances
+    int32_t* nn;           // per row (at its set's base): nearest neighbour, and the two smallest squared distances
     double* best;
     double* second;
     int32_t* fb_part;      // queries decided on more than four exact scores, partial counts per set

@@ -15,12 +15,15 @@
 // l.l'; 32 bits hold every sum).  By the triangle inequality the true distance
 // lies within s (e + e') of s sqrt(Dq), so an upper bound of a query's second
 // nearest distance becomes a threshold on Dq that no row it needs exceeds:
-//   1. a sample of the partner's rows (every kStride-th) gives, per query, the
-//      second smallest Dq of the sample, and with it the bound;
-//   2. one sweep over all rows lists the few rows at or below the threshold
-//      (twice kStride of them, and the rows that rounding cannot tell apart);
+//   1. a sample of the partner's rows (one chunk in sample_stride) gives, per
+//      query, the second smallest Dq of the sample, and with it the bound;
+//   2. one sweep over the rows lists the few at or below the threshold (twice
+//      the stride of them, and the rows that rounding cannot tell apart);
 //   3. the listed Dq tighten the bound, and the rows that remain are scored
 //      with the plain FP64 sum of squared differences in dimension order.
+// Rows lie in order of their norm within tiles of 1,024: a row whose norm
+// differs from a query's by more than the bound is farther than it, so both
+// passes skip the chunks (16 rows) outside the band that their queries reach.
 // Rows whose norm leaves the range (a handful: the scale holds rows up to
 // kRangeRms times the root mean square norm) take no part in the integer
 // sweep: every query that such a row could reach scores them exactly, and as
@@ -30,6 +33,7 @@
 // Forms.  Both directions in full, or (large products) one-sided: the smaller
 // set of a pair against the larger, then only the rows that are some query's
 // nearest neighbour back.
+#include <float.h>
 #include <limits.h>
 #include <math.h>
 
@@ -62,6 +66,12 @@ constexpr int kLimb = 32639;        // largest |q|: 127 * 256 + 127
 constexpr int kMinCap = 16;         // listed rows per query the pool always holds
 constexpr int kMaxCap = 512;
 constexpr int kEmitTile = 1024;     // rows per block of the mutual test
+constexpr int kSortTile = 1024;     // rows ordered by norm together
+constexpr int kTileChunks = kSortTile / kTileRows;
+static_assert(kTileChunks == kWave, "a lane per chunk of a sort tile");
+// FP32 sums of up to 64 squares and a root, for a row and for the query, twice over
+constexpr float kNormSlack = 2e-5f;
+constexpr int kSortBlocks = 512;    // blocks that order rows
 constexpr int kRestBlocks = 1024;   // grid of score_rest
 constexpr int kFbParts = 16;        // counters per set of the queries decided on more than four scores
 
@@ -82,10 +92,14 @@ __device__ __forceinline__ const float* set_row(const MatchSet& s, int i, int di
 }
 
 // Sample stride of a set of n rows: a query's list holds about twice the
-// stride, the sample pass costs 1 / stride of the sweep.  Small sets, whose
-// sweep is short, take a denser sample; below 64 rows every row is in it, so
-// that it holds two rows whenever the set does.
-__host__ __device__ __forceinline__ int sample_stride(int n) { return n < 64 ? 1 : (n < 65536 ? 4 : 8); }
+// stride, the sample pass costs 1 / stride of the sweep; below 64 rows every row
+// is in the sample, so that it holds two rows whenever the set does.  Every
+// stride-th chunk of a sort tile is sampled, another one of four in each tile
+// (a chunk holds rows of about one norm).
+__host__ __device__ __forceinline__ int sample_stride(int n) { return n < 64 ? 1 : 4; }
+__device__ __forceinline__ bool in_sample(int chunk, int stride) {
+    return ((chunk + chunk / kTileChunks) & (stride - 1)) == 0;
+}
 
 // ------------------------------------------------------------------ plan --
 
@@ -141,7 +155,6 @@ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; 
 __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, MatchCtl* ctl, int* s_scan) {
     const int groups = (live && n_p > 0) ? ceil_div(nq, kGroup) : 0;
     const int chunks = ceil_div(n_p, kTileRows);
-    const int s_chunks = ceil_div(ceil_div(n_p, sample_stride(n_p)), kTileRows);
     int all[2] = {groups, static_cast<int>(min(static_cast<int64_t>(groups) * chunks, static_cast<int64_t>(1) << 40) >> 10)};
     int tot_all[2];
     block_scan_k<2>(all, tot_all, s_scan);
@@ -156,7 +169,7 @@ __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, M
     }
     const int want_s = all_groups > 0 ? kTileWaves / all_groups : 1;
     const int s_segs = min(max(want_s, 1), kMaxSampleSegs);
-    int v[3] = {groups, groups * min(s_segs, max(s_chunks, 1)), groups * ceil_div(chunks, depth)};
+    int v[3] = {groups, groups * min(s_segs, max(ceil_div(chunks, kTileChunks), 1)), groups * ceil_div(chunks, depth)};
     int tot[3];
     block_scan_k<3>(v, tot, s_scan);
     if (live) {
@@ -175,8 +188,95 @@ __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, M
     }
 }
 
+// The rows of each sort tile (1,024 rows of a set) in order of their norm about
+// zero: perm, inv, the slots' norms and the chunks' norm ranges.  A chunk so holds
+// rows of nearly one norm, and a query, whose nearest rows differ from it in norm
+// by no more than in distance, skips most chunks.  Needs neither the centre nor
+// the scale and so runs beside the plan: within the rounding it was a chain of its
+// own of 35 us, here it adds 5 us to the plan's 15.  An order over the whole set would save another third of the
+// sweep and take two launches more.  FP32 serves: the norms only bound, with a
+// margin for their rounding, what may be skipped.
+__device__ void order_rows(const MatchSet* sets, int n_sets, int dim, const SinglePair& single, int first, int step,
+                           const MatchWs& w) {
+    constexpr int kPerRound = kSortTile / 8;
+    __shared__ int s_scan[2 * (kPlanThreads / kWave)];
+    __shared__ int s_tile0[kPlanThreads], s_base[kPlanThreads], s_n[kPlanThreads];
+    __shared__ uint32_t s_key[kSortTile];
+    __shared__ float s_nu[kSortTile];
+    const bool by_value = single.on != 0;
+    const int t = threadIdx.x;
+    const int n = t >= n_sets ? 0 : (by_value ? (t ? single.nb : single.na) : *sets[t].n);
+    int v[2] = {ceil_div(n, kTileRows), ceil_div(n, kSortTile)}, tot[2];
+    block_scan_k<2>(v, tot, s_scan);
+    s_n[t] = n;
+    s_base[t] = v[0] * kTileRows;
+    s_tile0[t] = v[1];
+    __syncthreads();
+    const int j = t & 7;
+    for (int tile = first; tile < tot[1]; tile += step) {
+        const int c = find_set(n_sets, tile, [&](int s) { return static_cast<int64_t>(s_tile0[s]); });
+        const int e0 = (tile - s_tile0[c]) * kSortTile, cnt = min(kSortTile, s_n[c] - e0);
+        const int64_t base = s_base[c] + e0;
+        const MatchSet set = by_value ? (c ? single.b : single.a) : sets[c];
+#pragma unroll 4
+        for (int u = 0; u < kSortTile / kPerRound; ++u) {
+            const int r = u * kPerRound + t / 8;
+            float x2 = 0.0f;
+            if (r < cnt) {
+                const float* x = set_row(set, e0 + r, dim);
+#pragma unroll
+                for (int d = 0; d < 8; ++d) {
+                    const float xs = 8 * d + j < dim ? x[8 * d + j] : 0.0f;
+                    x2 = fmaf(xs, xs, x2);
+                }
+            }
+#pragma unroll
+            for (int d = 1; d < 8; d <<= 1) x2 += __shfl_xor(x2, d, 8);
+            if (j == 0) {
+                // clamping brings norms closer, if anything; NaN, in rows that take no part, is clamped too
+                const float nu = sqrtf(fminf(x2, FLT_MAX));
+                s_nu[r] = nu;
+                // 22 bits of the norm and the row: distinct keys (~0 for the places past the set's end)
+                s_key[r] = r >= cnt ? ~0u : ((__float_as_uint(nu) >> 9) << 10) | static_cast<uint32_t>(r);
+            }
+        }
+        __syncthreads();
+        // bitonic, a key per thread: partners closer than a wavefront trade through shuffles
+        uint32_t key = s_key[t];
+#pragma unroll 1
+        for (int k = 2; k <= kSortTile; k <<= 1) {
+#pragma unroll 1
+            for (int d = k >> 1; d > 0; d >>= 1) {
+                uint32_t o;
+                if (d >= kWave) {
+                    __syncthreads();
+                    s_key[t] = key;
+                    __syncthreads();
+                    o = s_key[t ^ d];
+                } else {
+                    o = __shfl_xor(key, d, kWave);
+                }
+                key = ((t & d) == 0) == ((t & k) == 0) ? min(key, o) : max(key, o);
+            }
+        }
+        if (t < cnt) {
+            const int row = static_cast<int>(key & 1023u);
+            const int64_t slot = base + t;
+            w.perm[slot] = e0 + row;
+            w.inv[base + row] = e0 + t;
+            w.nu[slot] = s_nu[row];
+            // the chunk's norms, by the first and last row's key
+            const uint32_t edge = key >> 10 << 9;
+            if (t % kTileRows == 0) w.c_norm[slot / kTileRows].x = __uint_as_float(edge) * (1.0f - kNormSlack);
+            if (t % kTileRows == kTileRows - 1 || t == cnt - 1)
+                w.c_norm[slot / kTileRows].y = __uint_as_float(edge + 512u) * (1.0f + kNormSlack);
+        }
+        __syncthreads();  // the tables are free for the next tile
+    }
+}
+
 // One launch: block 0 plans, block 1 + i finds the centre and the scale of
-// pair i.  With `single` the two sets come by value (and are written, with the
+// pair i, the rest order the rows.  With `single` the two sets come by value (and are written, with the
 // output record, for the kernels that follow); the status is then cleared too.
 //
 // Centre: the mean of kCentreRows rows at even strides over both sets, in a
@@ -184,8 +284,14 @@ __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, M
 // rounded); scale: kRangeRms root mean square norms about it span kRange.
 __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n_sets, int dim, int one_sided,
                                                            int64_t pool, SetPlan* plan, MatchCtl* ctl, PairScale* pp,
-                                                           SinglePair single, DevStatus* st) {
+                                                           SinglePair single, MatchWs w, DevStatus* st) {
     const bool by_value = single.on != 0;
+    const int n_pairs = n_sets / 2;
+    if (static_cast<int>(blockIdx.x) > n_pairs) {
+        order_rows(sets, n_sets, dim, single, static_cast<int>(blockIdx.x) - 1 - n_pairs,
+                   static_cast<int>(gridDim.x) - 1 - n_pairs, w);
+        return;
+    }
     if (blockIdx.x > 0) {
         constexpr int kGroups = kPlanThreads / kMaxMatchDim;  // 16 row groups of 64 dimensions
         constexpr int kPer = kCentreRows / kGroups;
@@ -260,19 +366,17 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
     const int n = !live ? 0 : (by_value ? (c ? single.nb : single.na) : *sets[c].n);
     const int n_p = !paired ? 0 : (by_value ? (c ? single.na : single.nb) : *sets[c ^ 1].n);
     const int chunks = ceil_div(n, kTileRows);
-    const int smp = ceil_div(ceil_div(n, sample_stride(n)), kTileRows);
     const int emit = (c & 1) ? 0 : (paired ? max(1, ceil_div(n, kEmitTile)) : 0);
-    int v[3] = {chunks, smp, emit};
-    int tot[3];
-    block_scan_k<3>(v, tot, s_scan);
+    int v[2] = {chunks, emit};
+    int tot[2];
+    block_scan_k<2>(v, tot, s_scan);
     // one buffer descriptor spans a set's packed rows: keep them below 2 GiB
     if (static_cast<int64_t>(chunks) * kTileRows * kRowBytes > INT32_MAX) st->err_capacity = 1;
     if (live) {
         SetPlan pl{};
         pl.n = n;
         pl.base = v[0] * kTileRows;
-        pl.s_base = v[1] * kTileRows;
-        pl.emit_off = v[2];
+        pl.emit_off = v[1];
         plan[c] = pl;
     }
     // one-sided: the larger set of each pair (the second on a tie) brings rows only
@@ -284,7 +388,7 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
     if (c == 0) {
         st->match_products = work;
         ctl->slots = tot[0] * kTileRows;
-        ctl->emit_tiles = tot[2];
+        ctl->emit_tiles = tot[1];
         // whole 128-byte lines, an odd number of them: with lists a power of two apart the first
         // lines of all lists fall on the same memory channels
         const int64_t cap = pool / max(tot[0] * kTileRows, 1);
@@ -326,8 +430,7 @@ __device__ __forceinline__ int64_t piece_at(int64_t row, int half, int g) {
 }
 
 // Eight lanes per row (lane j: dimensions 8 j .. 8 j + 7): the row's bytes, its
-// norm and rounding error, into its slot and, for every sample_stride-th row,
-// into the sample.  Also readies the slot for the passes that follow.
+// norm and rounding error, into its slot.  Also readies the slot for the passes that follow.
 // Bound by the descriptors' reads and the packed rows' writes (4 dim + 160
 // bytes a row).
 __global__ __launch_bounds__(kBlock) void match_round(const MatchSet* __restrict__ sets, SetPlan* plan, int n_sets,
@@ -340,14 +443,11 @@ __global__ __launch_bounds__(kBlock) void match_round(const MatchSet* __restrict
     for (int64_t k = tid; k < slots / kWave + n_sets + 1; k += gs) w.grp_done[k] = 0;
     for (int64_t k = tid; k < n_sets * kFbParts; k += gs) w.fb_part[k] = 0;
     const int j = threadIdx.x & 7;
-    const auto put = [&](unsigned char* rows, int64_t row, const uint2& h, const uint2& l) {
-        *reinterpret_cast<uint2*>(rows + piece_at(row, 0, j >> 1) + 8 * (j & 1)) = h;
-        *reinterpret_cast<uint2*>(rows + piece_at(row, 1, j >> 1) + 8 * (j & 1)) = l;
-    };
     for (int64_t slot = tid / 8; slot < slots; slot += gs / 8) {
         const int c = find_set(n_sets, slot, [&](int s) { return static_cast<int64_t>(plan[s].base); });
-        const int n = plan[c].n, i = static_cast<int>(slot) - plan[c].base;
-        const bool row = i < n;
+        const int at = static_cast<int>(slot) - plan[c].base;
+        const bool row = at < plan[c].n;
+        const int i = row ? w.perm[slot] : 0;
         const double s = pp[c >> 1].scale, inv = pp[c >> 1].inv;
         uint2 vh = make_uint2(0u, 0u), vl = make_uint2(0u, 0u);
         unsigned long long n2 = 0ull;
@@ -387,24 +487,12 @@ __global__ __launch_bounds__(kBlock) void match_round(const MatchSet* __restrict
         const bool out = row && !(ok && static_cast<double>(n2) <= kRange * kRange);
         if (out) vh = vl = make_uint2(0u, 0u);
         const int hn = row && !out ? half_norm(static_cast<uint32_t>(n2)) : kNoRow;
-        const int st = sample_stride(n);
-        put(w.rows, slot, vh, vl);
-        if (row && i % st == 0) {
-            const int64_t at = plan[c].s_base + i / st;
-            put(w.s_rows, at, vh, vl);
-            if (j == 0) w.s_half[at] = hn;
-        }
-        if (row && i == n - 1) {  // the padding of the sample's last chunk
-            const int smp = ceil_div(n, st);
-            for (int k = smp; k < ceil_div(smp, kTileRows) * kTileRows; ++k) {
-                put(w.s_rows, plan[c].s_base + k, make_uint2(0u, 0u), make_uint2(0u, 0u));
-                if (j == 0) w.s_half[plan[c].s_base + k] = kNoRow;
-            }
-        }
+        *reinterpret_cast<uint2*>(w.rows + piece_at(slot, 0, j >> 1) + 8 * (j & 1)) = vh;
+        *reinterpret_cast<uint2*>(w.rows + piece_at(slot, 1, j >> 1) + 8 * (j & 1)) = vl;
         if (j == 0) {
             w.half[slot] = hn;
             w.cnt[slot] = 0;
-            w.nn[slot] = -1;
+            if (row) w.nn[plan[c].base + i] = -1;
             // rounded up: the residuals come from a handful of FP64 roundings; < 0: not in the sweep
             w.err[slot] = row && !out ? static_cast<float>(sqrt(e2) * (1.0 + 1e-6)) + 1e-4f : -1.0f;
             if (out) w.out_list[plan[c].base + atomicAdd(&plan[c].n_out, 1)] = i;
@@ -483,6 +571,19 @@ __device__ __forceinline__ QueryRegs load_queries(const SetPlan& qc, const int32
     return q;
 }
 
+// Raw scores of a chunk's 16 rows against one 16-query tile: lane l holds
+// column l % 16 and rows 4 (l / 16) + 0..3.
+__device__ __forceinline__ i32x4 tile_scores(const ChunkRegs& a, const i32x4& qh, const i32x4& ql) {
+    i32x4 w = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.h, qh, i32x4{0, 0, 0, 0}, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w[r] = static_cast<int>(static_cast<uint32_t>(w[r]) << 8);
+    w = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.h, ql, w, 0, 0, 0);
+    w = __builtin_amdgcn_mfma_i32_16x16x64_i8(a.l, qh, w, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w[r] = static_cast<int>((static_cast<uint32_t>(w[r]) << 8) + static_cast<uint32_t>(a.n[r]));
+    return __builtin_amdgcn_mfma_i32_16x16x64_i8(a.l, ql, w, 0, 0, 0);
+}
+
 // Raw scores of a chunk's 16 rows against the four 16-query tiles: lane l
 // holds column l % 16 and rows 4 (l / 16) + 0..3 of each.  The partial sums go
 // through the products' accumulators, shifted between them (all sums modulo
@@ -509,27 +610,42 @@ __device__ __forceinline__ void group_scores(const ChunkRegs& a, const QueryRegs
     }
 }
 
-// Runs use(chunk registers, chunk) over the chunks [c0, c1), the next chunk's
-// loads ahead of its use.  (A second chunk ahead, in a loop of three register
-// sets, was no faster: the loop is bound by issue, not by the loads.)
+// Runs use(chunk registers, chunk) over the chunks base + (set bits of todo),
+// the next chunk's loads ahead of its use.  (A second chunk ahead, in a loop of
+// three register sets, was no faster: the loop is bound by issue, not by the
+// loads.)
 template <class F>
-__device__ __forceinline__ void for_chunks(const RowBuf& b, int c0, int c1, int lane, F use) {
-    ChunkRegs next = load_chunk(b, c0, lane);
-    for (int k = c0; k < c1; ++k) {
+__device__ __forceinline__ void for_chunks(const RowBuf& b, int base, uint64_t todo, int lane, F use) {
+    if (!todo) return;  // uniform
+    int k = base + __builtin_ctzll(todo);
+    ChunkRegs next = load_chunk(b, k, lane);
+    do {
+        todo &= todo - 1;
+        const int kn = todo ? base + __builtin_ctzll(todo) : k;
         const ChunkRegs a = next;
-        next = load_chunk(b, min(k + 1, c1 - 1), lane);
+        next = load_chunk(b, kn, lane);
         __builtin_amdgcn_sched_barrier(0);
         use(a, k);
         __builtin_amdgcn_sched_barrier(0);
-    }
+        k = kn;
+    } while (todo);
+}
+
+// How far the nearest rows of a query can lie, given a score that two rows
+// reach and the summed rounding errors, in the descriptors' units, rounded up.
+__device__ __forceinline__ float reach_of(int w2, double e, double scale) {
+    if (w2 == kNoRow) return INFINITY;
+    return static_cast<float>((sqrt(score_d2(w2) + 2.0) + e) * scale * (1.0 + 1e-6) + 1e-18);  // and squares that underflow
 }
 
 __device__ __forceinline__ int med3(int a, int b, int c) { return max(min(a, b), min(max(a, b), c)); }
 
-// Best and second best raw score of every query over a segment of the sample.
+// Best and second best raw score of every query over a segment of the sample
+// (whole sort tiles).  Of each sort tile the chunks in the group's own norm range
+// go first; what they find limits the norms at which the rest can matter.
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sample_tiles(
-    const SetPlan* __restrict__ plan, int n_sets, const int32_t* __restrict__ list, MatchWs w,
-    const MatchCtl* __restrict__ ctl, const DevStatus* __restrict__ st) {
+    const SetPlan* __restrict__ plan, int n_sets, int dim, const int32_t* __restrict__ list,
+    const PairScale* __restrict__ pp, MatchWs w, const MatchCtl* __restrict__ ctl, const DevStatus* __restrict__ st) {
     const int lane = lane_id();
     const int total = st->err_capacity ? 0 : ctl->s_tiles;
     for (int tile = static_cast<int>(blockIdx.x) * kWavesPerBlock + static_cast<int>(threadIdx.x / kWave);
@@ -537,18 +653,46 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         const int tu = __builtin_amdgcn_readfirstlane(tile);
         const int c = find_set(n_sets, tu, [&](int s) { return static_cast<int64_t>(plan[s].s_tile_off); });
         const SetPlan qc = plan[c], pc = plan[c ^ 1];
-        const int chunks = ceil_div(ceil_div(pc.n, sample_stride(pc.n)), kTileRows);
-        const int segs = min(ctl->s_segs, chunks);
+        const int chunks = ceil_div(pc.n, kTileRows), tiles = max(ceil_div(chunks, kTileChunks), 1);
+        const int segs = min(ctl->s_segs, tiles);
+        const int stride = sample_stride(pc.n);
         const int local = tu - qc.s_tile_off;
         const int g = local % qc.groups, sg = local / qc.groups;
-        const int c0 = static_cast<int>(static_cast<int64_t>(chunks) * sg / segs);
-        const int c1 = static_cast<int>(static_cast<int64_t>(chunks) * (sg + 1) / segs);
-        const RowBuf b = row_buf(w.s_rows, w.s_half, pc.s_base, chunks);
+        const int t0 = static_cast<int>(static_cast<int64_t>(tiles) * sg / segs);
+        const int t1 = static_cast<int>(static_cast<int64_t>(tiles) * (sg + 1) / segs);
+        const RowBuf b = row_buf(w.rows, w.half, pc.base, chunks);
         const QueryRegs q = load_queries(qc, list, g, w.rows, lane);
+        // the norms of the group and of each 16 queries (those out of range left out), and the
+        // queries' half norms by column
+        float lo[kTilesPerWave], hi[kTilesPerWave];
+        int own[kTilesPerWave];
+        {
+            const int i = g * kGroup + lane;
+            const int slot = list ? list[qc.base + min(i, qc.nq - 1)] : qc.base + min(i, qc.nq - 1);
+            const bool act = i < qc.nq && w.err[slot] >= 0.0f;
+            const float nu = w.nu[slot];
+            const int half = w.half[slot];
+            float l = act ? nu * (1.0f - kNormSlack) : INFINITY, h = act ? nu * (1.0f + kNormSlack) : -INFINITY;
+#pragma unroll
+            for (int d = 1; d < kTileCols; d <<= 1) {
+                l = fminf(l, __shfl_xor(l, d, kWave));
+                h = fmaxf(h, __shfl_xor(h, d, kWave));
+            }
+            const int o = act ? half + 1 : kNoRow;
+#pragma unroll
+            for (int t = 0; t < kTilesPerWave; ++t) {
+                own[t] = __shfl(o, t * kTileCols + (lane & 15), kWave);
+                lo[t] = __shfl(l, t * kTileCols, kWave);
+                hi[t] = __shfl(h, t * kTileCols, kWave);
+            }
+        }
+        const float lo_g = fminf(fminf(lo[0], lo[1]), fminf(lo[2], lo[3]));
+        const float hi_g = fmaxf(fmaxf(hi[0], hi[1]), fmaxf(hi[2], hi[3]));
+        const double scale = pp[c >> 1].scale;
         int m1[kTilesPerWave], m2[kTilesPerWave];
 #pragma unroll
         for (int t = 0; t < kTilesPerWave; ++t) m1[t] = m2[t] = kNoRow;
-        for_chunks(b, c0, c1, lane, [&](const ChunkRegs& a, int) {
+        const auto see = [&](const ChunkRegs& a, int) {
             i32x4 s[kTilesPerWave];
             group_scores(a, q, s);
 #pragma unroll
@@ -559,7 +703,53 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     m1[t] = max(m1[t], s[t][r]);
                 }
             }
-        });
+        };
+        // the chunks of sort tile tl in the sample, and their norms
+        const auto chunk_norms = [&](int tl, bool& have) {
+            const int k = tl * kTileChunks + lane;
+            have = k < chunks && in_sample(k, stride);
+            return w.c_norm[pc.base / kTileRows + max(min(k, chunks - 1), 0)];
+        };
+        const auto near_of = [&](const float2& cn, bool have) { return ballot(have && cn.x <= hi_g && cn.y >= lo_g); };
+        for (int tl = t0; tl < t1; ++tl) {
+            bool have;
+            const float2 cn = chunk_norms(tl, have);
+            for_chunks(b, tl * kTileChunks, near_of(cn, have), lane, see);
+        }
+        for (int tl = t0; tl < t1; ++tl) {
+            bool have;
+            const float2 cn = chunk_norms(tl, have);
+            // the farthest that a query of each 16 may have to look, by what its column knows
+            uint64_t need[kTilesPerWave];
+#pragma unroll
+            for (int t = 0; t < kTilesPerWave; ++t) {
+                int a1 = m1[t], a2 = m2[t];
+#pragma unroll
+                for (int d = 16; d < kWave; d <<= 1) {
+                    const int o1 = __shfl_xor(a1, d, kWave), o2 = __shfl_xor(a2, d, kWave);
+                    a2 = max(min(a1, o1), max(a2, o2));
+                    a1 = max(a1, o1);
+                }
+                int least = own[t] == kNoRow ? INT_MAX : (a2 == kNoRow ? kNoRow : a2 + own[t]);
+#pragma unroll
+                for (int d = 1; d < kTileCols; d <<= 1) least = min(least, __shfl_xor(least, d, kWave));
+                const float reach = least == INT_MAX ? 0.0f : reach_of(least, 2.0 * most_err(dim), scale);
+                need[t] = ballot(have && cn.x <= hi[t] + reach && cn.y >= lo[t] - reach);
+            }
+            const uint64_t rest = ((need[0] | need[1]) | (need[2] | need[3])) & ~near_of(cn, have);
+            for_chunks(b, tl * kTileChunks, rest, lane, [&](const ChunkRegs& a, int k) {
+#pragma unroll
+                for (int t = 0; t < kTilesPerWave; ++t) {
+                    if (!((need[t] >> (k - tl * kTileChunks)) & 1)) continue;  // uniform
+                    const i32x4 s = tile_scores(a, q.h[t], q.l[t]);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        m2[t] = med3(m1[t], m2[t], s[r]);
+                        m1[t] = max(m1[t], s[r]);
+                    }
+                }
+            });
+        }
         // the four row groups of a column
 #pragma unroll
         for (int t = 0; t < kTilesPerWave; ++t) {
@@ -576,22 +766,27 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     }
 }
 
-constexpr int kStage = 512;  // hits a wavefront gathers in LDS before it hands them out
+constexpr int kStage = 384;  // hits a wavefront gathers in LDS before it hands them out
 
 // The sweep: every row at or above a query's least score goes to the query's
-// list (row, raw score).  Bound by the matrix unit (256 cycles per chunk and
-// 64 queries) and, at a little less, by the vector instructions beside it,
-// which overlap across the four wavefronts of a SIMD.  A chunk in two has a hit;
-// hits gather in LDS, and are handed out up to kStage at a time: ranked per
-// query in LDS, with one global atomic per query (they cost a latency each time,
-// and one per hit, on the few counters of a dense run, several).  Consecutive
-// tiles sweep the same run of chunks for consecutive groups, so the run is read
-// from cache; loads run two chunks ahead.
+// list (row, raw score).  Chunks whose norms no query of a 16-query tile can
+// reach are passed over, without their loads where no tile of the group needs
+// them: a scan pair keeps a sixth to a quarter of the products, indoor rooms a
+// quarter to two fifths (18,000 rows both ways: 150 us -> 101 us; two sets of
+// 100,000: 3.5 ms -> 2.0 ms).  A chunk that all four tiles need runs their products
+// interleaved.  What is left is dense in hits: a lane's four scores go to LDS as
+// they are (one write per lane with a hit; sorting the single hits out on the
+// spot was a quarter of the time, 101 us -> 78 us) and are handed out when the
+// stage is full: ranked per query in LDS, with one global atomic per query.
+// Consecutive tiles sweep the same run of chunks for consecutive groups, so the
+// run is read from cache; loads run a chunk ahead.
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sweep_tiles(
-    const SetPlan* __restrict__ plan, int n_sets, int dim, const int32_t* __restrict__ list, MatchWs w,
-    const MatchCtl* __restrict__ ctl, const DevStatus* __restrict__ st) {
-    __shared__ uint2 s_hit[kWavesPerBlock][kStage];
-    __shared__ uint16_t s_rank[kWavesPerBlock][kStage];
+    const SetPlan* __restrict__ plan, int n_sets, int dim, const int32_t* __restrict__ list,
+    const PairScale* __restrict__ pp, MatchWs w, const MatchCtl* __restrict__ ctl, const DevStatus* __restrict__ st) {
+    __shared__ i32x4 s_hit[kWavesPerBlock][kStage];     // a lane's four scores,
+    __shared__ uint32_t s_at[kWavesPerBlock][kStage];   // their first row and column,
+    __shared__ uint16_t s_rank[kWavesPerBlock][kStage]; // and the place of the first in its list
+    __shared__ int s_least[kWavesPerBlock][kGroup];
     __shared__ int s_cnt[kWavesPerBlock][kGroup];
     __shared__ int s_slot[kWavesPerBlock][kGroup];
     const int lane = lane_id();
@@ -609,7 +804,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         const int c0 = sg * depth, c1 = min(c0 + depth, chunks);
         const RowBuf b = row_buf(w.rows, w.half, pc.base, chunks);
         const QueryRegs q = load_queries(qc, list, g, w.rows, lane);
-        const int s_segs = min(ctl->s_segs, ceil_div(ceil_div(pc.n, sample_stride(pc.n)), kTileRows));
+        const int s_segs = min(ctl->s_segs, ceil_div(chunks, kTileChunks));
         // query `lane` of the group: its slot and the least raw score of a row that it may need
         // (the sample's partials, all in flight; the chain per tile column took 13 us)
         const int iq = g * kGroup + lane;
@@ -627,73 +822,104 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             m2 = max(min(m1, part[k].x), max(m2, part[k].y));
             m1 = max(m1, part[k].x);
         }
+        const bool act = iq < qc.nq && err >= 0.0f;
+        const int w2 = m2 == kNoRow ? m2 : m2 + own;
+        const double e = static_cast<double>(err) + e_rows;
         // never below the score of a row that takes no part
-        const int least_l = iq < qc.nq && err >= 0.0f
-                                ? max(least_score(m2 == kNoRow ? m2 : m2 + own, static_cast<double>(err) + e_rows) - own,
-                                      INT_MIN + 1)
-                                : INT_MAX;
+        const int least_l = act ? max(least_score(w2, e) - own, INT_MIN + 1) : INT_MAX;
         int least[kTilesPerWave];
 #pragma unroll
         for (int t = 0; t < kTilesPerWave; ++t) least[t] = __shfl(least_l, t * kTileCols + (lane & 15), kWave);
+        // the norms that each 16-query tile may need, and the chunks of the run that hold some
+        const float nu = w.nu[slot_l], reach = reach_of(w2, e, pp[c >> 1].scale);
+        float lo = act ? nu * (1.0f - kNormSlack) - reach : INFINITY, hi = act ? nu * (1.0f + kNormSlack) + reach : -INFINITY;
+#pragma unroll
+        for (int d = 1; d < kTileCols; d <<= 1) {
+            lo = fminf(lo, __shfl_xor(lo, d, kWave));
+            hi = fmaxf(hi, __shfl_xor(hi, d, kWave));
+        }
+        s_least[wv][lane] = least_l;
+        s_slot[wv][lane] = slot_l;
         int n_hit = 0;
         const auto hand_out = [&]() {
             s_cnt[wv][lane] = 0;
             __builtin_amdgcn_wave_barrier();
 #pragma unroll 1
-            for (int k = lane; k < n_hit; k += kWave)
-                s_rank[wv][k] = static_cast<uint16_t>(atomicAdd(&s_cnt[wv][s_hit[wv][k].x >> 26], 1));
+            for (int k = lane; k < n_hit; k += kWave) {
+                const int col = static_cast<int>(s_at[wv][k] >> 26);
+                const i32x4 v = s_hit[wv][k];
+                const int lt = s_least[wv][col];
+                s_rank[wv][k] = static_cast<uint16_t>(
+                    atomicAdd(&s_cnt[wv][col], (v[0] >= lt) + (v[1] >= lt) + (v[2] >= lt) + (v[3] >= lt)));
+            }
             __builtin_amdgcn_wave_barrier();
             const int mine = s_cnt[wv][lane];
             s_cnt[wv][lane] = mine ? atomicAdd(&w.cnt[slot_l], mine) : 0;
-            s_slot[wv][lane] = slot_l;
             __builtin_amdgcn_wave_barrier();
 #pragma unroll 1
             for (int k = lane; k < n_hit; k += kWave) {
-                const uint2 h = s_hit[wv][k];
-                const int col = static_cast<int>(h.x >> 26);
-                const int at = s_cnt[wv][col] + s_rank[wv][k];
-                if (at < cap)
-                    w.pool[static_cast<int64_t>(s_slot[wv][col]) * cap + at] = make_uint2(h.x & 0x3ffffffu, h.y);
+                const uint32_t where = s_at[wv][k];
+                const int col = static_cast<int>(where >> 26);
+                const i32x4 v = s_hit[wv][k];
+                const int lt = s_least[wv][col];
+                int at = s_cnt[wv][col] + s_rank[wv][k];
+                uint2* out = w.pool + static_cast<int64_t>(s_slot[wv][col]) * cap;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    if (v[r] < lt) continue;
+                    if (at < cap) out[at] = make_uint2((where & 0x3ffffffu) + r, static_cast<uint32_t>(v[r]));
+                    ++at;
+                }
             }
             __builtin_amdgcn_wave_barrier();
             n_hit = 0;
         };
-        for_chunks(b, c0, c1, lane, [&](const ChunkRegs& a, int k) {
-            i32x4 s[kTilesPerWave];
-            group_scores(a, q, s);
-            uint64_t has[kTilesPerWave];
+        for (int k0 = c0; k0 < c1; k0 += kWave) {
+            // the chunks that each 16 queries need
+            uint64_t need[kTilesPerWave];
+            {
+                const float2 cn = w.c_norm[pc.base / kTileRows + min(k0 + lane, c1 - 1)];
 #pragma unroll
-            for (int t = 0; t < kTilesPerWave; ++t)
-                has[t] = ballot(max(max(s[t][0], s[t][1]), max(s[t][2], s[t][3])) >= least[t]);
-            if ((has[0] | has[1]) | (has[2] | has[3])) {
-                // rare, and kept small: one copy of the code for the four tiles
-                const uint32_t row = static_cast<uint32_t>(k * kTileRows + 4 * (lane >> 4));
-#pragma unroll 1
                 for (int t = 0; t < kTilesPerWave; ++t) {
-                    const uint64_t any = t == 0 ? has[0] : (t == 1 ? has[1] : (t == 2 ? has[2] : has[3]));
-                    if (!any) continue;  // uniform
-                    i32x4 v = s[0];
-                    int lt = least[0];
-#pragma unroll
-                    for (int u = 1; u < kTilesPerWave; ++u) {
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) v[r] = t == u ? s[u][r] : v[r];
-                        lt = t == u ? least[u] : lt;
-                    }
-                    if (n_hit > kStage - 4 * kWave) hand_out();
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const bool hit = v[r] >= lt;
-                        const uint64_t m = ballot(hit);
-                        if (hit)
-                            s_hit[wv][n_hit + lanes_below(m)] =
-                                make_uint2((row + r) | (static_cast<uint32_t>(t * kTileCols + (lane & 15)) << 26),
-                                           static_cast<uint32_t>(v[r]));
-                        n_hit += __popcll(m);
-                    }
+                    const float tl = __shfl(lo, t * kTileCols, kWave), th = __shfl(hi, t * kTileCols, kWave);
+                    need[t] = ballot(k0 + lane < c1 && cn.x <= th && cn.y >= tl);
                 }
             }
-        });
+            const uint64_t all = (need[0] & need[1]) & (need[2] & need[3]);
+            for_chunks(b, k0, (need[0] | need[1]) | (need[2] | need[3]), lane, [&](const ChunkRegs& a, int k) {
+                i32x4 s[kTilesPerWave];
+                uint64_t has[kTilesPerWave];
+                if ((all >> (k - k0)) & 1) {
+                    group_scores(a, q, s);
+#pragma unroll
+                    for (int t = 0; t < kTilesPerWave; ++t)
+                        has[t] = ballot(max(max(s[t][0], s[t][1]), max(s[t][2], s[t][3])) >= least[t]);
+                } else {
+#pragma unroll
+                    for (int t = 0; t < kTilesPerWave; ++t) {
+                        has[t] = 0ull;
+                        if (!((need[t] >> (k - k0)) & 1)) continue;  // uniform
+                        s[t] = tile_scores(a, q.h[t], q.l[t]);
+                        has[t] = ballot(max(max(s[t][0], s[t][1]), max(s[t][2], s[t][3])) >= least[t]);
+                    }
+                }
+                if ((has[0] | has[1]) | (has[2] | has[3])) {
+                    const uint32_t where =
+                        static_cast<uint32_t>(k * kTileRows + 4 * (lane >> 4)) | (static_cast<uint32_t>(lane & 15) << 26);
+#pragma unroll
+                    for (int t = 0; t < kTilesPerWave; ++t) {
+                        if (!has[t]) continue;  // uniform
+                        if ((has[t] >> lane) & 1) {
+                            const int at = n_hit + lanes_below(has[t]);
+                            s_hit[wv][at] = s[t];
+                            s_at[wv][at] = where + (static_cast<uint32_t>(t * kTileCols) << 26);
+                        }
+                        n_hit += __popcll(has[t]);
+                    }
+                    if (n_hit > kStage - kTilesPerWave * kWave) hand_out();
+                }
+            });
+        }
         if (n_hit) hand_out();
     }
 }
@@ -778,7 +1004,8 @@ __device__ __forceinline__ Nearest score_query(const MatchSet& qs, const MatchSe
     }
     const int least =
         max(least_score(m2 == kNoRow ? m2 : m2 + own, e + most_err(dim)) - own, INT_MIN + 1);
-    const float* y = set_row(qs, static_cast<int>(slot) - qc.base, dim);
+    const float* y = set_row(qs, w.perm[slot], dim);
+    const int32_t* perm = w.perm + pc.base;  // listed rows are places in the norm order
     Nearest o{INFINITY, INFINITY, INT_MAX, 0};
     const auto take = [&](int j) {
         const double d = exact_d2(set_row(ps, j, dim), y, dim);
@@ -794,13 +1021,13 @@ __device__ __forceinline__ Nearest score_query(const MatchSet& qs, const MatchSe
     for (int u = 0; u < kRegList; ++u)
         if (static_cast<int>(ent[u].y) >= least) {
             ++o.scored;
-            take(static_cast<int>(ent[u].x));
+            take(perm[ent[u].x]);
         }
     for (int k = kRegList * W + gl; k < m; k += W) {
         const uint2 en = src[k];
         if (static_cast<int>(en.y) < least) continue;
         ++o.scored;
-        take(static_cast<int>(en.x));
+        take(perm[en.x]);
     }
     const auto merge = [&]() {
 #pragma unroll
@@ -872,9 +1099,10 @@ __global__ __launch_bounds__(kBlock) void score_lists(const MatchSet* __restrict
                 const Nearest o = score_query<kScoreLanes>(sets[c], sets[c ^ 1], qc, pc, dim, pp[c >> 1].scale, w, slot,
                                                            found, cap, gl);
                 if (gl == 0) {
-                    w.nn[slot] = o.j1 == INT_MAX ? -1 : o.j1;
-                    w.best[slot] = o.b1;
-                    w.second[slot] = o.b2;
+                    const int64_t at = qc.base + w.perm[slot];
+                    w.nn[at] = o.j1 == INT_MAX ? -1 : o.j1;
+                    w.best[at] = o.b1;
+                    w.second[at] = o.b2;
                     if (o.scored > 4) atomicAdd(&s_more, 1);
                 }
             }
@@ -935,9 +1163,10 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
         const Nearest o = score_query<kWave>(sets[c], sets[c ^ 1], plan[c], plan[c ^ 1], dim, pp[c >> 1].scale, w, slot,
                                              w.cnt[slot], ctl->cap, L);
         if (L == 0) {
-            w.nn[slot] = o.j1 == INT_MAX ? -1 : o.j1;
-            w.best[slot] = o.b1;
-            w.second[slot] = o.b2;
+            const int64_t at = plan[c].base + w.perm[slot];
+            w.nn[at] = o.j1 == INT_MAX ? -1 : o.j1;
+            w.best[at] = o.b1;
+            w.second[at] = o.b2;
             if (o.scored > 4) atomicAdd(&w.fb_part[c * kFbParts + k % kFbParts], 1);
         }
     }
@@ -955,7 +1184,8 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
             const int64_t slot = w.long_list[w.slot_cap - 1 - f];
             const int c = find_set(n_sets, slot, [&](int s) { return static_cast<int64_t>(plan[s].base); });
             const MatchSet ps = sets[c ^ 1];
-            const float* y = set_row(sets[c], static_cast<int>(slot) - plan[c].base, dim);
+            const int row = w.perm[slot];
+            const float* y = set_row(sets[c], row, dim);
             const int np = plan[c ^ 1].n, len = (np + S - 1) / S;
             const int end = min(np, (sg + 1) * len);
             double b1 = INFINITY, b2 = INFINITY;
@@ -999,9 +1229,10 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
             }
             merge();
             if (L == 0) {
-                w.nn[slot] = j1 == INT_MAX ? -1 : j1;
-                w.best[slot] = b1;
-                w.second[slot] = b2;
+                const int64_t at = plan[c].base + row;
+                w.nn[at] = j1 == INT_MAX ? -1 : j1;
+                w.best[at] = b1;
+                w.second[at] = b2;
             }
         }
         return;
@@ -1055,7 +1286,7 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
         const int64_t slot = have ? w.fb_list[plan[c].base + local] : plan[c].base;
         double y[kD];
         {
-            const float* yr = set_row(sets[c], static_cast<int>(slot - plan[c].base), dim);
+            const float* yr = set_row(sets[c], w.perm[slot], dim);
 #pragma unroll
             for (int t = 0; t < kD; ++t) {
                 const double v = yr[min(t, dim - 1)];  // never predicated: all loads in flight
@@ -1168,9 +1399,10 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
                 for (int o = 1; o < kWaves; ++o)
                     combine_best(b1, j1, b2, s_b1[o * kWave + L], s_j1[o * kWave + L], s_b2[o * kWave + L]);
                 if (have) {
-                    w.nn[slot] = (j1 == INT_MAX) ? -1 : j1;
-                    w.best[slot] = b1;
-                    w.second[slot] = b2;
+                    const int64_t at = plan[c].base + w.perm[slot];
+                    w.nn[at] = (j1 == INT_MAX) ? -1 : j1;
+                    w.best[at] = b1;
+                    w.second[at] = b2;
                 }
                 if (L == 0) w.grp_done[g] = 0;  // ready for a later scan on this workspace
             }
@@ -1201,7 +1433,7 @@ __global__ __launch_bounds__(kBlock) void image_lists(SetPlan* plan, int n_sets,
             const int c = find_set(n_sets, slot, [&](int s) { return static_cast<int64_t>(plan[s].base); });
             const int i = static_cast<int>(slot) - plan[c].base;
             if (i < plan[c].nq && (c ^ 1) < n_sets) {
-                j = w.nn[slot];
+                j = w.nn[plan[c].base + w.perm[slot]];  // in norm order, so that the images come in it too
                 p = c ^ 1;
                 if (j >= 0) claim = atomicCAS(&w.nn[plan[p].base + j], -1, -2) == -1;
             }
@@ -1218,7 +1450,7 @@ __global__ __launch_bounds__(kBlock) void image_lists(SetPlan* plan, int n_sets,
             if (claim && p == pl) k = at + lanes_below(same);
             pending &= ~same;
         }
-        if (claim) w.img_list[plan[p].base + k] = plan[p].base + j;
+        if (claim) w.img_list[plan[p].base + k] = plan[p].base + w.inv[plan[p].base + j];
     }
 }
 
@@ -1320,16 +1552,16 @@ MatchWs carve_match(Carver& c, int n_sets, int64_t q_cap, int dim) {
     w.n_sets = n_sets;
     // every set starts on a chunk
     w.slot_cap = w.q_cap + static_cast<int64_t>(n_sets) * kTileRows;
-    // the sample of a set: a quarter of it, or all of it below 64 rows, in whole chunks
-    const int64_t s_cap = w.q_cap / 4 + static_cast<int64_t>(n_sets) * (64 + kTileRows);
     const int64_t grp_cap = w.q_cap / kGroup + n_sets;
     w.ctl = c.take<MatchCtl>(1);
     w.plan = c.take<SetPlan>(static_cast<size_t>(std::max(n_sets, 1)));
     w.pp = c.take<PairScale>(static_cast<size_t>(n_sets / 2 + 1));
     w.rows = c.take<unsigned char>(static_cast<size_t>(w.slot_cap) * kRowBytes);
     w.half = c.take<int>(static_cast<size_t>(w.slot_cap));
-    w.s_rows = c.take<unsigned char>(static_cast<size_t>(s_cap) * kRowBytes);
-    w.s_half = c.take<int>(static_cast<size_t>(s_cap));
+    w.nu = c.take<float>(static_cast<size_t>(w.slot_cap));
+    w.c_norm = c.take<float2>(static_cast<size_t>(w.slot_cap / kTileRows + 1));
+    w.perm = c.take<int32_t>(static_cast<size_t>(w.slot_cap));
+    w.inv = c.take<int32_t>(static_cast<size_t>(w.slot_cap));
     // s_segs <= max(1, kTileWaves / groups): at most kTileWaves groups of partials, or one each
     w.s_best = c.take<int2>(static_cast<size_t>(std::max<int64_t>(grp_cap, kTileWaves)) * kGroup);
     w.err = c.take<float>(static_cast<size_t>(w.slot_cap));
@@ -1361,9 +1593,9 @@ kmg_status match_queries(const MatchSet* sets, int n_sets, int dim, const int32_
                          const MatchWs& w, hipStream_t s) {
     {
         StageScope sc(ST_MATCH_TOPK, s);
-        sample_tiles<<<kTileBlocks, kBlock, 0, s>>>(w.plan, n_sets, list, w, w.ctl, st);
+        sample_tiles<<<kTileBlocks, kBlock, 0, s>>>(w.plan, n_sets, dim, list, w.pp, w, w.ctl, st);
         KMG_TRY(launch_status());
-        sweep_tiles<<<kTileBlocks, kBlock, 0, s>>>(w.plan, n_sets, dim, list, w, w.ctl, st);
+        sweep_tiles<<<kTileBlocks, kBlock, 0, s>>>(w.plan, n_sets, dim, list, w.pp, w, w.ctl, st);
         KMG_TRY(launch_status());
         timer_note_work(&st->match_products);
     }
@@ -1388,8 +1620,9 @@ kmg_status match_sets(MatchSet* sets, int n_sets, int dim, int64_t products, con
     const bool one_sided = tuning().match_form == 0 && products > kOneSidedProducts;
     {
         StageScope sc(ST_MATCH_PACK, s);
-        match_plan<<<1 + n_sets / 2, kPlanThreads, 0, s>>>(sets, n_sets, dim, one_sided ? 1 : 0, w.pool_cap, w.plan,
-                                                           w.ctl, w.pp, single, st);
+        const int order = static_cast<int>(std::min<int64_t>(w.q_cap / kSortTile + n_sets, kSortBlocks));
+        match_plan<<<1 + n_sets / 2 + order, kPlanThreads, 0, s>>>(sets, n_sets, dim, one_sided ? 1 : 0, w.pool_cap,
+                                                                   w.plan, w.ctl, w.pp, single, w, st);
         KMG_TRY(launch_status());
         match_round<<<grid_cap(w.slot_cap * 8, kBlock), kBlock, 0, s>>>(sets, w.plan, n_sets, dim, w.pp, w, w.ctl);
         KMG_TRY(launch_status());

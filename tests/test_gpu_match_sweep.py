@@ -89,6 +89,27 @@ def test_equal_rows(K, orc):
     check(K, orc, np.zeros((90, 33)), np.zeros((70, 33)))
 
 
+@pytest.mark.parametrize("shape", [(1024, 1023), (1024, 1025), (2049, 2048), (3000, 1100)])
+@pytest.mark.parametrize("norms", ["equal", "spread", "huge", "tiny", "bad"])
+def test_norm_order(K, orc, shape, norms):
+    # sets around the borders of the tiles that rows are ordered in by norm: all norms equal (nothing
+    # is skipped), over six decades (nearly all is), with squares beyond FP32's range at either end, and
+    # with rows that are not numbers (no row is their nearest)
+    rng = np.random.default_rng(sum(shape))
+    Y = rows(rng, shape[1], 33)
+    X = np.abs(Y[rng.integers(0, shape[1], shape[0])] * (1 + 0.05 * rng.standard_normal((shape[0], 33))))
+    if norms == "equal":
+        X, Y = (v / np.linalg.norm(v, axis=1, keepdims=True) for v in (X, Y))
+    if norms == "spread":
+        X, Y = (v * 10.0 ** rng.uniform(-3, 3, (v.shape[0], 1)) for v in (X, Y))
+    if norms in ("huge", "tiny"):
+        s = 1e18 if norms == "huge" else 1e-22
+        X, Y = X * s, Y * s
+    if norms == "bad":
+        X[::97, 5], Y[::89, 7], Y[3::60, 1] = np.nan, np.nan, np.inf
+    check(K, orc, X, Y)
+
+
 def test_forms_agree(K):
     # above the size from which matching is one-sided: the same pairs and distances both ways
     from synth import synthetic_descriptors
