@@ -316,15 +316,20 @@ struct SearchWs {
     uint32_t cap_table;
 };
 SearchWs carve_search(Carver& c, int64_t m_cap);
+size_t search_scan_status_elems(const SearchWs& w, int64_t m_cap);
 // Grid build and the count pass over the kept points (count st->m_kept <=
 // m_cap, SoA stride `stride`, cloud ids kept_cloud (nullable = cloud 0)).
 // off receives m_cap + 1 offsets; the total goes to st->nnz.
 // use_rn: search at r_normal instead of r_FPFH; build_grid false reuses the
 // cell grid of an earlier call on the same workspace.  cleared: the caller
 // has already emptied the cell table (keys, ccount, cfill) and zeroed deg.
+// scan_status (optional): zeroed look-back words for the two scans (cell
+// counts, then degrees), search_scan_status_elems(w, m_cap) of them (scan_tmp
+// holds as many).
 kmg_status search_count_batch(const CloudDev* cl, const float* xyz, int64_t stride, const int32_t* kept_cloud,
                               int64_t m_cap, DevStatus* st, const SearchWs& w, int32_t* off, hipStream_t s,
-                              bool build_grid = true, int use_rn = 0, bool cleared = false, bool inserted = false);
+                              bool build_grid = true, int use_rn = 0, bool cleared = false, bool inserted = false,
+                              uint64_t* scan_status = nullptr);
 // Fill pass (lists ascending) and normals.  Writes nothing into nbr when
 // st->nnz > nbr_cap (device-side check; st->err_capacity is set).
 kmg_status search_fill_batch(const CloudDev* cl, const float* xyz, int64_t stride, const int32_t* kept_cloud,
@@ -345,7 +350,6 @@ kmg_status search_lists_first(const CloudDev* cl, const float* xyz, int64_t stri
                               int32_t* nbr, int32_t* pad, int64_t pad_cap, int32_t* long_q, float* nrm,
                               int64_t nrm_stride, uint8_t* flags, hipStream_t s, bool inserted = false,
                               uint64_t* scan_status = nullptr);
-size_t search_scan_status_elems(const SearchWs& w, int64_t m_cap);
 
 // ---- features.hip ---------------------------------------------------------
 // Row stride of the SPFH counts, in entries: 3H rounded up to a multiple of 8,

@@ -751,7 +751,7 @@ SearchWs carve_search(Carver& c, int64_t m_cap) {
     w.pslot = c.take<int32_t>(static_cast<size_t>(std::max<int64_t>(m_cap, 1)));
     w.pts = c.take<float4>(static_cast<size_t>(std::max<int64_t>(m_cap, 1)));
     w.deg = c.take<int32_t>(static_cast<size_t>(m_cap) + 1);
-    w.scan_tmp = c.take<int64_t>(std::max(scan_temp_elems(m_cap + 1), scan_temp_elems(w.cap_table)));
+    w.scan_tmp = c.take<int64_t>(search_scan_status_elems(w, m_cap));
     return w;
 }
 
@@ -789,8 +789,8 @@ kmg_status build_grid(const CloudDev* cl, const float* xyz, int64_t stride, cons
 
 kmg_status search_count_batch(const CloudDev* cl, const float* xyz, int64_t stride, const int32_t* kept_cloud,
                               int64_t m_cap, DevStatus* st, const SearchWs& w, int32_t* off, hipStream_t s,
-                              bool grid, int use_rn, bool cleared, bool inserted) {
-    if (grid) KMG_TRY(build_grid(cl, xyz, stride, kept_cloud, m_cap, st, w, s, cleared, inserted));
+                              bool grid, int use_rn, bool cleared, bool inserted, uint64_t* scan_status) {
+    if (grid) KMG_TRY(build_grid(cl, xyz, stride, kept_cloud, m_cap, st, w, s, cleared, inserted, scan_status));
     {
         StageScope sc(ST_SEARCH_COUNT, s);
         if (!cleared) KMG_TRY(fill_u32(reinterpret_cast<uint32_t*>(w.deg), 0u, static_cast<size_t>(m_cap) + 1, s));
@@ -799,7 +799,11 @@ kmg_status search_count_batch(const CloudDev* cl, const float* xyz, int64_t stri
             KMG_TRY(launch_count(t.search_waves, t.count_queries, cl, grid_of(w), kept_cloud, m_cap, w.deg, use_rn,
                                  st, s));
         }
-        KMG_TRY(scan_exclusive(w.deg, off, m_cap + 1, &st->nnz, w.scan_tmp, s));
+        if (scan_status)
+            KMG_TRY(scan_exclusive_onepass(w.deg, off, m_cap + 1, &st->nnz, scan_status + scan_temp_elems(w.cap_table),
+                                           &st->err_sync, s));
+        else
+            KMG_TRY(scan_exclusive(w.deg, off, m_cap + 1, &st->nnz, w.scan_tmp, s));
     }
     return KMG_OK;
 }

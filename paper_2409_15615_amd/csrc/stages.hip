@@ -6,27 +6,48 @@ namespace kmg {
 
 namespace {
 
+// Clears the status, writes the cloud's record (block 0) and does the fills of
+// the call (a launch each, they were half of a small call's launches).
 // off (optional): the caller's neighbour lists, whose volume off[m_kept] goes
 // to st->nnz.
-__global__ void init_single(DevStatus* st, CloudDev* cl, CloudDev v, int64_t n_raw, int64_t m_kept,
-                            const int32_t* off) {
-    const int i = threadIdx.x;
-    uint32_t* w = reinterpret_cast<uint32_t*>(st);
-    for (int k = i; k < static_cast<int>(sizeof(DevStatus) / 4); k += blockDim.x) w[k] = 0u;
-    __syncthreads();
-    if (i == 0) {
-        st->n_raw = n_raw;
-        st->m_kept = m_kept;
-        if (off) st->nnz = off[m_kept];
-        cl[0] = v;
+__global__ __launch_bounds__(256) void init_single(DevStatus* st, CloudDev* cl, CloudDev v, int64_t n_raw,
+                                                   int64_t m_kept, const int32_t* off, FillJobs fills) {
+    if (blockIdx.x == 0) {
+        const int i = threadIdx.x;
+        uint32_t* w = reinterpret_cast<uint32_t*>(st);
+        for (int k = i; k < static_cast<int>(sizeof(DevStatus) / 4); k += blockDim.x) w[k] = 0u;
+        __syncthreads();
+        if (i == 0) {
+            st->n_raw = n_raw;
+            st->m_kept = m_kept;
+            if (off) st->nnz = off[m_kept];
+            cl[0] = v;
+        }
     }
+    run_fill_jobs(fills);
 }
 
-kmg_status init(DevStatus* st, CloudDev* cl, const CloudDev& v, int64_t n_raw, int64_t m_kept, hipStream_t s,
-                const int32_t* off = nullptr) {
-    init_single<<<1, 64, 0, s>>>(st, cl, v, n_raw, m_kept, off);
+void add_fill(FillJobs& f, void* p, uint64_t v, int64_t n, int32_t bytes) { f.job[f.n_jobs++] = FillJob{p, v, n, bytes}; }
+
+// The cell hash, the degrees and the look-back words of a search over m points.
+void add_search_fills(FillJobs& f, const SearchWs& w, int64_t m) {
+    add_fill(f, w.keys, kEmptyKey, w.cap_table, 8);
+    add_fill(f, w.ccount, 0ull, w.cap_table, 4);
+    add_fill(f, w.cfill, 0ull, w.cap_table, 4);
+    add_fill(f, w.deg, 0ull, m + 1, 4);
+    add_fill(f, w.scan_tmp, 0ull, static_cast<int64_t>(search_scan_status_elems(w, m)), 8);
+}
+
+kmg_status init(DevStatus* st, CloudDev* cl, const CloudDev& v, int64_t n_raw, int64_t m_kept, const FillJobs& fills,
+                hipStream_t s, const int32_t* off = nullptr) {
+    int64_t most = 1;
+    for (int k = 0; k < fills.n_jobs; ++k) most = std::max(most, fills.job[k].n);
+    init_single<<<static_cast<unsigned>(std::min<int64_t>((most + 255) / 256, 4096)), 256, 0, s>>>(st, cl, v, n_raw,
+                                                                                                  m_kept, off, fills);
     return launch_status();
 }
+
+uint64_t* look_back_words(int64_t* scan_tmp) { return reinterpret_cast<uint64_t*>(scan_tmp); }
 
 kmg_status read_status(DevStatus* st, DevStatus* host, hipStream_t s) {
     KMG_TRY_HIP(hipMemcpyAsync(host, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
@@ -83,11 +104,17 @@ kmg_status voxelize(const float* xyz, int64_t n, double voxel, int32_t* kept_idx
     p.tau_lin = 1.0;
     p.tau_num = 1;
     p.n_bins = 1;
-    KMG_TRY(init(st, cl, make_cloud(p, xyz, n, 0), n, 0, s));
-    KMG_TRY(voxelize_batch(cl, 1, n, st, w, cap, 0, kept_idx, kept_xyz, nullptr, nullptr, s));
+    FillJobs fills{};
+    add_fill(fills, w.keys, kEmptyKey, w.cap_table, 8);
+    add_fill(fills, w.mins, 0x7fffffffull, w.cap_table, 4);
+    add_fill(fills, w.scan_tmp, 0ull, static_cast<int64_t>(scan_temp_elems(n)), 8);
+    KMG_TRY(init(st, cl, make_cloud(p, xyz, n, 0), n, 0, fills, s));
+    KMG_TRY(voxelize_batch(cl, 1, n, st, w, cap, 0, kept_idx, kept_xyz, nullptr, nullptr, s, true, nullptr,
+                           look_back_words(w.scan_tmp)));
     DevStatus h;
     KMG_TRY(read_status(st, &h, s));
     if (h.err_range) return KMG_ERR_RANGE;
+    if (h.err_sync) return KMG_ERR_DEVICE;
     *n_kept_host = h.m_kept;
     if (h.m_kept > cap) return KMG_ERR_CAPACITY;
     return KMG_OK;
@@ -122,12 +149,16 @@ kmg_status normals(const float* xyz, int64_t m, const kmg_params& p, float* nrm,
         nbr_n = c.take<int32_t>(static_cast<size_t>(nbr_n_cap));
     }
     if (!c.fits()) return KMG_ERR_WORKSPACE;
-    KMG_TRY(init(st, cl, make_cloud(p, nullptr, 0, 0), 0, m, s));
+    FillJobs fills{};
+    add_search_fills(fills, w, m);
+    KMG_TRY(init(st, cl, make_cloud(p, nullptr, 0, 0), 0, m, fills, s));
     DevStatus h;
     if (classic) {
         // search 1 (r_normal) and the normals from its lists
-        KMG_TRY(search_count_batch(cl, xyz, m, nullptr, m, st, w, off_n, s, true, 1));
+        KMG_TRY(search_count_batch(cl, xyz, m, nullptr, m, st, w, off_n, s, true, 1, true, false,
+                                   look_back_words(w.scan_tmp)));
         KMG_TRY(read_status(st, &h, s));
+        if (h.err_sync) return KMG_ERR_DEVICE;
         if (h.err_range || (h.dense & 2) || h.nnz > INT32_MAX) return KMG_ERR_RANGE;
         if (h.nnz > nbr_n_cap) {
             *nnz_host = h.nnz;
@@ -136,9 +167,14 @@ kmg_status normals(const float* xyz, int64_t m, const kmg_params& p, float* nrm,
         KMG_TRY(search_fill_batch(cl, xyz, m, nullptr, m, nbr_n_cap, (h.dense & 1) != 0, st, w, off_n, nbr_n, nrm, m,
                                   flags, n_normal, s, 1, true));
     }
-    // Faster-PFH: the one search at r_FPFH; classic: search 2, lists only
-    KMG_TRY(search_count_batch(cl, xyz, m, nullptr, m, st, w, off, s, !classic, 0));
+    // Faster-PFH: the one search at r_FPFH; classic: search 2, lists only, over the same grid
+    if (classic)
+        KMG_TRY(search_count_batch(cl, xyz, m, nullptr, m, st, w, off, s, false, 0));
+    else
+        KMG_TRY(search_count_batch(cl, xyz, m, nullptr, m, st, w, off, s, true, 0, true, false,
+                                   look_back_words(w.scan_tmp)));
     KMG_TRY(read_status(st, &h, s));
+    if (h.err_sync) return KMG_ERR_DEVICE;
     if (h.err_range || (h.dense & 2) || h.nnz > INT32_MAX) return KMG_ERR_RANGE;
     *nnz_host = h.nnz;
     if (h.nnz > nbr_cap) return KMG_ERR_CAPACITY;
@@ -182,24 +218,32 @@ kmg_status fpfh(const float* xyz, const float* nrm, uint8_t* flags, const int32_
         nbr3 = c.take<int32_t>(static_cast<size_t>(std::max<int64_t>(nnz3_cap, 1)));
     }
     if (!c.fits()) return KMG_ERR_WORKSPACE;
-    KMG_TRY(init(st, cl, make_cloud(p, nullptr, 0, 0), 0, m, s, off));
+    FillJobs fills{};
+    add_fill(fills, w.jflag, 0ull, std::max<int64_t>(m, 1), 4);
+    add_fill(fills, w.scan_tmp, 0ull, static_cast<int64_t>(scan_temp_elems(m)), 8);
+    if (classic) add_search_fills(fills, sw, m);
+    KMG_TRY(init(st, cl, make_cloud(p, nullptr, 0, 0), 0, m, fills, s, off));
     if (!classic) {
         KMG_TRY(features_batch(cl, 1, xyz, m, nullptr, m, H, st, w, off, NbrLists{nbr}, nrm, m, flags, spfh_out,
-                               fpfh_out, j_idx, nullptr, s));
+                               fpfh_out, j_idx, nullptr, s, true, nullptr, look_back_words(w.scan_tmp)));
     } else {
         // SPFH over the lists of search 2; search 3 (r_FPFH again) for the FPFH sum
-        KMG_TRY(spfh_batch(cl, xyz, m, nullptr, m, H, st, w, off, NbrLists{nbr}, nrm, m, flags, spfh_out, s));
-        KMG_TRY(search_count_batch(cl, xyz, m, nullptr, m, st, sw, off3, s, true, 0));
+        KMG_TRY(spfh_batch(cl, xyz, m, nullptr, m, H, st, w, off, NbrLists{nbr}, nrm, m, flags, spfh_out, s, true));
+        KMG_TRY(search_count_batch(cl, xyz, m, nullptr, m, st, sw, off3, s, true, 0, true, false,
+                                   look_back_words(sw.scan_tmp)));
         DevStatus h3;
         KMG_TRY(read_status(st, &h3, s));
+        if (h3.err_sync) return KMG_ERR_DEVICE;
         if (h3.err_range || (h3.dense & 2)) return KMG_ERR_RANGE;
         if (h3.nnz > nnz3_cap) return KMG_ERR_WORKSPACE;
         KMG_TRY(search_fill_batch(cl, xyz, m, nullptr, m, nnz3_cap, (h3.dense & 1) != 0, st, sw, off3, nbr3, nullptr,
                                   m, flags, nullptr, s, 0, false));
-        KMG_TRY(fpfh_batch(1, xyz, m, m, H, st, w, off3, NbrLists{nbr3}, flags, fpfh_out, j_idx, nullptr, s));
+        KMG_TRY(fpfh_batch(1, xyz, m, m, H, st, w, off3, NbrLists{nbr3}, flags, fpfh_out, j_idx, nullptr, s, nullptr,
+                           look_back_words(w.scan_tmp)));
     }
     DevStatus h;
     KMG_TRY(read_status(st, &h, s));
+    if (h.err_sync) return KMG_ERR_DEVICE;
     *n_j_host = h.n_j;
     if (stats_host) {
         stats_host[0] = h.feat_fp64;
