@@ -21,7 +21,9 @@
  *  - Descriptors are row-major float32, 3*H values per point (H = n_bins).
  *  - `stream` is a hipStream_t passed as void* (NULL = the null stream).
  *    Work is enqueued on it; calls that return a count through a host
- *    pointer synchronise that stream before returning.
+ *    pointer wait for that stream to reach the count before returning (it
+ *    comes through a few hundred bytes of pinned host memory, of which the
+ *    library keeps at most 16 such pieces).
  *  - Indices are int32 and refer to the kept (voxelized) cloud, except
  *    kept_idx, which maps kept points back to raw input indices.
  *  - Errors are returned as kmg_status; no call aborts or throws.  On
@@ -254,8 +256,8 @@ kmg_status kmg_normals(const float* xyz, int64_t m, const kmg_params* p, float* 
  *   p->mode    KMG_MODE_FASTER_PFH only (KMG_ERR_ARG otherwise).
  * Every call on a GPU shares that GPU's array: calls that overlap on one
  * device (two streams, two threads) race and must be serialised by the
- * caller.  The call itself allocates nothing; like kmg_normals it
- * synchronises `stream` to return *nnz.
+ * caller.  The call itself allocates no device memory; like kmg_normals it
+ * waits for `stream` to return *nnz.
  */
 #define KMG_STATIC_MAX_POINTS 262144
 kmg_status kmg_normals_static(const float* xyz, int64_t m, const kmg_params* p, float* normals, uint8_t* flags,

@@ -185,7 +185,7 @@ kmg_status batch_run(int n_pairs, int64_t raw_cap, int64_t nnz_cap, int H, int p
     } else {
         KMG_TRY(search_count_batch(w.cl, w.kept_xyz, raw_cap, w.kept_cloud, raw_cap, w.st, w.srch, w.off, s, true,
                                    0, true, true));
-        KMG_TRY(search_fill_batch(w.cl, w.kept_xyz, raw_cap, w.kept_cloud, raw_cap, nnz_cap, true, w.st, w.srch,
+        KMG_TRY(search_fill_batch(w.cl, w.kept_xyz, raw_cap, w.kept_cloud, raw_cap, nnz_cap, kFillAll, w.st, w.srch,
                                   w.off, w.nbr, w.nrm, raw_cap, w.flags, nullptr, s));
     }
     // the list-first search leaves the lists in the pad rows (the longer ones in nbr);

@@ -443,9 +443,9 @@ kmg_status corr_graph(const float* src, int64_t src_stride, const float* tgt, in
     KMG_TRY(scan_exclusive(w.deg, off, static_cast<int64_t>(n) + 1, w.nnz, w.scan_tmp, s));
     int64_t nnz = 0;
     int32_t err = 0;
-    KMG_TRY_HIP(hipMemcpyAsync(&nnz, w.nnz, sizeof(nnz), hipMemcpyDeviceToHost, s));
-    KMG_TRY_HIP(hipMemcpyAsync(&err, w.err, sizeof(err), hipMemcpyDeviceToHost, s));
-    KMG_TRY_HIP(hipStreamSynchronize(s));
+    Report r;
+    KMG_TRY(r.post(w.nnz, sizeof(nnz), w.err, sizeof(err), s));
+    KMG_TRY(r.wait(&nnz, &err));
     if (err) return KMG_ERR_RANGE;
     *nnz_host = nnz;
     if (nnz > adj_cap) return KMG_ERR_CAPACITY;
@@ -487,8 +487,9 @@ kmg_status max_kcore(const int32_t* off, const int32_t* adj, int32_t n, int32_t*
     kcore_members<<<1, kPeelThreads, 0, s>>>(core, n, members, w.info);
     KMG_TRY(launch_status());
     int32_t info[3];
-    KMG_TRY_HIP(hipMemcpyAsync(info, w.info, sizeof(info), hipMemcpyDeviceToHost, s));
-    KMG_TRY_HIP(hipStreamSynchronize(s));
+    Report r;
+    KMG_TRY(r.post(w.info, sizeof(info), nullptr, 0, s));
+    KMG_TRY(r.wait(info));
     if (info[2]) return KMG_ERR_RANGE;
     *max_core_host = info[0];
     *n_members_host = info[1];

@@ -261,6 +261,34 @@ __device__ __forceinline__ void run_fill_jobs(const FillJobs& f) {
 kmg_status fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s);
 kmg_status fill_u64(uint64_t* p, uint64_t v, size_t n, hipStream_t s);
 
+// ---- report.hip -----------------------------------------------------------
+constexpr int kReportWords = 127;
+struct ReportSlot {  // pinned host memory
+    uint32_t ticket;
+    uint32_t words[kReportWords];
+};
+// Result words of a call (4-byte words of one or two device records): post
+// enqueues the kernel that sends them, wait returns once they are here, and with
+// them everything enqueued before them.  One report at a time.
+class Report {
+  public:
+    Report() = default;
+    Report(const Report&) = delete;
+    Report& operator=(const Report&) = delete;
+    ~Report();
+    kmg_status post(const void* a, size_t a_bytes, const void* b, size_t b_bytes, hipStream_t s);
+    kmg_status wait(void* a, void* b = nullptr);
+
+  private:
+    ReportSlot* slot_ = nullptr;
+    hipStream_t stream_ = nullptr;
+    const void* a_ = nullptr;
+    const void* b_ = nullptr;
+    uint32_t ticket_ = 0;
+    int na_ = 0, nb_ = 0;
+    bool posted_ = false;
+};
+
 // ---- voxel.hip ------------------------------------------------------------
 struct VoxelWs {
     uint64_t* keys;
@@ -330,12 +358,15 @@ kmg_status search_count_batch(const CloudDev* cl, const float* xyz, int64_t stri
                               int64_t m_cap, DevStatus* st, const SearchWs& w, int32_t* off, hipStream_t s,
                               bool build_grid = true, int use_rn = 0, bool cleared = false, bool inserted = false,
                               uint64_t* scan_status = nullptr);
-// Fill pass (lists ascending) and normals.  Writes nothing into nbr when
-// st->nnz > nbr_cap (device-side check; st->err_capacity is set).
+// Fill pass (lists ascending), its dense pass (lists longer than the first
+// takes; st->dense tells whether there are any) and normals, by `parts`.
+// Writes nothing into nbr when st->nnz > nbr_cap (device-side check;
+// st->err_capacity is set).
+enum : int { kFillLists = 1, kFillDense = 2, kFillNormals = 4, kFillAll = 7 };
 kmg_status search_fill_batch(const CloudDev* cl, const float* xyz, int64_t stride, const int32_t* kept_cloud,
-                             int64_t m_cap, int64_t nbr_cap, bool dense_pass, DevStatus* st, const SearchWs& w,
+                             int64_t m_cap, int64_t nbr_cap, int parts, DevStatus* st, const SearchWs& w,
                              const int32_t* off, int32_t* nbr, float* nrm, int64_t nrm_stride, uint8_t* flags,
-                             int32_t* n_normal, hipStream_t s, int use_rn = 0, bool with_normals = true);
+                             int32_t* n_normal, hipStream_t s, int use_rn = 0);
 // The list-first form of the grid build, search and normals (r_FPFH lists,
 // tables cleared beforehand): one search pass writes |N(q)| and each list
 // that fits a row of the pad (pad_cap entries shared evenly by the kept

@@ -1692,9 +1692,9 @@ kmg_status match(const float* dp, const int32_t* rp, int64_t np, const float* dq
     KMG_TRY(match_sets(sets, 2, dim, np * nq, p, st, w, outs, counts, 8, s, nullptr, 0));
     int64_t hc[8];
     DevStatus hs;
-    KMG_TRY_HIP(hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, s));
-    KMG_TRY_HIP(hipMemcpyAsync(&hs, st, sizeof(hs), hipMemcpyDeviceToHost, s));
-    KMG_TRY_HIP(hipStreamSynchronize(s));
+    Report r;
+    KMG_TRY(r.post(counts, sizeof(hc), st, sizeof(hs), s));
+    KMG_TRY(r.wait(hc, &hs));
     timer_collect();
     if (hs.err_capacity) return KMG_ERR_WORKSPACE;
     if (hs.err_sync) return KMG_ERR_DEVICE;

@@ -408,7 +408,7 @@ __global__ __launch_bounds__(kWaves* kWave) void radius_fill2(const CloudDev* __
         if (blockIdx.x == 0 && threadIdx.x == 0 && st->nnz > nbr_cap) st->err_capacity = 1;
         if (st->nnz > nbr_cap) return;  // no fill beyond the caller's list capacity
     }
-    if (st->err_range) return;  // no search over a partial grid
+    if (st->err_range || st->err_sync) return;  // no search over a partial grid, no lists at partial offsets
     const int row = kFirst ? pad_stride(nbr_cap, m) : 0;
     for (int64_t pw = static_cast<int64_t>(blockIdx.x) * kWaves + wv; 2 * pw < m;
          pw += static_cast<int64_t>(gridDim.x) * kWaves) {
@@ -848,21 +848,22 @@ kmg_status search_lists_first(const CloudDev* cl, const float* xyz, int64_t stri
 }
 
 kmg_status search_fill_batch(const CloudDev* cl, const float* xyz, int64_t stride, const int32_t* kept_cloud,
-                             int64_t m_cap, int64_t nbr_cap, bool dense_pass, DevStatus* st, const SearchWs& w,
+                             int64_t m_cap, int64_t nbr_cap, int parts, DevStatus* st, const SearchWs& w,
                              const int32_t* off, int32_t* nbr, float* nrm, int64_t nrm_stride, uint8_t* flags,
-                             int32_t* n_normal, hipStream_t s, int use_rn, bool with_normals) {
+                             int32_t* n_normal, hipStream_t s, int use_rn) {
     if (m_cap <= 0) return KMG_OK;
     {
         StageScope sc(ST_SEARCH_FILL, s);
-        KMG_TRY(launch_fill(tuning().search_waves, cl, grid_of(w), kept_cloud, m_cap,
-                            FillOut{off, nbr, nbr_cap, nullptr, nullptr}, use_rn, st, s));
-        if (dense_pass) {
+        if (parts & kFillLists)
+            KMG_TRY(launch_fill(tuning().search_waves, cl, grid_of(w), kept_cloud, m_cap,
+                                FillOut{off, nbr, nbr_cap, nullptr, nullptr}, use_rn, st, s));
+        if (parts & kFillDense) {
             radius_search<true, kMaxDegree, 1><<<grid_cap(m_cap, 1), kWave, 0, s>>>(
                 cl, grid_of(w), kept_cloud, m_cap, nullptr, off, nbr, nbr_cap, 1, use_rn, st);
             KMG_TRY(launch_status());
         }
     }
-    if (with_normals) {
+    if (parts & kFillNormals) {
         StageScope sc(ST_NORMALS, s);
         normals_kernel<<<grid_cap(m_cap * kNormalLanes, kBlock), kBlock, 0, s>>>(
             cl, xyz, stride, kept_cloud, m_cap, off, nbr, nbr_cap, nrm, nrm_stride, flags, n_normal, st);

@@ -50,10 +50,35 @@ kmg_status init(DevStatus* st, CloudDev* cl, const CloudDev& v, int64_t n_raw, i
 uint64_t* look_back_words(int64_t* scan_tmp) { return reinterpret_cast<uint64_t*>(scan_tmp); }
 
 kmg_status read_status(DevStatus* st, DevStatus* host, hipStream_t s) {
-    KMG_TRY_HIP(hipMemcpyAsync(host, st, sizeof(DevStatus), hipMemcpyDeviceToHost, s));
-    KMG_TRY_HIP(hipStreamSynchronize(s));
+    Report r;
+    KMG_TRY(r.post(st, sizeof(DevStatus), nullptr, 0, s));
+    KMG_TRY(r.wait(host));
     timer_collect();
     return KMG_OK;
+}
+
+// The fill after a count pass.  The lists go first, behind the report of the
+// count: while the host reads it the GPU already fills (nothing, when the lists
+// exceed the capacity, their offsets or the supported range).
+kmg_status fill_counted(const CloudDev* cl, const float* xyz, int64_t m, int64_t nbr_cap, DevStatus* st,
+                        const SearchWs& w, const int32_t* off, int32_t* nbr, float* nrm, uint8_t* flags,
+                        int32_t* n_normal, hipStream_t s, int use_rn, bool with_normals, int64_t* nnz_host,
+                        kmg_status over_capacity) {
+    Report r;
+    DevStatus h;
+    const int64_t cap = std::min<int64_t>(nbr_cap, INT32_MAX);  // 32-bit offsets
+    KMG_TRY(r.post(st, sizeof(DevStatus), nullptr, 0, s));
+    KMG_TRY(search_fill_batch(cl, xyz, m, nullptr, m, cap, kFillLists, st, w, off, nbr, nrm, m, flags, n_normal, s,
+                              use_rn));
+    KMG_TRY(r.wait(&h));
+    timer_collect();
+    if (h.err_sync) return KMG_ERR_DEVICE;
+    if (h.err_range || (h.dense & 2) || h.nnz > INT32_MAX) return KMG_ERR_RANGE;
+    if (nnz_host) *nnz_host = h.nnz;
+    if (h.nnz > nbr_cap) return over_capacity;
+    return search_fill_batch(cl, xyz, m, nullptr, m, cap,
+                             ((h.dense & 1) ? kFillDense : 0) | (with_normals ? kFillNormals : 0), st, w, off, nbr, nrm,
+                             m, flags, n_normal, s, use_rn);
 }
 
 }  // namespace
@@ -152,20 +177,15 @@ kmg_status normals(const float* xyz, int64_t m, const kmg_params& p, float* nrm,
     FillJobs fills{};
     add_search_fills(fills, w, m);
     KMG_TRY(init(st, cl, make_cloud(p, nullptr, 0, 0), 0, m, fills, s));
-    DevStatus h;
     if (classic) {
         // search 1 (r_normal) and the normals from its lists
         KMG_TRY(search_count_batch(cl, xyz, m, nullptr, m, st, w, off_n, s, true, 1, true, false,
                                    look_back_words(w.scan_tmp)));
-        KMG_TRY(read_status(st, &h, s));
-        if (h.err_sync) return KMG_ERR_DEVICE;
-        if (h.err_range || (h.dense & 2) || h.nnz > INT32_MAX) return KMG_ERR_RANGE;
-        if (h.nnz > nbr_n_cap) {
-            *nnz_host = h.nnz;
-            return KMG_ERR_CAPACITY;
-        }
-        KMG_TRY(search_fill_batch(cl, xyz, m, nullptr, m, nbr_n_cap, (h.dense & 1) != 0, st, w, off_n, nbr_n, nrm, m,
-                                  flags, n_normal, s, 1, true));
+        int64_t nnz_n = 0;
+        const kmg_status got = fill_counted(cl, xyz, m, nbr_n_cap, st, w, off_n, nbr_n, nrm, flags, n_normal, s, 1,
+                                            true, &nnz_n, KMG_ERR_CAPACITY);
+        if (got == KMG_ERR_CAPACITY) *nnz_host = nnz_n;
+        KMG_TRY(got);
     }
     // Faster-PFH: the one search at r_FPFH; classic: search 2, lists only, over the same grid
     if (classic)
@@ -173,13 +193,8 @@ kmg_status normals(const float* xyz, int64_t m, const kmg_params& p, float* nrm,
     else
         KMG_TRY(search_count_batch(cl, xyz, m, nullptr, m, st, w, off, s, true, 0, true, false,
                                    look_back_words(w.scan_tmp)));
-    KMG_TRY(read_status(st, &h, s));
-    if (h.err_sync) return KMG_ERR_DEVICE;
-    if (h.err_range || (h.dense & 2) || h.nnz > INT32_MAX) return KMG_ERR_RANGE;
-    *nnz_host = h.nnz;
-    if (h.nnz > nbr_cap) return KMG_ERR_CAPACITY;
-    KMG_TRY(search_fill_batch(cl, xyz, m, nullptr, m, nbr_cap, (h.dense & 1) != 0, st, w, off, nbr, nrm, m, flags,
-                              n_normal, s, 0, !classic));
+    KMG_TRY(fill_counted(cl, xyz, m, nbr_cap, st, w, off, nbr, nrm, flags, n_normal, s, 0, !classic, nnz_host,
+                         KMG_ERR_CAPACITY));
     timer_collect();
     return KMG_OK;
 }
@@ -231,13 +246,8 @@ kmg_status fpfh(const float* xyz, const float* nrm, uint8_t* flags, const int32_
         KMG_TRY(spfh_batch(cl, xyz, m, nullptr, m, H, st, w, off, NbrLists{nbr}, nrm, m, flags, spfh_out, s, true));
         KMG_TRY(search_count_batch(cl, xyz, m, nullptr, m, st, sw, off3, s, true, 0, true, false,
                                    look_back_words(sw.scan_tmp)));
-        DevStatus h3;
-        KMG_TRY(read_status(st, &h3, s));
-        if (h3.err_sync) return KMG_ERR_DEVICE;
-        if (h3.err_range || (h3.dense & 2)) return KMG_ERR_RANGE;
-        if (h3.nnz > nnz3_cap) return KMG_ERR_WORKSPACE;
-        KMG_TRY(search_fill_batch(cl, xyz, m, nullptr, m, nnz3_cap, (h3.dense & 1) != 0, st, sw, off3, nbr3, nullptr,
-                                  m, flags, nullptr, s, 0, false));
+        KMG_TRY(fill_counted(cl, xyz, m, nnz3_cap, st, sw, off3, nbr3, nullptr, flags, nullptr, s, 0, false, nullptr,
+                             KMG_ERR_WORKSPACE));
         KMG_TRY(fpfh_batch(1, xyz, m, m, H, st, w, off3, NbrLists{nbr3}, flags, fpfh_out, j_idx, nullptr, s, nullptr,
                            look_back_words(w.scan_tmp)));
     }
