@@ -33,20 +33,28 @@ constexpr int kBlock = 256;
 constexpr int kPeelThreads = 1024;
 constexpr int kMaxKcore = KMG_MAX_KCORE_VERTICES;  // LDS: 4 + 2 + 2 bytes per vertex
 
+// Also clears what the call counts in: the ranks, the degrees, the look-back
+// words of their scan and the index flag.
 __global__ __launch_bounds__(kBlock) void ratio_keys(const float* __restrict__ d1, const float* __restrict__ d2,
-                                                     int64_t k, uint64_t* __restrict__ keys) {
+                                                     int64_t k, uint64_t* __restrict__ keys,
+                                                     int32_t* __restrict__ rank, FillJobs fills) {
     for (int64_t e = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; e < k;
          e += static_cast<int64_t>(gridDim.x) * kBlock) {
         const double a = d1[e], b = d2[e];
         const double r = b > 0.0 ? a / b : (a > 0.0 ? INFINITY : 0.0);
         keys[e] = static_cast<uint64_t>(__double_as_longlong(r));
+        rank[e] = 0;
     }
+    run_fill_jobs(fills);
 }
 
 // rank[e] = number of correspondences f ordered before e by (key, position).
 // Block (x, y) counts, for the keys of tile x, the keys of tiles y, y + gy, ...
-// (staged in LDS) that come first, and adds its counts with one atomic per key;
-// rank_emit then writes sel[rank] = e for the first n_tau ranks.
+// (staged in LDS) that come first, and adds its counts with one atomic per key.
+// Equal keys count where they lie before: all of a tile before x, none of one
+// after it, so that only tile x itself compares positions.  The LDS reads of
+// eight keys are in flight at a time (one at a time: 19 us for 2,780
+// correspondences, now 9).
 constexpr int kRankTiles = 64;  // y tiles of the counting grid
 
 __global__ __launch_bounds__(kBlock) void rank_count(const uint64_t* __restrict__ keys, int64_t k,
@@ -59,33 +67,40 @@ __global__ __launch_bounds__(kBlock) void rank_count(const uint64_t* __restrict_
     for (int64_t f0 = static_cast<int64_t>(blockIdx.y) * kBlock; f0 < k;
          f0 += static_cast<int64_t>(gridDim.y) * kBlock) {
         __syncthreads();
-        if (f0 + threadIdx.x < k) s_key[threadIdx.x] = keys[f0 + threadIdx.x];
+        // keys are at most the bits of +inf or NaN (below ~0): the places past the end count nowhere
+        s_key[threadIdx.x] = f0 + threadIdx.x < k ? keys[f0 + threadIdx.x] : ~0ull;
         __syncthreads();
-        const int nf = static_cast<int>(min<int64_t>(kBlock, k - f0));
-        for (int t = 0; t < nf; ++t) {
-            const uint64_t o = s_key[t];
-            cnt += (o < me || (o == me && f0 + t < e)) ? 1 : 0;
+        const int64_t x0 = static_cast<int64_t>(blockIdx.x) * kBlock;
+        if (f0 == x0) {
+#pragma unroll 8
+            for (int t = 0; t < kBlock; ++t) {
+                const uint64_t o = s_key[t];
+                cnt += (o < me || (o == me && t < static_cast<int>(threadIdx.x))) ? 1 : 0;
+            }
+        } else if (f0 < x0) {  // a whole tile: its last key is inside
+#pragma unroll 8
+            for (int t = 0; t < kBlock; ++t) cnt += s_key[t] <= me ? 1 : 0;
+        } else {
+#pragma unroll 8
+            for (int t = 0; t < kBlock; ++t) cnt += s_key[t] < me ? 1 : 0;
         }
     }
     if (live && cnt) atomicAdd(rank + e, cnt);
 }
 
-__global__ __launch_bounds__(kBlock) void rank_emit(const int32_t* __restrict__ rank, int64_t k, int32_t n_tau,
-                                                    int32_t* __restrict__ sel) {
-    for (int64_t e = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; e < k;
-         e += static_cast<int64_t>(gridDim.x) * kBlock)
-        if (rank[e] < n_tau) sel[rank[e]] = static_cast<int32_t>(e);
-}
-
+// The first n_tau ranks: sel[rank] = e and vertex rank's coordinates.
 // Correspondence indices outside the clouds set err and read point 0 instead.
 __global__ __launch_bounds__(kBlock) void gather_vertices(const float* __restrict__ src, int64_t src_stride,
                                                           const float* __restrict__ tgt, int64_t tgt_stride,
                                                           const int32_t* __restrict__ pairs,
-                                                          const int32_t* __restrict__ sel, int32_t n,
-                                                          float4* __restrict__ va, float4* __restrict__ vb,
-                                                          int32_t* __restrict__ err) {
-    for (int v = blockIdx.x * kBlock + threadIdx.x; v < n; v += gridDim.x * kBlock) {
-        const int64_t e = sel[v];
+                                                          const int32_t* __restrict__ rank, int64_t k, int32_t n_tau,
+                                                          int32_t* __restrict__ sel, float4* __restrict__ va,
+                                                          float4* __restrict__ vb, int32_t* __restrict__ err) {
+    for (int64_t e = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; e < k;
+         e += static_cast<int64_t>(gridDim.x) * kBlock) {
+        const int v = rank[e];
+        if (v >= n_tau) continue;
+        sel[v] = static_cast<int32_t>(e);
         int i = pairs[2 * e], j = pairs[2 * e + 1];
         if (i < 0 || i >= src_stride || j < 0 || j >= tgt_stride) {
             atomicOr(err, 1);
@@ -113,23 +128,56 @@ __device__ __forceinline__ bool compatible(float4 au, float4 bu, float4 av, floa
     return fabs(db - da) <= two_beta;
 }
 
+// The same decision from FP32 where it is certain: dx, dy, dz are rounded
+// differences of FP32 coordinates and the norm's relative error is below 4e-7,
+// so with 1e-6 (da + db) and the squares that underflow allowed for, only a
+// pair within that of the threshold (one in some ten thousand), and what is
+// not finite, takes the FP64 form (`sure` false).
+__device__ __forceinline__ bool compatible_fp32(float4 au, float4 bu, float4 av, float4 bv, float two_beta,
+                                                bool& sure) {
+    const float ax = au.x - av.x, ay = au.y - av.y, az = au.z - av.z;
+    const float bx = bu.x - bv.x, by = bu.y - bv.y, bz = bu.z - bv.z;
+    const float da = sqrtf(fmaf(az, az, fmaf(ay, ay, ax * ax)));
+    const float db = sqrtf(fmaf(bz, bz, fmaf(by, by, bx * bx)));
+    const float gap = fabsf(db - da) - two_beta;
+    sure = fabsf(gap) > fmaf(1e-6f, da + db + fabsf(two_beta), 1e-18f) && da + db < INFINITY;
+    return gap < 0.0f;
+}
+
+// One wavefront per row.  Two FP64 square roots per pair, and the loads of one
+// piece of 64 columns at a time, took 29 us (count) and 33 us (fill) for 2,780
+// vertices; the FP32 decision with four pieces in flight takes 17 and 23.
 template <bool kFill>
 __global__ __launch_bounds__(kBlock) void graph_rows(const float4* __restrict__ va, const float4* __restrict__ vb,
                                                      int32_t n, double beta, int32_t* __restrict__ deg,
                                                      const int32_t* __restrict__ off, int32_t* __restrict__ adj) {
+    constexpr int kCols = 4;  // 64-column pieces whose loads are in flight together
     const int lane = lane_id();
     const double two_beta = 2.0 * beta;
+    const float two_beta_f = static_cast<float>(two_beta);
     for (int64_t u = global_wave(); u < n; u += wave_count()) {
         const float4 au = va[u], bu = vb[u];
         int found = 0;
         int32_t* out = kFill ? adj + off[u] : nullptr;
-        for (int base = 0; base < n; base += kWave) {
-            const int v = base + lane;
-            const int vc = min(v, n - 1);  // unconditional loads; the mask applies afterwards
-            const bool e = v < n && v != u && compatible(au, bu, va[vc], vb[vc], two_beta);
-            const uint64_t b = ballot(e);
-            if (kFill && e) out[found + lanes_below(b)] = v;
-            found += __popcll(b);
+        for (int base = 0; base < n; base += kCols * kWave) {
+            float4 av[kCols], bv[kCols];
+#pragma unroll
+            for (int k = 0; k < kCols; ++k) {
+                const int vc = min(base + k * kWave + lane, n - 1);  // unconditional loads; the mask applies afterwards
+                av[k] = va[vc];
+                bv[k] = vb[vc];
+            }
+#pragma unroll
+            for (int k = 0; k < kCols; ++k) {
+                const int v = base + k * kWave + lane;
+                bool sure;
+                bool near = compatible_fp32(au, bu, av[k], bv[k], two_beta_f, sure);
+                if (ballot(!sure)) near = compatible(au, bu, av[k], bv[k], two_beta);  // uniform
+                const bool e = v < n && v != u && near;
+                const uint64_t b = ballot(e);
+                if (kFill && e) out[found + lanes_below(b)] = v;
+                found += __popcll(b);
+            }
         }
         if (!kFill && lane == 0) deg[u] = found;
     }
@@ -141,48 +189,82 @@ __global__ __launch_bounds__(kBlock) void graph_rows(const float4* __restrict__ 
 // a sweep that changes nothing proves a fixed point, and a fixed point reached
 // from above is the core numbers (if h[v] >= x, v has x neighbours with h >= x,
 // so {h >= x} lies in the x-core).  Updates are in place (a neighbour's newer,
-// smaller value only speeds convergence).  Sweep k runs only if sweep k - 1
-// changed something (flag[k] set); one wavefront per vertex.
-constexpr int kHSweeps = 48;  // sweeps launched; the block peel finishes graphs that need more
-constexpr int kHRegs = 8;     // neighbour values held in registers per lane (deg <= 512)
+// smaller value only speeds convergence).  One wavefront per vertex.
+// A sweep looks only at the vertices that the last one concerns (due[v] = its
+// number; flag = kDue): a vertex whose value fell from a to b concerns itself and the
+// neighbours with b < h <= a, of whose count it was one.  (A neighbour whose
+// value fell in the same sweep, and may have been read before it did, concerns
+// itself.)  After one that changed nothing the next looks at all (kAll), for rows
+// that name each other need not be taken on trust, and if that changes nothing
+// either, the values stand (kSettled).  A clique of true correspondences so is settled after two sweeps, and
+// the rest of the graph after some more of about 6 us, the latencies of one row;
+// re-reading all rows took 9 us a sweep (2,780 vertices, 2.8 million entries, 15
+// sweeps; the first 104 us where a row's values were read again for each step of
+// the search, now 20).  A row's loads are all in flight, and its values are searched in
+// registers.  Six rounds per launch, each from a copy of h in LDS, took 60 us a
+// launch: the copies of all blocks come from the same few lines.
+enum : int { kSettled = 0, kAll = 1, kDue = 2 };  // what the next sweep is to do
+constexpr int kHSweeps = 48;  // sweeps launched at most; the block peel finishes graphs that need more
+constexpr int kHChunk = 8;    // sweeps between two looks of the host at the convergence flag
+constexpr int kHRegs = 32;    // neighbour values held in registers per lane (deg <= 2048)
+static_assert(kHSweeps % kHChunk == 0, "whole chunks");
 
 __global__ __launch_bounds__(kBlock) void kcore_hinit(const int32_t* __restrict__ off, int32_t n,
-                                                      int32_t* __restrict__ h, int32_t* __restrict__ flag) {
-    for (int v = blockIdx.x * kBlock + threadIdx.x; v < n; v += gridDim.x * kBlock) h[v] = off[v + 1] - off[v];
-    for (int i = blockIdx.x * kBlock + threadIdx.x; i <= kHSweeps; i += gridDim.x * kBlock) flag[i] = i == 0;
+                                                      int32_t* __restrict__ h, int32_t* __restrict__ due,
+                                                      int32_t* __restrict__ flag, int32_t* __restrict__ info) {
+    if (blockIdx.x == 0 && threadIdx.x < 3) info[threadIdx.x] = 0;
+    for (int v = blockIdx.x * kBlock + threadIdx.x; v < n; v += gridDim.x * kBlock) {
+        h[v] = off[v + 1] - off[v];
+        due[v] = 0;
+    }
+    for (int i = blockIdx.x * kBlock + threadIdx.x; i <= kHSweeps; i += gridDim.x * kBlock) flag[i] = i == 0 ? kAll : kSettled;
 }
 
 __global__ __launch_bounds__(kBlock) void kcore_hsweep(const int32_t* __restrict__ off,
-                                                       const int32_t* __restrict__ adj, int32_t n, int32_t* h,
+                                                       const int32_t* __restrict__ adj, int32_t n, int32_t* h, int32_t* due,
                                                        int32_t* flag, int sweep, int32_t* __restrict__ info) {
-    if (flag[sweep] == 0) return;  // converged
     const int lane = lane_id();
+    const int todo = flag[sweep];
     bool changed = false;
     for (int64_t vw = global_wave(); vw < n; vw += wave_count()) {
         const int v = static_cast<int>(vw);
+        const int now = due[v];
         const int cap = h[v];
-        if (cap == 0) continue;
         const int b = off[v], deg = off[v + 1] - b;
+        if (todo == kSettled) return;  // looked at beside the row's own loads
+        if (cap == 0 || (todo == kDue && now < sweep)) continue;
         int hi = min(cap, deg);
         int lo = 0;
         int val[kHRegs];
         const bool in_regs = deg <= kHRegs * kWave;
+        if (in_regs) {
 #pragma unroll
-        for (int r = 0; r < kHRegs; ++r) {
-            const int t = r * kWave + lane;
-            val[r] = -1;
-            if (in_regs && t < deg) {
-                const int u = adj[b + t];
-                if (u < 0 || u >= n) info[2] = 1;  // not a vertex: reported, never followed
-                else val[r] = h[u];
+            for (int r = 0; r < kHRegs; ++r) {
+                const int t = r * kWave + lane;
+                val[r] = -1;
+                if (r * kWave < deg) val[r] = t < deg ? adj[b + t] : -1;  // uniform
             }
+            bool bad = false;
+#pragma unroll
+            for (int r = 0; r < kHRegs; ++r) {
+                if (r * kWave >= deg) continue;  // uniform
+                const int u = val[r];
+                const bool in = u >= 0 && u < n;
+                bad = bad || (!in && r * kWave + lane < deg);  // not a vertex: reported, never followed
+                const int w = h[in ? u : v];
+                val[r] = in ? w : -1;
+            }
+            if (bad) info[2] = 1;
         }
         // count of neighbour values >= x (from registers, or re-read for long rows)
         auto count_ge = [&](int x) {
             int c = 0;
             if (in_regs) {
 #pragma unroll
-                for (int r = 0; r < kHRegs; ++r) c += __popcll(ballot(val[r] >= x));
+                for (int r = 0; r < kHRegs; r += 4)
+                    if (r * kWave < deg)  // uniform
+                        c += __popcll(ballot(val[r] >= x)) + __popcll(ballot(val[r + 1] >= x)) +
+                             __popcll(ballot(val[r + 2] >= x)) + __popcll(ballot(val[r + 3] >= x));
             } else {
                 for (int t0 = 0; t0 < deg; t0 += kWave) {
                     const int t = t0 + lane;
@@ -197,10 +279,12 @@ __global__ __launch_bounds__(kBlock) void kcore_hsweep(const int32_t* __restrict
             }
             return c;
         };
-        if (count_ge(hi) >= hi) {
+        const int at_hi = count_ge(hi);
+        if (at_hi >= hi) {
             lo = hi;
         } else {
-            --hi;  // invariant: count_ge(lo) >= lo, count_ge(hi + 1) < hi + 1
+            lo = at_hi;  // below hi as many values reach at_hi at least
+            --hi;        // invariant: count_ge(lo) >= lo, count_ge(hi + 1) < hi + 1
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
                 if (count_ge(mid) >= mid) lo = mid;
@@ -208,27 +292,25 @@ __global__ __launch_bounds__(kBlock) void kcore_hsweep(const int32_t* __restrict
             }
         }
         if (lo < cap) {
-            if (lane == 0) h[v] = lo;
+            if (lane == 0) {
+                h[v] = lo;
+                due[v] = sweep + 1;
+            }
+            if (in_regs) {
+#pragma unroll
+                for (int r = 0; r < kHRegs; ++r)
+                    if (r * kWave < deg && val[r] > lo && val[r] <= cap) due[adj[b + r * kWave + lane]] = sweep + 1;
+            } else {
+                for (int t = lane; t < deg; t += kWave) {
+                    const int u = adj[b + t];
+                    if (u >= 0 && u < n && h[u] > lo && h[u] <= cap) due[u] = sweep + 1;
+                }
+            }
             changed = true;
         }
     }
-    if (changed && lane == 0) flag[sweep + 1] = 1;
-}
-
-// After the sweeps: if they converged, the core numbers are h (and their maximum
-// goes to info[0]); otherwise the block peel has written both.
-__global__ __launch_bounds__(kBlock) void kcore_hfinish(const int32_t* __restrict__ h, int32_t n,
-                                                        const int32_t* __restrict__ flag, int32_t* __restrict__ core,
-                                                        int32_t* __restrict__ info) {
-    if (flag[kHSweeps] != 0) return;
-    int mx = -1;
-    for (int v = blockIdx.x * kBlock + threadIdx.x; v < n; v += gridDim.x * kBlock) {
-        core[v] = h[v];
-        mx = max(mx, h[v]);
-    }
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) mx = max(mx, __shfl_xor(mx, d, kWave));
-    if (lane_id() == 0 && mx >= 0) atomicMax(info, mx);
+    if (changed && lane == 0) flag[sweep + 1] = kDue;
+    if (todo == kDue && blockIdx.x == 0 && threadIdx.x == 0) atomicMax(flag + sweep + 1, static_cast<int>(kAll));
 }
 
 // One block: core numbers of the graph (off, adj) on n <= kMaxKcore vertices.
@@ -245,7 +327,7 @@ __global__ __launch_bounds__(kPeelThreads) void kcore_peel(const int32_t* __rest
                                                            int32_t* __restrict__ core_out,
                                                            int32_t* __restrict__ info,
                                                            const int32_t* __restrict__ skip) {
-    if (skip && *skip == 0) return;  // the h-index sweeps converged
+    if (skip && *skip == kSettled) return;  // the h-index sweeps converged
     extern __shared__ int32_t s_mem[];
     int32_t* s_deg = s_mem;
     int16_t* s_core = reinterpret_cast<int16_t*>(s_deg + n);
@@ -325,20 +407,39 @@ __global__ __launch_bounds__(kPeelThreads) void kcore_peel(const int32_t* __rest
 
 size_t kcore_lds_bytes(int32_t n) { return static_cast<size_t>(n) * 8 + 16; }
 
-// members: vertices with the largest core number, ascending (one block).
-__global__ __launch_bounds__(kPeelThreads) void kcore_members(const int32_t* __restrict__ core, int32_t n,
-                                                              int32_t* __restrict__ members,
+// One block: core numbers (h, where the sweeps converged; else core and its
+// maximum come from the peel) and members, the vertices with the largest core
+// number, ascending.
+__global__ __launch_bounds__(kPeelThreads) void kcore_members(const int32_t* __restrict__ h,
+                                                              const int32_t* __restrict__ unsettled, int32_t* core,
+                                                              int32_t n, int32_t* __restrict__ members,
                                                               int32_t* __restrict__ info) {
-    __shared__ int s_base;
+    __shared__ int s_base, s_max;
     __shared__ int s_wave[kPeelThreads / kWave];
-    const int mx = info[0];
     const int lane = lane_id();
     const int wv = threadIdx.x / kWave;
-    if (threadIdx.x == 0) s_base = 0;
+    const bool settled = *unsettled == kSettled;
+    const int32_t* from = settled ? h : core;
+    if (threadIdx.x == 0) {
+        s_base = 0;
+        s_max = settled ? -1 : info[0];
+    }
     __syncthreads();
+    if (settled) {
+        int mx = -1;
+        for (int v = threadIdx.x; v < n; v += kPeelThreads) {
+            core[v] = h[v];
+            mx = max(mx, h[v]);
+        }
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) mx = max(mx, __shfl_xor(mx, d, kWave));
+        if (lane == 0) atomicMax(&s_max, mx);
+        __syncthreads();
+    }
+    const int mx = s_max;
     for (int v0 = 0; v0 < n; v0 += kPeelThreads) {
         const int v = v0 + threadIdx.x;
-        const bool in = v < n && core[v] == mx;
+        const bool in = v < n && from[v] == mx;
         const uint64_t b = ballot(in);
         if (lane == 0) s_wave[wv] = __popcll(b);
         __syncthreads();
@@ -353,7 +454,10 @@ __global__ __launch_bounds__(kPeelThreads) void kcore_members(const int32_t* __r
         }
         __syncthreads();
     }
-    if (threadIdx.x == 0) info[1] = s_base;
+    if (threadIdx.x == 0) {
+        info[0] = mx;
+        info[1] = s_base;
+    }
 }
 
 struct GraphWs {
@@ -375,7 +479,7 @@ GraphWs carve_graph(Carver& c, int64_t n_corr, int32_t n_tau) {
     w.vb = c.take<float4>(static_cast<size_t>(std::max(n_tau, 1)));
     w.deg = c.take<int32_t>(static_cast<size_t>(n_tau) + 1);
     w.nnz = c.take<int64_t>(1);
-    w.err = c.take<int32_t>(1);
+    w.err = c.take<int32_t>(2);  // an index outside its cloud; a bounded wait that gave up
     w.scan_tmp = c.take<int64_t>(scan_temp_elems(static_cast<int64_t>(n_tau) + 1));
     return w;
 }
@@ -383,6 +487,7 @@ GraphWs carve_graph(Carver& c, int64_t n_corr, int32_t n_tau) {
 struct KcoreWs {
     int32_t* info;
     int32_t* h;
+    int32_t* due;
     int32_t* flag;
 };
 
@@ -390,6 +495,7 @@ KcoreWs carve_kcore(Carver& c, int32_t n) {
     KcoreWs w;
     w.info = c.take<int32_t>(3);  // max core, members, bad index flag
     w.h = c.take<int32_t>(static_cast<size_t>(std::max(n, 1)));
+    w.due = c.take<int32_t>(static_cast<size_t>(std::max(n, 1)));
     w.flag = c.take<int32_t>(kHSweeps + 1);
     return w;
 }
@@ -422,31 +528,33 @@ kmg_status corr_graph(const float* src, int64_t src_stride, const float* tgt, in
         KMG_TRY(fill_u32(reinterpret_cast<uint32_t*>(off), 0u, 1, s));
         return KMG_OK;
     }
-    ratio_keys<<<grid_cap(n_corr, kBlock), kBlock, 0, s>>>(d1, d2, n_corr, w.keys);
+    FillJobs fills{};
+    fills.job[0] = FillJob{w.err, 0ull, 2, 4};
+    fills.job[1] = FillJob{w.deg, 0ull, static_cast<int64_t>(n) + 1, 4};
+    fills.job[2] = FillJob{w.scan_tmp, 0ull, static_cast<int64_t>(scan_temp_elems(static_cast<int64_t>(n) + 1)), 8};
+    fills.n_jobs = 3;
+    ratio_keys<<<grid_cap(n_corr, kBlock), kBlock, 0, s>>>(d1, d2, n_corr, w.keys, w.rank, fills);
     KMG_TRY(launch_status());
-    KMG_TRY(fill_u32(reinterpret_cast<uint32_t*>(w.rank), 0u, static_cast<size_t>(n_corr), s));
     {
         const int64_t tiles = (n_corr + kBlock - 1) / kBlock;
         const dim3 grid(static_cast<unsigned>(tiles), static_cast<unsigned>(std::min<int64_t>(tiles, kRankTiles)));
         rank_count<<<grid, kBlock, 0, s>>>(w.keys, n_corr, w.rank);
         KMG_TRY(launch_status());
     }
-    rank_emit<<<grid_cap(n_corr, kBlock), kBlock, 0, s>>>(w.rank, n_corr, n_tau, sel);
+    gather_vertices<<<grid_cap(n_corr, kBlock), kBlock, 0, s>>>(src, src_stride, tgt, tgt_stride, pairs, w.rank,
+                                                                n_corr, n_tau, sel, w.va, w.vb, w.err);
     KMG_TRY(launch_status());
-    KMG_TRY(fill_u32(reinterpret_cast<uint32_t*>(w.err), 0u, 1, s));
-    gather_vertices<<<grid_cap(n, kBlock), kBlock, 0, s>>>(src, src_stride, tgt, tgt_stride, pairs, sel, n, w.va,
-                                                           w.vb, w.err);
-    KMG_TRY(launch_status());
-    KMG_TRY(fill_u32(reinterpret_cast<uint32_t*>(w.deg), 0u, static_cast<size_t>(n) + 1, s));
     graph_rows<false><<<grid_cap(n, kBlock / kWave), kBlock, 0, s>>>(w.va, w.vb, n, beta, w.deg, nullptr, nullptr);
     KMG_TRY(launch_status());
-    KMG_TRY(scan_exclusive(w.deg, off, static_cast<int64_t>(n) + 1, w.nnz, w.scan_tmp, s));
+    KMG_TRY(scan_exclusive_onepass(w.deg, off, static_cast<int64_t>(n) + 1, w.nnz,
+                                   reinterpret_cast<uint64_t*>(w.scan_tmp), w.err + 1, s));
     int64_t nnz = 0;
-    int32_t err = 0;
+    int32_t err[2] = {0, 0};
     Report r;
     KMG_TRY(r.post(w.nnz, sizeof(nnz), w.err, sizeof(err), s));
-    KMG_TRY(r.wait(&nnz, &err));
-    if (err) return KMG_ERR_RANGE;
+    KMG_TRY(r.wait(&nnz, err));
+    if (err[0]) return KMG_ERR_RANGE;
+    if (err[1]) return KMG_ERR_DEVICE;
     *nnz_host = nnz;
     if (nnz > adj_cap) return KMG_ERR_CAPACITY;
     graph_rows<true><<<grid_cap(n, kBlock / kWave), kBlock, 0, s>>>(w.va, w.vb, n, beta, nullptr, off, adj);
@@ -462,7 +570,6 @@ kmg_status max_kcore(const int32_t* off, const int32_t* adj, int32_t n, int32_t*
     *n_members_host = 0;
     *max_core_host = -1;
     if (n == 0) return KMG_OK;
-    KMG_TRY(fill_u32(reinterpret_cast<uint32_t*>(w.info), 0u, 3, s));
     const size_t lds = kcore_lds_bytes(n);
     if (lds > 65536) {
         static const hipError_t raised = hipFuncSetAttribute(reinterpret_cast<const void*>(&kcore_peel),
@@ -470,26 +577,35 @@ kmg_status max_kcore(const int32_t* off, const int32_t* adj, int32_t n, int32_t*
                                                              static_cast<int>(kcore_lds_bytes(kMaxKcore)));
         if (raised != hipSuccess) return KMG_ERR_RANGE;  // this device cannot hold the graph's state on chip
     }
-    {
-        const unsigned g = grid_cap(std::max<int64_t>(n, kHSweeps + 1), kBlock);
-        kcore_hinit<<<g, kBlock, 0, s>>>(off, n, w.h, w.flag);
-        KMG_TRY(launch_status());
-        const unsigned gw = grid_cap(n, kBlock / kWave);
-        for (int k = 0; k < kHSweeps; ++k) {
-            kcore_hsweep<<<gw, kBlock, 0, s>>>(off, adj, n, w.h, w.flag, k, w.info);
+    kcore_hinit<<<grid_cap(std::max<int64_t>(n, kHSweeps + 1), kBlock), kBlock, 0, s>>>(off, n, w.h, w.due, w.flag, w.info);
+    KMG_TRY(launch_status());
+    // Sweeps in chunks, one chunk ahead of the host's look at the flag: launches past convergence
+    // do nothing, but cost 2 us each (26 of the 48 for 2,780 vertices).
+    Report seen[2];
+    bool settled = false;
+    for (int k = 0, chunk = 0; k < kHSweeps && !settled; ++chunk) {
+        for (const int end = k + kHChunk; k < end; ++k) {
+            kcore_hsweep<<<grid_cap(n, kBlock / kWave), kBlock, 0, s>>>(off, adj, n, w.h, w.due, w.flag, k, w.info);
             KMG_TRY(launch_status());
         }
+        KMG_TRY(seen[chunk & 1].post(w.flag + k, sizeof(int32_t), nullptr, 0, s));
+        int32_t more = kDue;
+        if (chunk > 0) KMG_TRY(seen[(chunk - 1) & 1].wait(&more));
+        settled = more == kSettled;
     }
-    kcore_peel<<<1, kPeelThreads, lds, s>>>(off, adj, n, core, w.info, w.flag + kHSweeps);
-    KMG_TRY(launch_status());
-    kcore_hfinish<<<grid_cap(n, kBlock), kBlock, 0, s>>>(w.h, n, w.flag, core, w.info);
-    KMG_TRY(launch_status());
-    kcore_members<<<1, kPeelThreads, 0, s>>>(core, n, members, w.info);
+    if (!settled) {
+        kcore_peel<<<1, kPeelThreads, lds, s>>>(off, adj, n, core, w.info, w.flag + kHSweeps);
+        KMG_TRY(launch_status());
+    }
+    kcore_members<<<1, kPeelThreads, 0, s>>>(w.h, w.flag + kHSweeps, core, n, members, w.info);
     KMG_TRY(launch_status());
     int32_t info[3];
     Report r;
     KMG_TRY(r.post(w.info, sizeof(info), nullptr, 0, s));
     KMG_TRY(r.wait(info));
+    int32_t last = 0;
+    for (Report& q : seen)
+        if (q.posted()) KMG_TRY(q.wait(&last));  // here already
     if (info[2]) return KMG_ERR_RANGE;
     *max_core_host = info[0];
     *n_members_host = info[1];

@@ -278,6 +278,7 @@ class Report {
     ~Report();
     kmg_status post(const void* a, size_t a_bytes, const void* b, size_t b_bytes, hipStream_t s);
     kmg_status wait(void* a, void* b = nullptr);
+    bool posted() const { return posted_; }
 
   private:
     ReportSlot* slot_ = nullptr;

@@ -409,7 +409,8 @@ def corr_graph(src_xyz, tgt_xyz, pairs, d1, d2, n_tau=3000, beta=0.45, ws=None):
     w = _ws(ws).get(int(lib.kmg_workspace_bytes(OP_GRAPH, k, n_tau, None)))
     n_sel = C.c_int32(0)
     nnz = C.c_int64(0)
-    cap = max(1, min(k, n_tau) * 64)
+    m = min(k, n_tau)
+    cap = max(1, min(m * (m - 1), max(m * 64, 1 << 22)))  # at most 16 MB for a guess; a second run costs a whole one
     for _ in range(2):
         adj = torch.empty(cap, dtype=torch.int32, device=dev)
         st = lib.kmg_corr_graph(_ptr(src_xyz), src_xyz.shape[1], _ptr(tgt_xyz), tgt_xyz.shape[1], _ptr(pairs),
