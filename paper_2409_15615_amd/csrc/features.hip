@@ -35,6 +35,12 @@ constexpr int kBlock = 256;
 constexpr int64_t kItemWork = 32;
 constexpr int kWaves = kBlock / kWave;
 constexpr int kBatch = 8;          // SPFH rows loaded together in the FPFH sum
+// Long lists differ in length: many small shares, which the dispatcher evens
+// out (a cloud of 215,000 points, mean 54: 244 -> 212 us against 2,048 blocks).
+// Short lists in pairs: one resident round (64 pairs, 3.6 million points: 2.47
+// -> 2.35 ms).
+constexpr unsigned kSpfhBlocks = 8192;
+constexpr unsigned kSpfhPairBlocks = 4 * kCUs;
 
 struct V3f {
     float x, y, z;
@@ -499,36 +505,39 @@ __global__ __launch_bounds__(kBlock) void fpfh_pairs(const float* __restrict__ x
                 w = (1.0 / sqrt(d2_exact(qx, qy, qz, kx, ky, kz))) * inv100[k];
             }
             const uint32_t bm = static_cast<uint32_t>(ballot(use) >> sh);
+            const int nuse = __popc(bm);
+            // in order: the used neighbours, then places of weight 0 (what their rows hold is finite)
+            const int at = use ? __popc(bm & below) : nuse + __popc(~bm & below);
             __builtin_amdgcn_wave_barrier();
             if (use) {
                 // the lane's whole row in 16-byte pieces, every row of the round in flight at once
-                const int at = __popc(bm & below);
                 const uint4* src = reinterpret_cast<const uint4*>(cnt16 + static_cast<int64_t>(k) * R);
                 uint4* dst = s_rows + at * R8;
                 for (int i = 0; i < R8; ++i) dst[i] = src[i];
-                s_w[wv][hf][at] = w;
             }
+            s_w[wv][hf][at] = use ? w : 0.0;
             __builtin_amdgcn_wave_barrier();
-            const int nuse = __popc(bm);
             const int numax = max(nuse, __shfl_xor(nuse, kHalf, kWave));
             // the rows summed in ascending neighbour order, bin by bin from LDS
-            const uint16_t* rows = reinterpret_cast<const uint16_t*>(s_rows);
-            for (int j = 0; j < numax; j += kBatchNarrow) {
+            const uint16_t* r0 = reinterpret_cast<const uint16_t*>(s_rows) + lb0;
+            const uint16_t* r1 = reinterpret_cast<const uint16_t*>(s_rows) + lb1;
+            const double* ws = s_w[wv][hf];
+            for (int j = 0; j < numax; j += kBatchNarrow) {  // kBatchNarrow divides the 32 places
                 double v0[kBatchNarrow], v1[kBatchNarrow], wj[kBatchNarrow];
 #pragma unroll
                 for (int u = 0; u < kBatchNarrow; ++u) {
-                    const int r = min(j + u, kHalf - 1);
-                    v0[u] = static_cast<double>(rows[r * R + lb0]);
-                    v1[u] = static_cast<double>(rows[r * R + lb1]);
-                    wj[u] = s_w[wv][hf][r];
+                    v0[u] = static_cast<double>(r0[u * R]);
+                    v1[u] = static_cast<double>(r1[u * R]);
+                    wj[u] = ws[u];
                 }
 #pragma unroll
                 for (int u = 0; u < kBatchNarrow; ++u) {
-                    if (j + u < nuse) {
-                        acc0 = acc0 + wj[u] * v0[u];
-                        acc1 = acc1 + wj[u] * v1[u];
-                    }
+                    acc0 = acc0 + wj[u] * v0[u];
+                    acc1 = acc1 + wj[u] * v1[u];
                 }
+                r0 += kBatchNarrow * R;
+                r1 += kBatchNarrow * R;
+                ws += kBatchNarrow;
             }
             __builtin_amdgcn_wave_barrier();
         }
@@ -769,9 +778,13 @@ kmg_status fpfh_as(const float* xyz, int64_t stride, int64_t m_cap, const uint8_
     if (kPairs) {
         // dynamic LDS: one SPFH row per lane of the block
         const size_t rows_lds = static_cast<size_t>(kBlock) * spfh_row(H) * sizeof(uint16_t);
-        fpfh_pairs<kRows><<<grid_cap((m_cap + 1) / 2, kWaves), kBlock, rows_lds, s>>>(xyz, stride, m_cap, flags, jflag, j_idx,
-                                                                              off, nb, H, cnt16, Pq, inv100, fpfh_out,
-                                                                              (tuning().xcd_split >> 1) & 1, st);
+        // one round of blocks: each runs as long as the launch, and a few left for a second round
+        // run alone (7 of 8 blocks per CU at once for rows of 33: 64 pairs 3.6 -> 3.0 ms)
+        const size_t used = rows_lds + sizeof(double) * kBlock;
+        const unsigned per_cu = static_cast<unsigned>(std::min<size_t>(std::max<size_t>(kLdsBytes / used, 1), 8));
+        const unsigned grid = std::min(grid_for((m_cap + 1) / 2, kWaves), per_cu * kCUs);
+        fpfh_pairs<kRows><<<grid, kBlock, rows_lds, s>>>(xyz, stride, m_cap, flags, jflag, j_idx, off, nb, H, cnt16, Pq,
+                                                         inv100, fpfh_out, (tuning().xcd_split >> 1) & 1, st);
     } else {
         fpfh_kernel<kRows><<<grid_cap(m_cap, kWaves), kBlock, 0, s>>>(xyz, stride, m_cap, flags, jflag, j_idx, off,
                                                                      nb, H, cnt16, Pq, inv100, fpfh_out,
@@ -884,14 +897,14 @@ kmg_status spfh_batch(const CloudDev* cl, const float* xyz, int64_t stride, cons
         // the range (0: one point per wavefront, kMaxDegree: two) the choice is made
         // here, and only that form is launched
         if (pair_mean < kMaxDegree) {
-            spfh_kernel<<<grid_cap(m_cap, kWaves), kBlock, 0, s>>>(cl, xyz, stride, kept_cloud, m_cap, nrm,
+            spfh_kernel<<<std::min(grid_for(m_cap, kWaves), kSpfhBlocks), kBlock, 0, s>>>(cl, xyz, stride, kept_cloud, m_cap, nrm,
                                                                   nrm_stride, flags, off, nb, H, w.cnt16, spfh_out,
                                                                   w.Pq, w.inv100, w.jflag, pair_mean,
                                                                   tuning().xcd_split & 1, st);
             KMG_TRY(launch_status());
         }
         if (pair_mean > 0) {
-            spfh_pairs<<<grid_cap((m_cap + 1) / 2, kWaves), kBlock, 0, s>>>(cl, xyz, stride, kept_cloud, m_cap, nrm,
+            spfh_pairs<<<std::min(grid_for((m_cap + 1) / 2, kWaves), kSpfhPairBlocks), kBlock, 0, s>>>(cl, xyz, stride, kept_cloud, m_cap, nrm,
                                                                            nrm_stride, flags, off, nb, H, w.cnt16,
                                                                            spfh_out, w.Pq, w.inv100, w.jflag,
                                                                            pair_mean, tuning().xcd_split & 1, st);

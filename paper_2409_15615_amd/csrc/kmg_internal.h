@@ -27,6 +27,8 @@ constexpr int kListSmall = 1024;                             // LDS neighbour li
 constexpr int kMaxDegree = 8192;                             // largest |N(q)| accepted
 constexpr int kMaxBins = 32;                                 // largest H (3H <= 96 descriptor values)
 constexpr int kMaxMatchDim = 64;                             // longest descriptor the matcher takes
+constexpr unsigned kCUs = 256;
+constexpr size_t kLdsBytes = 160 * 1024;                       // per CU
 constexpr int kPersistBlocks = 2048;                         // grid of the grid-stride kernels
 
 // Strict radius test d2 < r^2: an FP32 screen decides everything farther than
