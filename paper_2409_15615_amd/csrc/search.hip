@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kBlock) void cell_insert(const CloudDev* __restrict
         const LaneRun run = lane_run(key);
         int h = -1;
         if (run.head && key != kEmptyKey) {
-            h = static_cast<int>(hash_insert(keys, mask, key));
+            h = static_cast<int>(hash_insert(keys, mask, key, cell_home(key, mask)));
             atomicAdd(cnt + h, run.len);
         }
         h = __shfl(h, run.lead, kWave);
@@ -199,7 +199,8 @@ __global__ __launch_bounds__(kWaves* kWave) void radius_search(const CloudDev* _
             const int64_t cx = cell_coord(qp.x, inv_c) + (lane % 3) - 1;
             const int64_t cy = cell_coord(qp.y, inv_c) + (lane / 3) % 3 - 1;
             const int64_t cz = cell_coord(qp.z, inv_c) + lane / 9 - 1;
-            const int h = hash_find(g.keys, g.mask, pack_key(c, cx, cy, cz));
+            const uint64_t key = pack_key(c, cx, cy, cz);
+            const int h = hash_find(g.keys, g.mask, key, cell_home(key, g.mask));
             if (h >= 0) {
                 cs = g.start[h];
                 cc = g.count[h];
@@ -320,7 +321,8 @@ __global__ __launch_bounds__(kWaves* kWave) void radius_count2(const CloudDev* _
                 const int64_t cx = cell_coord(qp.x, inv_c) + (cell % 3) - 1;
                 const int64_t cy = cell_coord(qp.y, inv_c) + (cell / 3) % 3 - 1;
                 const int64_t cz = cell_coord(qp.z, inv_c) + cell / 9 - 1;
-                const int h = hash_find(g.keys, g.mask, pack_key(c, cx, cy, cz));
+                const uint64_t key = pack_key(c, cx, cy, cz);
+            const int h = hash_find(g.keys, g.mask, key, cell_home(key, g.mask));
                 if (h >= 0) {
                     cs[u] = g.start[h];
                     cc[u] = g.count[h];
@@ -425,7 +427,8 @@ __global__ __launch_bounds__(kWaves* kWave) void radius_fill2(const CloudDev* __
             const int64_t cx = cell_coord(qp.x, inv_c) + (hl % 3) - 1;
             const int64_t cy = cell_coord(qp.y, inv_c) + (hl / 3) % 3 - 1;
             const int64_t cz = cell_coord(qp.z, inv_c) + hl / 9 - 1;
-            const int h = hash_find(g.keys, g.mask, pack_key(c, cx, cy, cz));
+            const uint64_t key = pack_key(c, cx, cy, cz);
+            const int h = hash_find(g.keys, g.mask, key, cell_home(key, g.mask));
             if (h >= 0) {
                 cs = g.start[h];
                 cc = g.count[h];

@@ -47,7 +47,7 @@ __global__ __launch_bounds__(kBlock) void voxel_insert(const CloudDev* __restric
         const LaneRun run = lane_run(key);
         int h = -1;
         if (run.head && key != kEmptyKey) {
-            h = static_cast<int>(hash_insert(keys, mask, key));
+            h = static_cast<int>(hash_insert(keys, mask, key, hash_key(key) & mask));
             atomicMin(mins + h, static_cast<int32_t>(t));
         }
         h = __shfl(h, run.lead, kWave);
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(kBlock) void voxel_emit(const CloudDev* __restrict_
             const LaneRun run = lane_run(ckey);
             int h = -1;
             if (run.head && ckey != kEmptyKey) {
-                h = static_cast<int>(hash_insert(gi.keys, gi.mask, ckey));
+                h = static_cast<int>(hash_insert(gi.keys, gi.mask, ckey, cell_home(ckey, gi.mask)));
                 atomicAdd(gi.cnt + h, run.len);
             }
             h = __shfl(h, run.lead, kWave);  // the run's slot, in packed lanes
