@@ -22,6 +22,8 @@
 // Eq. A5); the query's own SPFH value is 100 c / P_q, divided exactly.
 #include <math.h>
 
+#include <type_traits>
+
 #include "kmg_device.h"
 
 namespace kmg {
@@ -177,6 +179,22 @@ __device__ __forceinline__ int cloud_of(const int32_t* kept_cloud, int64_t q) {
     return kept_cloud ? kept_cloud[q] : 0;
 }
 
+// Row q of the SPFH counts: the point's coordinates, its number of valid
+// neighbours (itself among them; 0 when it is not in B), then the 3H counts, so
+// that the FPFH sum finds all that it needs of a neighbour in one row.
+__device__ __forceinline__ uint16_t* spfh_counts(uint16_t* cnt16, int64_t q, int H) {
+    return cnt16 + q * spfh_row(H) + kSpfhHead;
+}
+__device__ __forceinline__ void spfh_head(uint16_t* cnt16, int64_t q, int H, const float* xyz, int64_t stride,
+                                          int n_valid) {
+    uint16_t* row = cnt16 + q * spfh_row(H);
+    float* p = reinterpret_cast<float*>(row);
+    p[0] = xyz[q];
+    p[1] = xyz[stride + q];
+    p[2] = xyz[2 * stride + q];
+    row[kSpfhHead - 1] = static_cast<uint16_t>(n_valid);
+}
+
 // Lists of a mean of at most kHalfListMean entries per point: two points per
 // wavefront, one per half of 32 lanes (each lane one neighbour of its half's
 // point per round, adding its three bins to the half's LDS histogram with
@@ -264,7 +282,8 @@ __device__ __forceinline__ void spfh_pairs_body(const CloudDev* __restrict__ cl,
         }
         __builtin_amdgcn_wave_barrier();  // the histogram is free for the next pair of points
         if (!live) continue;
-        uint16_t* row = cnt16 + q * spfh_row(H);
+        uint16_t* row = spfh_counts(cnt16, q, H);
+        if (hl == 0) spfh_head(cnt16, q, H, xyz, stride, has_b ? n_valid : 0);
         if (!has_b) {
             for (int t = hl; t < D; t += kHalf) {
                 row[t] = 0;
@@ -312,8 +331,9 @@ __device__ __forceinline__ void spfh_point(const CloudDev* __restrict__ cl, cons
     const int lane = lane_id();
     const int D = 3 * H;
     const int64_t s2 = 2 * stride, n2 = 2 * nrm_stride;
-    uint16_t* row = cnt16 + q * spfh_row(H);
+    uint16_t* row = spfh_counts(cnt16, q, H);
     if (!(flags[q] & 1)) {
+        if (lane == 0) spfh_head(cnt16, q, H, xyz, stride, 0);
         for (int t = lane; t < D; t += kWave) {
             row[t] = 0;
             if (spfh_out) spfh_out[q * D + t] = 0.0f;
@@ -381,6 +401,7 @@ __device__ __forceinline__ void spfh_point(const CloudDev* __restrict__ cl, cons
         }
     }
     if (lane == 0) {
+        spfh_head(cnt16, q, H, xyz, stride, n_valid);
         Pq[q] = P;
         inv100[q] = P > 0 ? 100.0 / static_cast<double>(P) : 0.0;
         jflag[q] = (n_valid >= cl[cloud_of(kept_cloud, q)].tau_j) ? 1 : 0;
@@ -434,95 +455,132 @@ __global__ __launch_bounds__(kBlock) void spfh_kernel(const CloudDev* __restrict
                    jflag, st, q, s_hist[threadIdx.x / kWave], prow);
 }
 
-// FPFH of rows of at most 64 values over the J list, two points per
-// wavefront: a half of 32 lanes per point, lane l of the half summing bins l
-// and l + 32.  The neighbours of a round of 32 are compacted in order into
-// the half's LDS list and their SPFH rows summed in that order, term by term
-// the sum fpfh_kernel forms.  The rows of the other kept points are zeroed.
-template <int kBatchNarrow>
-__global__ __launch_bounds__(kBlock) void fpfh_pairs(const float* __restrict__ xyz, int64_t stride, int64_t m_cap,
-                                                     const uint8_t* __restrict__ flags,
-                                                     const int32_t* __restrict__ jflag,
+// Places of a group's round, whole steps of the sum; rows of the block that the
+// sums may read (a group's last step runs into the next group's).
+__host__ __device__ constexpr int fpfh_places(int batch, int g) { return (g + batch - 1) / batch * batch; }
+__host__ __device__ constexpr int fpfh_lds_rows(int batch, int g) {
+    return (kWaves * (kWave / g) - 1) * g + fpfh_places(batch, g);
+}
+
+// FPFH of rows of at most 64 values over the J list, several points per
+// wavefront: a group of kG lanes per point, lane l of the group summing bins l
+// and l + kG (three points for up to 42 values: with two, 31 of 32 lanes had no
+// second bin to sum at 33 values).  The neighbours of a round of kG are compacted
+// in order into the group's LDS list and their SPFH rows summed in that order,
+// term by term the sum fpfh_kernel forms.  The rows of the other kept points are
+// zeroed.
+// Bound by the gather: a chain of loads per point (its list, the rows) and the
+// lines these touch.  So a neighbour is one row, coordinates included (apart they
+// were four more lines each), and the next point's place in the lists and first
+// neighbours are loaded while this one's rows are summed: 64 pairs (2 million
+// points) 3.01 -> 1.73 ms, a cloud of 215,000 232 -> 189 us.
+template <int kBatchNarrow, int kG>
+__global__ __launch_bounds__(kBlock) void fpfh_pairs(int64_t m_cap, const int32_t* __restrict__ jflag,
                                                      const int32_t* __restrict__ j_list,
                                                      const int32_t* __restrict__ off,
                                                      NbrLists nb, int H,
-                                                     const uint16_t* __restrict__ cnt16,
-                                                     const int32_t* __restrict__ Pq,
-                                                     const double* __restrict__ inv100, float* __restrict__ fpfh,
+                                                     const uint16_t* __restrict__ cnt16, float* __restrict__ fpfh,
                                                      int xcd, const DevStatus* st) {
 #pragma clang fp contract(off)
-    constexpr int kHalf = kWave / 2;
-    __shared__ double s_w[kWaves][2][kHalf];
-    // the SPFH rows of a round of 32 neighbours, one per lane, R entries each (dynamic)
+    constexpr int kPts = kWave / kG;
+    constexpr int kPlaces = fpfh_places(kBatchNarrow, kG);
+    __shared__ double s_w[kWaves][kPts][kPlaces];
+    // the SPFH rows of a round of kG neighbours, one per lane, R entries each (dynamic)
     extern __shared__ uint4 s_dyn[];
     const int wv = threadIdx.x / kWave;
     const int lane = lane_id();
-    const int hf = lane / kHalf, hl = lane % kHalf, sh = kHalf * hf;
-    const uint32_t below = (1u << hl) - 1u;
+    const bool in = lane < kPts * kG;  // lanes past the last group take part in nothing
+    const int gr = in ? lane / kG : kPts - 1, gl = in ? lane % kG : 0, sh = kG * gr;
+    const uint32_t group = static_cast<uint32_t>((1ull << kG) - 1), below = (1u << gl) - 1u;
     const int64_t m = clamp_count(st->m_kept, m_cap);
     if (st->err_range || st->err_capacity) return;  // the neighbour lists are incomplete
     const int D = 3 * H;
     const int R = spfh_row(H);
     const int R8 = R / 8;  // 16-byte pieces of a row
-    uint4* s_rows = s_dyn + (wv * 2 + hf) * kHalf * R8;
-    const int64_t s2 = 2 * stride;
+    uint4* s_rows = s_dyn + (wv * kPts + gr) * kG * R8;
+    if (gl < kPlaces - kG) s_w[wv][gr][kG + gl] = 0.0;  // the places past the group stay empty
     const int64_t gt = static_cast<int64_t>(gridDim.x) * kBlock;
     for (int64_t t = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; t < m * D; t += gt)
         if (!jflag[t / D]) fpfh[t] = 0.0f;
     const int64_t n_j = clamp_count(st->n_j, m);
     const int prow = nb.pad ? pad_stride(nb.pad_cap, m) : 0;
-    const XcdItems it = xcd ? xcd_items((n_j + 1) / 2, off[m] + kItemWork * n_j,
-                                        [&](int64_t i) { return off[j_list[2 * i]] + kItemWork * 2 * i; })
-                            : cyclic_items((n_j + 1) / 2);
+    const XcdItems it = xcd ? xcd_items((n_j + kPts - 1) / kPts, off[m] + kItemWork * n_j,
+                                        [&](int64_t i) { return off[j_list[kPts * i]] + kItemWork * kPts * i; })
+                            : cyclic_items((n_j + kPts - 1) / kPts);
+    const uint4* rows_g = reinterpret_cast<const uint4*>(cnt16);
+    // the point of an item, its list's bounds, its first round of neighbours (-1: none)
+    const auto point_of = [&](int64_t pw) {
+        return in && pw < it.end && kPts * pw + gr < n_j ? j_list[kPts * pw + gr] : -1;
+    };
+    const auto most = [&](int v) {  // over the groups
+        int r = __builtin_amdgcn_readlane(v, 0);
+#pragma unroll
+        for (int g = 1; g < kPts; ++g) r = max(r, __builtin_amdgcn_readlane(v, g * kG));
+        return r;
+    };
+    const auto first_of = [&](int q, int b, int e) {
+        return gl < e - b ? list_of(nb, prow, q, b, e)[gl] : -1;
+    };
+    int q = point_of(it.first), q1 = point_of(it.first + it.stride);
+    int b = 0, e = 0;
+    if (q >= 0) {
+        b = off[q];
+        e = off[q + 1];
+    }
+    int k = first_of(q, b, e);
+    // lanes own bins gl and gl + kG; lanes past D read bin D - 1 and are never stored
+    const int lb0 = kSpfhHead + min(gl, D - 1), lb1 = kSpfhHead + min(gl + kG, D - 1);
     for (int64_t pw = it.first; pw < it.end; pw += it.stride) {
-        const bool live = 2 * pw + hf < n_j;
-        const int64_t q = live ? j_list[2 * pw + hf] : 0;
-        float qx = 0.f, qy = 0.f, qz = 0.f;
-        int b = 0, e = 0;
-        if (live) {
-            qx = xyz[q];
-            qy = xyz[stride + q];
-            qz = xyz[s2 + q];
-            b = off[q];
-            e = off[q + 1];
+        const int q2 = point_of(pw + 2 * it.stride);
+        int b1 = 0, e1 = 0, k1 = -1;
+        if (q1 >= 0) {
+            b1 = off[q1];
+            e1 = off[q1 + 1];
         }
+        const uint16_t* own = cnt16 + static_cast<int64_t>(max(q, 0)) * R;
+        const uint4 head = *reinterpret_cast<const uint4*>(own);
+        const int own0 = own[lb0], own1 = own[lb1];
+        const float qx = __uint_as_float(head.x), qy = __uint_as_float(head.y), qz = __uint_as_float(head.z);
         const int len = e - b;
         const int32_t* lp = list_of(nb, prow, q, b, e);
-        const int lmax = max(len, __shfl_xor(len, kHalf, kWave));
-        // lanes own bins hl and hl + 32; lanes past D read bin D - 1 and are never stored
-        const int lb0 = min(hl, D - 1), lb1 = min(hl + kHalf, D - 1);
+        const int lmax = most(len);
         double acc0 = 0.0, acc1 = 0.0;
-        for (int base = 0; base < lmax; base += kHalf) {
+        for (int base = 0; base < lmax; base += kG) {
+            if (base > 0) k = in && base + gl < len ? lp[base + gl] : -1;
             bool use = false;
             double w = 0.0;
-            int k = 0;
-            if (base + hl < len) {
-                k = lp[base + hl];
-                const float kx = xyz[k], ky = xyz[stride + k], kz = xyz[s2 + k];
-                use = (k != q) && (flags[k] & 1);
-                // the weight of SPFH(k) = c (100 / P_k) folded with 1 / w_k (P_k >= 1: q is in M[k]);
-                // 100 / P_k is loaded beside the coordinates (the weight of an unused lane is dropped)
-                w = (1.0 / sqrt(d2_exact(qx, qy, qz, kx, ky, kz))) * inv100[k];
+            uint4 piece = {0u, 0u, 0u, 0u};
+            const uint4* src = rows_g + static_cast<int64_t>(max(k, 0)) * R8;
+            if (k >= 0) {
+                piece = src[0];
+                const int nv = static_cast<int>(piece.w & 0xffffu);
+                use = k != q && nv > 0;
+                // the weight of SPFH(k) = c (100 / P_k) folded with 1 / w_k (P_k >= 1: q is in M[k])
+                const int P = nv - 1;
+                const double inv = P > 0 ? 100.0 / static_cast<double>(P) : 0.0;
+                w = (1.0 / sqrt(d2_exact(qx, qy, qz, __uint_as_float(piece.x), __uint_as_float(piece.y),
+                                         __uint_as_float(piece.z)))) * inv;
             }
-            const uint32_t bm = static_cast<uint32_t>(ballot(use) >> sh);
+            const uint32_t bm = static_cast<uint32_t>(ballot(use) >> sh) & group;
             const int nuse = __popc(bm);
             // in order: the used neighbours, then places of weight 0 (what their rows hold is finite)
             const int at = use ? __popc(bm & below) : nuse + __popc(~bm & below);
             __builtin_amdgcn_wave_barrier();
             if (use) {
                 // the lane's whole row in 16-byte pieces, every row of the round in flight at once
-                const uint4* src = reinterpret_cast<const uint4*>(cnt16 + static_cast<int64_t>(k) * R);
                 uint4* dst = s_rows + at * R8;
-                for (int i = 0; i < R8; ++i) dst[i] = src[i];
+                dst[0] = piece;
+                for (int i = 1; i < R8; ++i) dst[i] = src[i];
             }
-            s_w[wv][hf][at] = use ? w : 0.0;
+            if (in) s_w[wv][gr][at] = use ? w : 0.0;
             __builtin_amdgcn_wave_barrier();
-            const int numax = max(nuse, __shfl_xor(nuse, kHalf, kWave));
+            if (base == 0) k1 = first_of(q1, b1, e1);
+            const int numax = most(nuse);
             // the rows summed in ascending neighbour order, bin by bin from LDS
             const uint16_t* r0 = reinterpret_cast<const uint16_t*>(s_rows) + lb0;
             const uint16_t* r1 = reinterpret_cast<const uint16_t*>(s_rows) + lb1;
-            const double* ws = s_w[wv][hf];
-            for (int j = 0; j < numax; j += kBatchNarrow) {  // kBatchNarrow divides the 32 places
+            const double* ws = s_w[wv][gr];
+            for (int j = 0; j < numax; j += kBatchNarrow) {
                 double v0[kBatchNarrow], v1[kBatchNarrow], wj[kBatchNarrow];
 #pragma unroll
                 for (int u = 0; u < kBatchNarrow; ++u) {
@@ -541,18 +599,24 @@ __global__ __launch_bounds__(kBlock) void fpfh_pairs(const float* __restrict__ x
             }
             __builtin_amdgcn_wave_barrier();
         }
-        if (!live) continue;
-        float* out = fpfh + q * D;
-        const int P = Pq[q];
-        const uint16_t* sq = cnt16 + q * R;
-        if (P == 0) {
-            if (hl < D) out[hl] = 0.0f;
-            if (hl + kHalf < D) out[hl + kHalf] = 0.0f;
-            continue;
+        if (q >= 0) {
+            float* out = fpfh + static_cast<int64_t>(q) * D;
+            const int P = static_cast<int>(head.w & 0xffffu) - 1;  // q is in B
+            if (P <= 0) {
+                if (gl < D) out[gl] = 0.0f;
+                if (gl + kG < D) out[gl + kG] = 0.0f;
+            } else {
+                const double inv = 1.0 / static_cast<double>(P);
+                if (gl < D) out[gl] = static_cast<float>(spfh_value(own0, P) + inv * acc0);
+                if (gl + kG < D) out[gl + kG] = static_cast<float>(spfh_value(own1, P) + inv * acc1);
+            }
         }
-        const double inv = 1.0 / static_cast<double>(P);
-        if (hl < D) out[hl] = static_cast<float>(spfh_value(sq[hl], P) + inv * acc0);
-        if (hl + kHalf < D) out[hl + kHalf] = static_cast<float>(spfh_value(sq[hl + kHalf], P) + inv * acc1);
+        if (lmax == 0) k1 = first_of(q1, b1, e1);
+        q = q1;
+        q1 = q2;
+        b = b1;
+        e = e1;
+        k = k1;
     }
 }
 
@@ -603,7 +667,7 @@ __device__ __forceinline__ void fpfh_point(const float* __restrict__ xyz, int64_
                 double v0[kBatchNarrow];
 #pragma unroll
                 for (int u = 0; u < kBatchNarrow; ++u)
-                    v0[u] = static_cast<double>(cnt16[static_cast<int64_t>(s_k[j + u]) * R + lb0]);
+                    v0[u] = static_cast<double>(cnt16[static_cast<int64_t>(s_k[j + u]) * R + kSpfhHead + lb0]);
 #pragma unroll
                 for (int u = 0; u < kBatchNarrow; ++u) acc0 = acc0 + s_w[j + u] * v0[u];
             }
@@ -612,7 +676,7 @@ __device__ __forceinline__ void fpfh_point(const float* __restrict__ xyz, int64_
             double v0[kBatch], v1[kBatch];
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
-                const uint16_t* sk = cnt16 + static_cast<int64_t>(s_k[j + u]) * R;
+                const uint16_t* sk = cnt16 + static_cast<int64_t>(s_k[j + u]) * R + kSpfhHead;
                 v0[u] = static_cast<double>(sk[lb0]);
                 v1[u] = D > kWave ? static_cast<double>(sk[lb1]) : 0.0;
             }
@@ -625,13 +689,13 @@ __device__ __forceinline__ void fpfh_point(const float* __restrict__ xyz, int64_
         }
         for (; j < nuse; ++j) {
             const double wj = s_w[j];
-            const uint16_t* sk = cnt16 + static_cast<int64_t>(s_k[j]) * R;
+            const uint16_t* sk = cnt16 + static_cast<int64_t>(s_k[j]) * R + kSpfhHead;
             acc0 = acc0 + wj * static_cast<double>(sk[lb0]);
             if (D > kWave) acc1 = acc1 + wj * static_cast<double>(sk[lb1]);
         }
     }
     const int P = Pq[q];
-    const uint16_t* sq = cnt16 + q * R;
+    const uint16_t* sq = cnt16 + q * R + kSpfhHead;
     if (P == 0) {
         if (lane < D) out[lane] = 0.0f;
         if (lane + kWave < D) out[lane + kWave] = 0.0f;
@@ -776,15 +840,22 @@ kmg_status fpfh_as(const float* xyz, int64_t stride, int64_t m_cap, const uint8_
                    const int32_t* j_idx, const int32_t* off, NbrLists nb, int H, const uint16_t* cnt16,
                    const int32_t* Pq, const double* inv100, float* fpfh_out, const DevStatus* st, hipStream_t s) {
     if (kPairs) {
-        // dynamic LDS: one SPFH row per lane of the block
-        const size_t rows_lds = static_cast<size_t>(kBlock) * spfh_row(H) * sizeof(uint16_t);
-        // one round of blocks: each runs as long as the launch, and a few left for a second round
-        // run alone (7 of 8 blocks per CU at once for rows of 33: 64 pairs 3.6 -> 3.0 ms)
-        const size_t used = rows_lds + sizeof(double) * kBlock;
-        const unsigned per_cu = static_cast<unsigned>(std::min<size_t>(std::max<size_t>(kLdsBytes / used, 1), 8));
-        const unsigned grid = std::min(grid_for((m_cap + 1) / 2, kWaves), per_cu * kCUs);
-        fpfh_pairs<kRows><<<grid, kBlock, rows_lds, s>>>(xyz, stride, m_cap, flags, jflag, j_idx, off, nb, H, cnt16, Pq,
-                                                         inv100, fpfh_out, (tuning().xcd_split >> 1) & 1, st);
+        const int xcd = (tuning().xcd_split >> 1) & 1;
+        const auto launch = [&](auto g) {
+            constexpr int kG = decltype(g)::value, kPts = kWave / kG;
+            const size_t rows = static_cast<size_t>(fpfh_lds_rows(kRows, kG)) * spfh_row(H) * sizeof(uint16_t);
+            const size_t used = rows + sizeof(double) * kWaves * kPts * fpfh_places(kRows, kG);
+            // one round of blocks: each runs as long as the launch, and a few left for a second round
+            // run alone (7 of 8 blocks per CU at once for rows of 33: 64 pairs 3.6 -> 3.0 ms); kRows of
+            // 4 and more also take more registers
+            const size_t per_cu = std::min<size_t>(std::max<size_t>(kLdsBytes / used, 1),
+                                                   kRows <= 2 ? 7 : (kRows == 4 ? 5 : (kRows == 8 ? 4 : 2)));
+            const unsigned grid = std::min(grid_for((m_cap + kPts - 1) / kPts, kWaves),
+                                           static_cast<unsigned>(per_cu) * kCUs);
+            fpfh_pairs<kRows, kG><<<grid, kBlock, rows, s>>>(m_cap, jflag, j_idx, off, nb, H, cnt16, fpfh_out, xcd, st);
+        };
+        if (3 * H <= 42) launch(std::integral_constant<int, 21>{});
+        else launch(std::integral_constant<int, 32>{});
     } else {
         fpfh_kernel<kRows><<<grid_cap(m_cap, kWaves), kBlock, 0, s>>>(xyz, stride, m_cap, flags, jflag, j_idx, off,
                                                                      nb, H, cnt16, Pq, inv100, fpfh_out,
