@@ -55,32 +55,55 @@ __device__ __forceinline__ V3f crossf(V3f a, V3f b) {
 }
 __device__ __forceinline__ V3f scalef(V3f a, float s) { return {a.x * s, a.y * s, a.z * s}; }
 
-// FP32 features and bins for a given role assignment (qa: a = q, b = k).
-// Returns false when a decision is too close to call in FP32: a short frame
-// axis (||d x u|| < 0.2), a near-degenerate f1 argument (|(w.n_b, u.n_b)| <
-// 0.2), or a scaled feature within 2e-4 of an integer.  The FP32 error of the
-// scaled features is below 2e-5 outside those cases.
-__device__ __forceinline__ bool bins_f32_roles(V3f d0, float dl, V3f nq, V3f nk, bool qa, int H, int bins[3]) {
+// atan2 for the screen below: atan(t) / t on [0, 1] as a polynomial in t^2 fitted
+// for the least largest error (Lawson's reweighted least squares), t by the
+// hardware reciprocal; within 7e-7 of atan2 for any finite arguments that are
+// not both tiny.
+__device__ __forceinline__ float atan2_screen(float y, float x) {
+    const float ax = fabsf(x), ay = fabsf(y);
+    const float t = fminf(ax, ay) * __builtin_amdgcn_rcpf(fmaxf(ax, ay));
+    const float z = t * t;
+    float p = 0.006811775732785463f;
+    p = fmaf(p, z, -0.03360416740179062f);
+    p = fmaf(p, z, 0.07962360978126526f);
+    p = fmaf(p, z, -0.13233338296413422f);
+    p = fmaf(p, z, 0.19807814061641693f);
+    p = fmaf(p, z, -0.3331736922264099f);
+    p = fmaf(p, z, 0.9999961256980896f) * t;
+    p = ay > ax ? 1.57079632679489661923f - p : p;
+    p = x < 0.0f ? 3.14159265358979323846f - p : p;
+    return copysignf(p, y);
+}
+
+// FP32 features and bins for a given role assignment (qa: a = q, b = k), rdl =
+// 1 / ||d0||.  Returns false when a decision is too close to call in FP32: a
+// short frame axis (||d x u|| < 0.2), a near-degenerate f1 argument (|(w.n_b,
+// u.n_b)| < 0.2), or a scaled feature within 2e-4 of an integer; and for what
+// is not a number.  The FP32 error of the scaled features is below 3e-5 outside
+// those cases (hardware reciprocal roots, 1e-7 relative; f1 2e-6 + 7e-7 times
+// H / 2 pi).
+__device__ __forceinline__ bool bins_f32_roles(V3f d0, float rdl, V3f nq, V3f nk, bool qa, int H, int bins[3]) {
     const V3f u = qa ? nq : nk;
     const V3f nb = qa ? nk : nq;
-    const V3f d = scalef(d0, (qa ? 1.0f : -1.0f) / dl);
+    const V3f d = scalef(d0, qa ? rdl : -rdl);
     V3f v = crossf(d, u);
-    const float vl = sqrtf(dotf(v, v));
-    if (vl < 0.2f) return false;
-    v = scalef(v, 1.0f / vl);
+    const float v2 = dotf(v, v);
+    if (!(v2 >= 0.04f)) return false;
+    v = scalef(v, __builtin_amdgcn_rsqf(v2));
     const V3f w = crossf(u, v);
     const float y = dotf(w, nb), x = dotf(u, nb);
-    if (x * x + y * y < 0.04f) return false;
-    const float f[3] = {atan2f(y, x), dotf(v, nb), dotf(u, d)};
+    if (!(x * x + y * y >= 0.04f)) return false;
+    const float f[3] = {atan2_screen(y, x), dotf(v, nb), dotf(u, d)};
     const float lo[3] = {-3.14159265358979323846f, -1.0f, -1.0f};
-    const float sc[3] = {H / 6.28318530717958647692f, 0.5f * H, 0.5f * H};
+    const float sc[3] = {H * 0.15915494309189533577f, 0.5f * H, 0.5f * H};
+    bool sure = true;
 #pragma unroll
     for (int l = 0; l < 3; ++l) {
         const float s = (f[l] - lo[l]) * sc[l];
-        if (fabsf(s - rintf(s)) < 2e-4f) return false;
+        sure = sure && fabsf(s - rintf(s)) >= 2e-4f;
         bins[l] = min(max(static_cast<int>(floorf(s)), 0), H - 1);
     }
-    return true;
+    return sure;
 }
 
 // FP32 features and bins.  The a/b roles follow the unsigned angle; when
@@ -88,17 +111,22 @@ __device__ __forceinline__ bool bins_f32_roles(V3f d0, float dl, V3f nq, V3f nk,
 // neighbours with nearly equal normals, the common case on planes) both role
 // assignments are evaluated, and if both are reliable and give the same bins,
 // the bins are those of either FP64 decision.  Returns false when the FP64
-// path has to decide.
+// path has to decide.  The first evaluation is the same code for lanes with
+// one role and with two: apart, a wavefront with both kinds ran three.
 __device__ __forceinline__ bool bins_f32(V3f pq, V3f nq, V3f pk, V3f nk, int H, int bins[3]) {
     const V3f d0 = sub(pk, pq);
     const float aq = fabsf(dotf(nq, d0));
     const float ak = fabsf(dotf(nk, d0));
-    const float dl = sqrtf(dotf(d0, d0));
-    if (fabsf(aq - ak) > 1e-5f * dl) return bins_f32_roles(d0, dl, nq, nk, aq >= ak, H, bins);
-    int other[3];
-    if (!bins_f32_roles(d0, dl, nq, nk, true, H, bins)) return false;
-    if (!bins_f32_roles(d0, dl, nq, nk, false, H, other)) return false;
-    return bins[0] == other[0] && bins[1] == other[1] && bins[2] == other[2];
+    const float d2 = dotf(d0, d0);
+    const float rdl = __builtin_amdgcn_rsqf(d2);
+    const bool tie = !(fabsf(aq - ak) > 1e-5f * (d2 * rdl));
+    bool sure = bins_f32_roles(d0, rdl, nq, nk, tie || aq >= ak, H, bins);
+    if (tie && sure) {
+        int other[3];
+        sure = bins_f32_roles(d0, rdl, nq, nk, false, H, other) && bins[0] == other[0] && bins[1] == other[1] &&
+               bins[2] == other[2];
+    }
+    return sure;
 }
 
 __device__ __forceinline__ double dotd(const double a[3], const double b[3]) {
