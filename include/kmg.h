@@ -148,9 +148,8 @@ const char* kmg_stage_name(int32_t stage);
  *   count_queries   queries per wavefront in the count pass (the per-stage
  *                   calls, and batches under search_form 0): 1, 2 (default)
  *                   or 4.
- *   spfh_pair_mean  mean neighbour-list length up to which the SPFH pass
- *                   (Eq. A2-A4) takes two points per wavefront (default 24;
- *                   0 = never, 8192 = always).
+ *   spfh_pair_mean  0 .. 8192 (default 24); without effect: the SPFH pass
+ *                   (Eq. A2-A4) takes two points per wavefront throughout.
  *   fpfh_rows       SPFH rows per unrolled step of the FPFH sum (Eq. A5):
  *                   rows read from LDS per step where two J points share a
  *                   wavefront (3H <= 64), rows in flight per lane otherwise;

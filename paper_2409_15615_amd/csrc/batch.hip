@@ -181,18 +181,17 @@ kmg_status batch_run(int n_pairs, int64_t raw_cap, int64_t nnz_cap, int H, int p
     if (list_first) {
         KMG_TRY(search_lists_first(w.cl, w.kept_xyz, raw_cap, w.kept_cloud, raw_cap, nnz_cap, w.st, w.srch, w.off,
                                    w.nbr, w.pad, w.pad_cap, w.long_q, w.nrm, raw_cap, w.flags, s, true,
-                                   w.scan_status + w.n_vox_status));
+                                   w.scan_status + w.n_vox_status, w.feat.rec));
     } else {
         KMG_TRY(search_count_batch(w.cl, w.kept_xyz, raw_cap, w.kept_cloud, raw_cap, w.st, w.srch, w.off, s, true,
                                    0, true, true));
         KMG_TRY(search_fill_batch(w.cl, w.kept_xyz, raw_cap, w.kept_cloud, raw_cap, nnz_cap, kFillAll, w.st, w.srch,
-                                  w.off, w.nbr, w.nrm, raw_cap, w.flags, nullptr, s));
+                                  w.off, w.nbr, w.nrm, raw_cap, w.flags, nullptr, s, 0, w.feat.rec));
     }
     // the list-first search leaves the lists in the pad rows (the longer ones in nbr);
     // the J list emission also writes the clouds' J ranges and matching sets
     const NbrLists nb = list_first ? NbrLists{w.nbr, w.pad, w.pad_cap} : NbrLists{w.nbr};
-    KMG_TRY(features_batch(w.cl, C, w.kept_xyz, raw_cap, w.kept_cloud, raw_cap, H, w.st, w.feat, w.off, nb,
-                           w.nrm, raw_cap, w.flags, nullptr, w.fpfh, w.jlist, w.cs, s, true, w.sets,
+    KMG_TRY(features_batch(w.cl, C, w.kept_xyz, raw_cap, w.kept_cloud, raw_cap, H, w.st, w.feat, w.off, nb, w.flags, nullptr, w.fpfh, w.jlist, w.cs, s, true, w.sets,
                            w.scan_status + w.n_vox_status + w.n_search_status));
     // the pair counts and statuses come with the correspondences
     KMG_TRY(match_batch(w.sets, C, D, w.st, w.match, w.outs, counts, kCountsStride, s, w.cs, nnz_cap));

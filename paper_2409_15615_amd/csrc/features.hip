@@ -4,19 +4,19 @@
 // All clouds of a batch are processed by the same launches (grid-stride over
 // the kept points; each point reads its cloud's tau_num).
 //
-// SPFH: one wavefront per point q; lanes take the neighbours k of q, 64 at a
+// SPFH: half a wavefront per point q; lanes take the neighbours k of q, 32 at a
 // time.  Each lane computes the three features of (q, k) in FP32 and bins
 // them; a feature set that lies within a guard band of a bin edge or of an
 // ill-conditioned frame, or near the a/b selection tie with the two role
 // assignments binning differently, is recomputed in FP64 with the operation
 // order of the plain definition, so the bins equal the FP64 definition's.
-// Bin counts are formed with one ballot + popcount per (feature, bin): no
-// atomics, deterministic.  The FPFH pass keeps the counts (uint16, 66 bytes
-// per row of 33) and 100 / P_q per point, not the FP64 SPFH values: the
-// gather of a neighbour's row moves a quarter of the bytes.
+// Bin counts are integer atomics in LDS: deterministic.  The FPFH pass keeps the
+// counts (uint16, after the point's coordinates and neighbour count in a row of
+// 80 bytes for 33 bins), not the FP64 SPFH values: the gather of a neighbour
+// moves a third of the bytes.
 //
-// FPFH: one wavefront per point q in J; lanes first compute the weights
-// (1 / ||a_k - a_q||) (100 / P_k) of a chunk of neighbours (FP64) and compact
+// FPFH: a group of lanes per point q in J; lanes first compute the weights
+// (1 / ||a_k - a_q||) (100 / P_k) of a round of neighbours (FP64) and compact
 // them into LDS, then each lane owns descriptor bins and accumulates weight x
 // count over the chunk in ascending k, in FP64 (the term (1 / w_k) SPFH(k) of
 // Eq. A5); the query's own SPFH value is 100 c / P_q, divided exactly.
@@ -37,12 +37,9 @@ constexpr int kBlock = 256;
 constexpr int64_t kItemWork = 32;
 constexpr int kWaves = kBlock / kWave;
 constexpr int kBatch = 8;          // SPFH rows loaded together in the FPFH sum
-// Long lists differ in length: many small shares, which the dispatcher evens
-// out (a cloud of 215,000 points, mean 54: 244 -> 212 us against 2,048 blocks).
-// Short lists in pairs: one resident round (64 pairs, 3.6 million points: 2.47
-// -> 2.35 ms).
-constexpr unsigned kSpfhBlocks = 8192;
-constexpr unsigned kSpfhPairBlocks = 4 * kCUs;
+// One resident round of blocks for the SPFH pass (64 pairs, 3.6 million points:
+// 2.47 -> 2.35 ms against 2,048 blocks, two rounds).
+constexpr unsigned kSpfhBlocks = 4 * kCUs;
 
 struct V3f {
     float x, y, z;
@@ -213,33 +210,63 @@ __device__ __forceinline__ int cloud_of(const int32_t* kept_cloud, int64_t q) {
 __device__ __forceinline__ uint16_t* spfh_counts(uint16_t* cnt16, int64_t q, int H) {
     return cnt16 + q * spfh_row(H) + kSpfhHead;
 }
-__device__ __forceinline__ void spfh_head(uint16_t* cnt16, int64_t q, int H, const float* xyz, int64_t stride,
-                                          int n_valid) {
+__device__ __forceinline__ void spfh_head(uint16_t* cnt16, int64_t q, int H, const float4& a, int n_valid) {
     uint16_t* row = cnt16 + q * spfh_row(H);
     float* p = reinterpret_cast<float*>(row);
-    p[0] = xyz[q];
-    p[1] = xyz[stride + q];
-    p[2] = xyz[2 * stride + q];
+    p[0] = a.x;
+    p[1] = a.y;
+    p[2] = a.z;
     row[kSpfhHead - 1] = static_cast<uint16_t>(n_valid);
 }
 
-// Lists of a mean of at most kHalfListMean entries per point: two points per
-// wavefront, one per half of 32 lanes (each lane one neighbour of its half's
-// point per round, adding its three bins to the half's LDS histogram with
-// integer atomics; lane h of a half then reads bin h).  Longer lists:
-// spfh_kernel, one point per wavefront.  Each kernel checks the mean and
-// returns at once when the other one serves it
-// (one kernel holding both bodies was measured slower: its one-wave body runs
-// slower than alone, 64.7 -> 70.5 us for the pass on the LiDAR pair, more than
-// the launch it saves).  The threshold is measured: the 64-pair batch (mean
-// 22.5) runs 1.5x faster in pairs, the LiDAR pair (mean 29, but a long tail of
-// structure points next to scattered outliers with a few neighbours) 8% slower.
-constexpr int kHalfListMean = 24;  // the default of tuning().spfh_pair_mean
+// The FP64 recomputations, once per wavefront.
+__device__ __forceinline__ void count_fp64(DevStatus* st, uint32_t n64, uint32_t nedge) {
+    n64 = wave_sum(n64);
+    nedge = wave_sum(nedge);
+    if (lane_id() == 0) {
+        if (n64) atomicAdd(&st->feat_fp64, n64);
+        if (nedge) atomicAdd(&st->feat_edge, nedge);
+    }
+}
 
-__device__ __forceinline__ void spfh_pairs_body(const CloudDev* __restrict__ cl, const float* __restrict__ xyz,
-                                           int64_t stride, const int32_t* __restrict__ kept_cloud, int64_t m,
-                                           const float* __restrict__ nrm, int64_t nrm_stride,
-                                           const uint8_t* __restrict__ flags, const int32_t* __restrict__ off,
+// A point's record (coordinates, flag B; normal: one 32-byte piece, where the
+// arrays were seven lines), and what its SPFH starts with, so that it can be
+// loaded while the point before is worked on.  q < 0: no point.
+__device__ __forceinline__ bool rec_flag(const float4& a) { return (__float_as_int(a.w) & 1) != 0; }
+struct PointLoad {
+    float4 a, n;
+    int64_t q;
+    int b, e;
+};
+__device__ __forceinline__ PointLoad load_point(const float4* rec, const int32_t* off, int64_t q, int64_t m) {
+    PointLoad p;
+    p.a = p.n = make_float4(0.f, 0.f, 0.f, 0.f);
+    p.b = p.e = 0;
+    p.q = q < m ? q : -1;
+    if (q < m) {
+        p.a = rec[2 * q];
+        p.n = rec[2 * q + 1];
+        p.b = off[q];
+        p.e = off[q + 1];
+    }
+    return p;
+}
+__device__ __forceinline__ int first_neighbour(const NbrLists& nb, int prow, const PointLoad& p, int at) {
+    return at < p.e - p.b ? list_of(nb, prow, p.q, p.b, p.e)[at] : -1;
+}
+
+// SPFH of two points per wavefront, one per half of 32 lanes: each lane one
+// neighbour of its half's point per round, adding its three bins to the half's
+// LDS histogram with integer atomics; lane h of a half then reads bin h.
+// Bound by the chain of loads per point and the features' arithmetic.  A
+// neighbour is one record, and the next points' records, list bounds and first
+// neighbours are loaded while these are worked on: 64 pairs (3.6 million points,
+// mean list 22) 2.27 -> 1.79 ms.  One point per wavefront leaves lanes idle at the
+// end of each list and was slower for long lists too: a cloud of 215,000 points,
+// mean 54, 182 us against 156; a scan pair, mean 28, 61 against 49.
+__device__ __forceinline__ void spfh_pairs_body(const CloudDev* __restrict__ cl,
+                                           const int32_t* __restrict__ kept_cloud, int64_t m,
+                                           const float4* __restrict__ rec, const int32_t* __restrict__ off,
                                            NbrLists nb, int H, uint16_t* __restrict__ cnt16,
                                            float* __restrict__ spfh_out, int32_t* __restrict__ Pq,
                                            double* __restrict__ inv100, int32_t* __restrict__ jflag, int xcd,
@@ -248,26 +275,22 @@ __device__ __forceinline__ void spfh_pairs_body(const CloudDev* __restrict__ cl,
     const int lane = lane_id();
     const int hf = lane / kHalf, hl = lane % kHalf, sh = kHalf * hf;
     const int D = 3 * H;
-    const int64_t s2 = 2 * stride, n2 = 2 * nrm_stride;
     uint32_t n64 = 0, nedge = 0;
     const int prow = nb.pad ? pad_stride(nb.pad_cap, m) : 0;
     const XcdItems it = xcd ? xcd_items((m + 1) / 2, off[m] + kItemWork * m,
                                         [&](int64_t i) { return off[2 * i] + kItemWork * 2 * i; })
                             : cyclic_items((m + 1) / 2);
+    PointLoad p = load_point(rec, off, 2 * it.first + hf, it.first < it.end ? m : 0);
+    int k = first_neighbour(nb, prow, p, hl);
     for (int64_t pw = it.first; pw < it.end; pw += it.stride) {
-        const int64_t q = 2 * pw + hf;
-        const bool live = q < m;
-        const bool has_b = live && (flags[q] & 1);
-        V3f pq = {0.f, 0.f, 0.f}, nq = {0.f, 0.f, 0.f};
-        int b = 0, e = 0;
-        if (has_b) {
-            pq = {xyz[q], xyz[stride + q], xyz[s2 + q]};
-            nq = {nrm[q], nrm[nrm_stride + q], nrm[n2 + q]};
-            b = off[q];
-            e = off[q + 1];
-        }
-        const int len = e - b;
-        const int32_t* lp = list_of(nb, prow, q, b, e);
+        const PointLoad p1 = load_point(rec, off, 2 * (pw + it.stride) + hf, pw + it.stride < it.end ? m : 0);
+        int k1 = -1;
+        const int64_t q = p.q;
+        const bool live = q >= 0;
+        const bool has_b = live && rec_flag(p.a);
+        const V3f pq = {p.a.x, p.a.y, p.a.z}, nq = {p.n.x, p.n.y, p.n.z};
+        const int len = has_b ? p.e - p.b : 0;
+        const int32_t* lp = list_of(nb, prow, q, p.b, p.e);
         const int lmax = max(len, __shfl_xor(len, kHalf, kWave));
         int n_valid = 0;
         // the half's histogram in LDS (3H counters), one atomic per lane and feature
@@ -275,14 +298,19 @@ __device__ __forceinline__ void spfh_pairs_body(const CloudDev* __restrict__ cl,
         for (int t = hl; t < D; t += kHalf) hist[t] = 0u;
         __builtin_amdgcn_wave_barrier();
         for (int base = 0; base < lmax; base += kHalf) {
+            if (base > 0) k = base + hl < len ? lp[base + hl] : -1;
             bool valid = false;
             int bn[3] = {-1, -1, -1};
-            if (base + hl < len) {
-                const int k = lp[base + hl];
-                valid = (flags[k] & 1) != 0;
+            float4 ka = {0.f, 0.f, 0.f, 0.f}, kn = ka;
+            if (k >= 0 && has_b) {
+                ka = rec[2 * static_cast<int64_t>(k)];
+                kn = rec[2 * static_cast<int64_t>(k) + 1];
+            }
+            if (base == 0) k1 = first_neighbour(nb, prow, p1, hl);
+            if (k >= 0 && has_b) {
+                valid = rec_flag(ka);
                 if (valid && k != q) {
-                    const V3f pk = {xyz[k], xyz[stride + k], xyz[s2 + k]};
-                    const V3f nk = {nrm[k], nrm[nrm_stride + k], nrm[n2 + k]};
+                    const V3f pk = {ka.x, ka.y, ka.z}, nk = {kn.x, kn.y, kn.z};
                     if (!bins_f32(pq, nq, pk, nk, H, bn)) {
                         const BinsF64 r = bins_f64(pq, nq, pk, nk, H);
                         bn[0] = r.b[0];
@@ -309,9 +337,13 @@ __device__ __forceinline__ void spfh_pairs_body(const CloudDev* __restrict__ cl,
             c2 = static_cast<int>(hist[2 * H + hl]);
         }
         __builtin_amdgcn_wave_barrier();  // the histogram is free for the next pair of points
+        if (lmax == 0) k1 = first_neighbour(nb, prow, p1, hl);
+        const float4 pa = p.a;
+        p = p1;
+        k = k1;
         if (!live) continue;
         uint16_t* row = spfh_counts(cnt16, q, H);
-        if (hl == 0) spfh_head(cnt16, q, H, xyz, stride, has_b ? n_valid : 0);
+        if (hl == 0) spfh_head(cnt16, q, H, pa, has_b ? n_valid : 0);
         if (!has_b) {
             for (int t = hl; t < D; t += kHalf) {
                 row[t] = 0;
@@ -338,30 +370,26 @@ __device__ __forceinline__ void spfh_pairs_body(const CloudDev* __restrict__ cl,
             jflag[q] = (n_valid >= cl[cloud_of(kept_cloud, q)].tau_j) ? 1 : 0;
         }
     }
-    // the FP64 recomputation counts, once per wave
-    n64 = wave_sum(n64);
-    nedge = wave_sum(nedge);
-    if (lane == 0) {
-        if (n64) atomicAdd(&st->feat_fp64, n64);
-        if (nedge) atomicAdd(&st->feat_edge, nedge);
-    }
+    count_fp64(st, n64, nedge);
 }
 
-// SPFH of point q (Eq. A2-A4) by one wavefront: the body of spfh_kernel.
-__device__ __forceinline__ void spfh_point(const CloudDev* __restrict__ cl, const float* __restrict__ xyz,
-                                           int64_t stride, const int32_t* __restrict__ kept_cloud,
-                                           const float* __restrict__ nrm, int64_t nrm_stride,
-                                           const uint8_t* __restrict__ flags, const int32_t* __restrict__ off,
-                                           NbrLists nb, int H, uint16_t* __restrict__ cnt16,
-                                           float* __restrict__ spfh_out, int32_t* __restrict__ Pq,
-                                           double* __restrict__ inv100, int32_t* __restrict__ jflag, DevStatus* st,
-                                           int64_t q, uint32_t* s_hist, int prow) {
+// SPFH of point p (Eq. A2-A4) by one wavefront (the fused launch).  k: the
+// lane's neighbour of the first round (-1: none); next() is called once that
+// round's records are on their way.  n64, nedge: the lane's FP64 recomputations.
+template <class F>
+__device__ __forceinline__ void spfh_point(const CloudDev* __restrict__ cl, const int32_t* __restrict__ kept_cloud,
+                                           const float4* __restrict__ rec, NbrLists nb, int H,
+                                           uint16_t* __restrict__ cnt16, float* __restrict__ spfh_out,
+                                           int32_t* __restrict__ Pq, double* __restrict__ inv100,
+                                           int32_t* __restrict__ jflag, const PointLoad& p, int k,
+                                           uint32_t* s_hist, int prow, uint32_t& n64, uint32_t& nedge, F next) {
     const int lane = lane_id();
     const int D = 3 * H;
-    const int64_t s2 = 2 * stride, n2 = 2 * nrm_stride;
+    const int64_t q = p.q;
     uint16_t* row = spfh_counts(cnt16, q, H);
-    if (!(flags[q] & 1)) {
-        if (lane == 0) spfh_head(cnt16, q, H, xyz, stride, 0);
+    if (!rec_flag(p.a)) {
+        next();
+        if (lane == 0) spfh_head(cnt16, q, H, p.a, 0);
         for (int t = lane; t < D; t += kWave) {
             row[t] = 0;
             if (spfh_out) spfh_out[q * D + t] = 0.0f;
@@ -373,25 +401,27 @@ __device__ __forceinline__ void spfh_point(const CloudDev* __restrict__ cl, cons
         }
         return;
     }
-    const V3f pq = {xyz[q], xyz[stride + q], xyz[s2 + q]};
-    const V3f nq = {nrm[q], nrm[nrm_stride + q], nrm[n2 + q]};
-    const int b = off[q], e = off[q + 1];
-    const int32_t* lp = list_of(nb, prow, q, b, e);
+    const V3f pq = {p.a.x, p.a.y, p.a.z}, nq = {p.n.x, p.n.y, p.n.z};
+    const int len = p.e - p.b;
+    const int32_t* lp = list_of(nb, prow, q, p.b, p.e);
     // the wavefront's histogram in LDS (3H counters), one atomic per lane and feature
     for (int t = lane; t < D; t += kWave) s_hist[t] = 0u;
     __builtin_amdgcn_wave_barrier();
     int n_valid = 0;
-    uint32_t n64 = 0, nedge = 0;
-    for (int base = b; base < e; base += kWave) {
-        const int t = base + lane;
+    for (int base = 0; base == 0 || base < len; base += kWave) {
+        if (base > 0) k = base + lane < len ? lp[base + lane] : -1;
         bool valid = false;
         int bn[3] = {-1, -1, -1};
-        if (t < e) {
-            const int k = lp[t - b];
-            valid = (flags[k] & 1) != 0;
+        float4 ka = {0.f, 0.f, 0.f, 0.f}, kn = ka;
+        if (k >= 0) {
+            ka = rec[2 * static_cast<int64_t>(k)];
+            kn = rec[2 * static_cast<int64_t>(k) + 1];
+        }
+        if (base == 0) next();
+        if (k >= 0) {
+            valid = rec_flag(ka);
             if (valid && k != q) {
-                const V3f pk = {xyz[k], xyz[stride + k], xyz[s2 + k]};
-                const V3f nk = {nrm[k], nrm[nrm_stride + k], nrm[n2 + k]};
+                const V3f pk = {ka.x, ka.y, ka.z}, nk = {kn.x, kn.y, kn.z};
                 if (!bins_f32(pq, nq, pk, nk, H, bn)) {
                     const BinsF64 r = bins_f64(pq, nq, pk, nk, H);
                     bn[0] = r.b[0];
@@ -418,8 +448,6 @@ __device__ __forceinline__ void spfh_point(const CloudDev* __restrict__ cl, cons
         c2 = static_cast<int>(s_hist[2 * H + lane]);
     }
     __builtin_amdgcn_wave_barrier();  // the histogram is free for the wavefront's next point
-    n64 = wave_sum(n64);
-    nedge = wave_sum(nedge);
     const int P = n_valid - 1;
     if (lane < H) {
         const int cs[3] = {c0, c1, c2};
@@ -429,58 +457,27 @@ __device__ __forceinline__ void spfh_point(const CloudDev* __restrict__ cl, cons
         }
     }
     if (lane == 0) {
-        spfh_head(cnt16, q, H, xyz, stride, n_valid);
+        spfh_head(cnt16, q, H, p.a, n_valid);
         Pq[q] = P;
         inv100[q] = P > 0 ? 100.0 / static_cast<double>(P) : 0.0;
         jflag[q] = (n_valid >= cl[cloud_of(kept_cloud, q)].tau_j) ? 1 : 0;
-        if (n64) atomicAdd(&st->feat_fp64, n64);
-        if (nedge) atomicAdd(&st->feat_edge, nedge);
     }
 }
 
-__global__ __launch_bounds__(kBlock) void spfh_pairs(const CloudDev* __restrict__ cl, const float* __restrict__ xyz,
-                                                     int64_t stride, const int32_t* __restrict__ kept_cloud,
-                                                     int64_t m_cap, const float* __restrict__ nrm,
-                                                     int64_t nrm_stride, const uint8_t* __restrict__ flags,
+__global__ __launch_bounds__(kBlock) void spfh_pairs(const CloudDev* __restrict__ cl,
+                                                     const int32_t* __restrict__ kept_cloud,
+                                                     int64_t m_cap, const float4* __restrict__ rec,
                                                      const int32_t* __restrict__ off,
                                                      NbrLists nb, int H,
                                                      uint16_t* __restrict__ cnt16, float* __restrict__ spfh_out,
                                                      int32_t* __restrict__ Pq, double* __restrict__ inv100,
-                                                     int32_t* __restrict__ jflag, int pair_mean, int xcd,
+                                                     int32_t* __restrict__ jflag, int xcd,
                                                      DevStatus* st) {
     const int64_t m = clamp_count(st->m_kept, m_cap);
     if (st->err_range || st->err_capacity) return;  // the neighbour lists are incomplete
-    // long lists: spfh_kernel (0 = always spfh_kernel, kMaxDegree = always this pass)
-    if (pair_mean < kMaxDegree && (pair_mean == 0 || st->nnz > pair_mean * m)) return;
     __shared__ uint32_t s_hist[kWaves][2 * 3 * kMaxBins];
-    spfh_pairs_body(cl, xyz, stride, kept_cloud, m, nrm, nrm_stride, flags, off, nb, H, cnt16, spfh_out, Pq, inv100,
-                    jflag, xcd, st, s_hist[threadIdx.x / kWave]);
-}
-
-// SPFH (Eq. A2-A4) of every kept point when the mean list length exceeds
-// pair_mean, one point per wavefront; xcd selects the XCD-aware split of the
-// points over the wavefronts.
-__global__ __launch_bounds__(kBlock) void spfh_kernel(const CloudDev* __restrict__ cl, const float* __restrict__ xyz,
-                                                      int64_t stride, const int32_t* __restrict__ kept_cloud,
-                                                      int64_t m_cap, const float* __restrict__ nrm,
-                                                      int64_t nrm_stride, const uint8_t* __restrict__ flags,
-                                                      const int32_t* __restrict__ off,
-                                                      NbrLists nb, int H,
-                                                      uint16_t* __restrict__ cnt16, float* __restrict__ spfh_out,
-                                                      int32_t* __restrict__ Pq, double* __restrict__ inv100,
-                                                      int32_t* __restrict__ jflag, int pair_mean, int xcd,
-                                                      DevStatus* st) {
-    const int64_t m = clamp_count(st->m_kept, m_cap);
-    if (st->err_range || st->err_capacity) return;  // the neighbour lists are incomplete
-    // short lists: spfh_pairs (0 = always this pass, kMaxDegree = always spfh_pairs)
-    if (pair_mean >= kMaxDegree || (pair_mean > 0 && st->nnz <= pair_mean * m)) return;
-    const XcdItems it = xcd ? xcd_items(m, off[m] + kItemWork * m, [&](int64_t i) { return off[i] + kItemWork * i; })
-                            : cyclic_items(m);
-    __shared__ uint32_t s_hist[kWaves][3 * kMaxBins];
-    const int prow = nb.pad ? pad_stride(nb.pad_cap, m) : 0;
-    for (int64_t q = it.first; q < it.end; q += it.stride)
-        spfh_point(cl, xyz, stride, kept_cloud, nrm, nrm_stride, flags, off, nb, H, cnt16, spfh_out, Pq, inv100,
-                   jflag, st, q, s_hist[threadIdx.x / kWave], prow);
+    spfh_pairs_body(cl, kept_cloud, m, rec, off, nb, H, cnt16, spfh_out, Pq, inv100, jflag, xcd, st,
+                    s_hist[threadIdx.x / kWave]);
 }
 
 // Places of a group's round, whole steps of the sum; rows of the block that the
@@ -775,7 +772,7 @@ __global__ __launch_bounds__(kBlock) void fpfh_kernel(const float* __restrict__ 
 // cloud's counter to reach the cloud's kept count and then acquires.  Items
 // are handed out in order, so a waiting wavefront only ever waits for SPFH
 // items that running wavefronts hold.  Non-J rows of the FPFH are zeroed by
-// their FPFH items.  The same per-point bodies as spfh_kernel and fpfh_kernel:
+// their FPFH items.  The sums and their order are those of the separate passes:
 // bit-identical outputs.
 constexpr int kFuseChunk = 16;
 constexpr uint32_t kFuseSpinLimit = 1u << 22;
@@ -787,7 +784,7 @@ __device__ __forceinline__ int64_t cloud_kept(const CloudState* cs, int c, int64
 template <int kBatchNarrow>
 __global__ __launch_bounds__(kBlock) void features_fused(
     const CloudDev* __restrict__ cl, const float* __restrict__ xyz, int64_t stride,
-    const int32_t* __restrict__ kept_cloud, int64_t m_cap, const float* __restrict__ nrm, int64_t nrm_stride,
+    const int32_t* __restrict__ kept_cloud, int64_t m_cap, const float4* __restrict__ rec,
     uint8_t* __restrict__ flags, const int32_t* __restrict__ off, NbrLists nb, int H,
     uint16_t* __restrict__ cnt16, float* __restrict__ spfh_out, int32_t* __restrict__ Pq, double* __restrict__ inv100,
     int32_t* __restrict__ jflag, float* __restrict__ fpfh, const CloudState* __restrict__ cs, uint32_t* queue,
@@ -802,6 +799,7 @@ __global__ __launch_bounds__(kBlock) void features_fused(
     const int D = 3 * H;
     const int prow = nb.pad ? pad_stride(nb.pad_cap, m) : 0;
     const int64_t n_chunks = (m + kFuseChunk - 1) / kFuseChunk;
+    uint32_t n64 = 0, nedge = 0;
     int known = -1;  // a cloud whose SPFH this wavefront has seen complete (and acquired)
     while (true) {
         uint32_t item = 0;
@@ -811,9 +809,11 @@ __global__ __launch_bounds__(kBlock) void features_fused(
         if (item < n_chunks) {
             const int64_t p0 = static_cast<int64_t>(item) * kFuseChunk;
             const int64_t p1 = min(p0 + kFuseChunk, m);
-            for (int64_t q = p0; q < p1; ++q)
-                spfh_point(cl, xyz, stride, kept_cloud, nrm, nrm_stride, flags, off, nb, H, cnt16, spfh_out, Pq,
-                           inv100, jflag, st, q, s_hist[wv], prow);
+            for (int64_t q = p0; q < p1; ++q) {
+                const PointLoad p = load_point(rec, off, q, m);
+                spfh_point(cl, kept_cloud, rec, nb, H, cnt16, spfh_out, Pq, inv100, jflag, p,
+                           first_neighbour(nb, prow, p, lane), s_hist[wv], prow, n64, nedge, [] {});
+            }
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
             if (lane == 0) {
                 // the chunk's points by cloud (a chunk rarely crosses a cloud boundary)
@@ -859,6 +859,7 @@ __global__ __launch_bounds__(kBlock) void features_fused(
             }
         }
     }
+    count_fp64(st, n64, nedge);
 }
 
 // The FPFH launch with kRows SPFH rows in flight per lane (4, 8 or 16; the
@@ -973,6 +974,7 @@ FeatWs carve_feat(Carver& c, int64_t m_cap, int H) {
     const size_t mc = static_cast<size_t>(std::max<int64_t>(m_cap, 1));
     w.cnt16 = c.take<uint16_t>(mc * spfh_row(H));
     w.inv100 = c.take<double>(mc);
+    w.rec = c.take<float4>(2 * mc);
     w.queue = c.take<uint32_t>(1);
     w.ready = c.take<int32_t>(kMaxClouds);
     w.Pq = c.take<int32_t>(mc);
@@ -982,33 +984,18 @@ FeatWs carve_feat(Carver& c, int64_t m_cap, int H) {
     return w;
 }
 
-kmg_status spfh_batch(const CloudDev* cl, const float* xyz, int64_t stride, const int32_t* kept_cloud,
-                      int64_t m_cap, int H, DevStatus* st, const FeatWs& w, const int32_t* off, NbrLists nb,
-                      const float* nrm, int64_t nrm_stride, uint8_t* flags, float* spfh_out, hipStream_t s,
+kmg_status spfh_batch(const CloudDev* cl, const int32_t* kept_cloud, int64_t m_cap, int H, DevStatus* st,
+                      const FeatWs& w, const int32_t* off, NbrLists nb, float* spfh_out, hipStream_t s,
                       bool cleared) {
     if (!cleared)
         KMG_TRY(fill_u32(reinterpret_cast<uint32_t*>(w.jflag), 0u, static_cast<size_t>(std::max<int64_t>(m_cap, 1)),
                          s));
     if (m_cap > 0) {
         StageScope sc(ST_SPFH, s);
-        const int pair_mean = tuning().spfh_pair_mean;
-        // the two forms split on the mean list length on the device; at the ends of
-        // the range (0: one point per wavefront, kMaxDegree: two) the choice is made
-        // here, and only that form is launched
-        if (pair_mean < kMaxDegree) {
-            spfh_kernel<<<std::min(grid_for(m_cap, kWaves), kSpfhBlocks), kBlock, 0, s>>>(cl, xyz, stride, kept_cloud, m_cap, nrm,
-                                                                  nrm_stride, flags, off, nb, H, w.cnt16, spfh_out,
-                                                                  w.Pq, w.inv100, w.jflag, pair_mean,
-                                                                  tuning().xcd_split & 1, st);
-            KMG_TRY(launch_status());
-        }
-        if (pair_mean > 0) {
-            spfh_pairs<<<std::min(grid_for((m_cap + 1) / 2, kWaves), kSpfhPairBlocks), kBlock, 0, s>>>(cl, xyz, stride, kept_cloud, m_cap, nrm,
-                                                                           nrm_stride, flags, off, nb, H, w.cnt16,
-                                                                           spfh_out, w.Pq, w.inv100, w.jflag,
-                                                                           pair_mean, tuning().xcd_split & 1, st);
-            KMG_TRY(launch_status());
-        }
+        spfh_pairs<<<std::min(grid_for((m_cap + 1) / 2, kWaves), kSpfhBlocks), kBlock, 0, s>>>(
+            cl, kept_cloud, m_cap, w.rec, off, nb, H, w.cnt16, spfh_out, w.Pq, w.inv100, w.jflag,
+            tuning().xcd_split & 1, st);
+        KMG_TRY(launch_status());
     }
     return KMG_OK;
 }
@@ -1050,20 +1037,18 @@ kmg_status fpfh_batch(int n_clouds, const float* xyz, int64_t stride, int64_t m_
 // SPFH and FPFH in the fused persistent launch, then the J list.
 template <int kRows>
 void launch_fused(const CloudDev* cl, const float* xyz, int64_t stride, const int32_t* kept_cloud, int64_t m_cap,
-                  const float* nrm, int64_t nrm_stride, uint8_t* flags, const int32_t* off, NbrLists nb, int H,
-                  const FeatWs& w, float* spfh_out, float* fpfh_out, const CloudState* cs, DevStatus* st,
+                  uint8_t* flags, const int32_t* off, NbrLists nb, int H, const FeatWs& w, float* spfh_out, float* fpfh_out, const CloudState* cs, DevStatus* st,
                   hipStream_t s) {
-    features_fused<kRows><<<grid_cap(m_cap, kWaves), kBlock, 0, s>>>(cl, xyz, stride, kept_cloud, m_cap, nrm,
-                                                                      nrm_stride, flags, off, nb, H, w.cnt16, spfh_out,
+    features_fused<kRows><<<grid_cap(m_cap, kWaves), kBlock, 0, s>>>(cl, xyz, stride, kept_cloud, m_cap, w.rec,
+                                                                      flags, off, nb, H, w.cnt16, spfh_out,
                                                                       w.Pq, w.inv100, w.jflag, fpfh_out, cs, w.queue,
                                                                       w.ready, st);
 }
 
 kmg_status features_fused_batch(const CloudDev* cl, int n_clouds, const float* xyz, int64_t stride,
                                 const int32_t* kept_cloud, int64_t m_cap, int H, DevStatus* st, const FeatWs& w,
-                                const int32_t* off, NbrLists nb, const float* nrm, int64_t nrm_stride,
-                                uint8_t* flags, float* spfh_out, float* fpfh_out, int32_t* j_idx, CloudState* cs,
-                                hipStream_t s, bool cleared, MatchSet* sets) {
+                                const int32_t* off, NbrLists nb, uint8_t* flags, float* spfh_out, float* fpfh_out,
+                                int32_t* j_idx, CloudState* cs, hipStream_t s, bool cleared, MatchSet* sets) {
     if (sets && !cs) return KMG_ERR_ARG;
     if (!cleared)
         KMG_TRY(fill_u32(reinterpret_cast<uint32_t*>(w.jflag), 0u, static_cast<size_t>(std::max<int64_t>(m_cap, 1)),
@@ -1073,11 +1058,11 @@ kmg_status features_fused_batch(const CloudDev* cl, int n_clouds, const float* x
     if (m_cap > 0) {
         StageScope sc(ST_SPFH, s);  // SPFH and FPFH together
         switch (tuning().fpfh_rows) {
-            case 4: launch_fused<4>(cl, xyz, stride, kept_cloud, m_cap, nrm, nrm_stride, flags, off, nb, H, w,
+            case 4: launch_fused<4>(cl, xyz, stride, kept_cloud, m_cap, flags, off, nb, H, w,
                                     spfh_out, fpfh_out, cs, st, s); break;
-            case 16: launch_fused<16>(cl, xyz, stride, kept_cloud, m_cap, nrm, nrm_stride, flags, off, nb, H, w,
+            case 16: launch_fused<16>(cl, xyz, stride, kept_cloud, m_cap, flags, off, nb, H, w,
                                       spfh_out, fpfh_out, cs, st, s); break;
-            default: launch_fused<8>(cl, xyz, stride, kept_cloud, m_cap, nrm, nrm_stride, flags, off, nb, H, w,
+            default: launch_fused<8>(cl, xyz, stride, kept_cloud, m_cap, flags, off, nb, H, w,
                                      spfh_out, fpfh_out, cs, st, s); break;
         }
         KMG_TRY(launch_status());
@@ -1098,14 +1083,13 @@ kmg_status features_fused_batch(const CloudDev* cl, int n_clouds, const float* x
 
 kmg_status features_batch(const CloudDev* cl, int n_clouds, const float* xyz, int64_t stride,
                           const int32_t* kept_cloud, int64_t m_cap, int H, DevStatus* st, const FeatWs& w,
-                          const int32_t* off, NbrLists nb, const float* nrm, int64_t nrm_stride,
+                          const int32_t* off, NbrLists nb,
                           uint8_t* flags, float* spfh_out, float* fpfh_out, int32_t* j_idx, CloudState* cs,
                           hipStream_t s, bool cleared, MatchSet* sets, uint64_t* j_scan_status) {
     if (tuning().fuse_features)
-        return features_fused_batch(cl, n_clouds, xyz, stride, kept_cloud, m_cap, H, st, w, off, nb, nrm,
-                                    nrm_stride, flags, spfh_out, fpfh_out, j_idx, cs, s, cleared, sets);
-    KMG_TRY(spfh_batch(cl, xyz, stride, kept_cloud, m_cap, H, st, w, off, nb, nrm, nrm_stride, flags, spfh_out, s,
-                       cleared));
+        return features_fused_batch(cl, n_clouds, xyz, stride, kept_cloud, m_cap, H, st, w, off, nb,
+                                    flags, spfh_out, fpfh_out, j_idx, cs, s, cleared, sets);
+    KMG_TRY(spfh_batch(cl, kept_cloud, m_cap, H, st, w, off, nb, spfh_out, s, cleared));
     return fpfh_batch(n_clouds, xyz, stride, m_cap, H, st, w, off, nb, flags, fpfh_out, j_idx, cs, s, sets,
                       j_scan_status);
 }

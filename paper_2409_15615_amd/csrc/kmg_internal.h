@@ -364,12 +364,13 @@ kmg_status search_count_batch(const CloudDev* cl, const float* xyz, int64_t stri
 // Fill pass (lists ascending), its dense pass (lists longer than the first
 // takes; st->dense tells whether there are any) and normals, by `parts`.
 // Writes nothing into nbr when st->nnz > nbr_cap (device-side check;
-// st->err_capacity is set).
+// st->err_capacity is set).  rec (optional): the points' records for the
+// feature passes.
 enum : int { kFillLists = 1, kFillDense = 2, kFillNormals = 4, kFillAll = 7 };
 kmg_status search_fill_batch(const CloudDev* cl, const float* xyz, int64_t stride, const int32_t* kept_cloud,
                              int64_t m_cap, int64_t nbr_cap, int parts, DevStatus* st, const SearchWs& w,
                              const int32_t* off, int32_t* nbr, float* nrm, int64_t nrm_stride, uint8_t* flags,
-                             int32_t* n_normal, hipStream_t s, int use_rn = 0);
+                             int32_t* n_normal, hipStream_t s, int use_rn = 0, float4* rec = nullptr);
 // The list-first form of the grid build, search and normals (r_FPFH lists,
 // tables cleared beforehand): one search pass writes |N(q)| and each list
 // that fits a row of the pad (pad_cap entries shared evenly by the kept
@@ -383,7 +384,7 @@ kmg_status search_lists_first(const CloudDev* cl, const float* xyz, int64_t stri
                               int64_t m_cap, int64_t nbr_cap, DevStatus* st, const SearchWs& w, int32_t* off,
                               int32_t* nbr, int32_t* pad, int64_t pad_cap, int32_t* long_q, float* nrm,
                               int64_t nrm_stride, uint8_t* flags, hipStream_t s, bool inserted = false,
-                              uint64_t* scan_status = nullptr);
+                              uint64_t* scan_status = nullptr, float4* rec = nullptr);
 
 // ---- features.hip ---------------------------------------------------------
 // Row stride of the SPFH counts, in entries: 3H rounded up to a multiple of 8,
@@ -394,6 +395,7 @@ __host__ __device__ constexpr int spfh_row(int H) { return (kSpfhHead + 3 * H + 
 struct FeatWs {
     uint16_t* cnt16;  // SPFH bin counts (Eq. A4 numerators), m rows of spfh_row(H): the head, then 3H
     double* inv100;   // 100 / P_q (0 when P_q = 0)
+    float4* rec;      // per point: coordinates and flag B, normal (made before the features run)
     uint32_t* queue;  // work queue of the fused SPFH / FPFH launch
     int32_t* ready;   // per cloud: points whose SPFH is written (fused launch)
     int32_t* Pq;
@@ -405,18 +407,18 @@ FeatWs carve_feat(Carver& c, int64_t m_cap, int H);
 // Step 2, SPFH, FPFH and the J list over the kept points (count st->m_kept).
 // j_idx receives the kept indices of the J points (in the batch's global kept
 // space); cs, when given, receives the per-cloud J ranges, and sets (with cs)
-// each cloud's matching set.  cleared: jflag is zero already.
+// each cloud's matching set.  cleared: jflag is zero already.  w.rec holds the
+// points' records (the normals pass or the caller's init wrote them).
 kmg_status features_batch(const CloudDev* cl, int n_clouds, const float* xyz, int64_t stride,
                           const int32_t* kept_cloud, int64_t m_cap, int H, DevStatus* st, const FeatWs& w,
-                          const int32_t* off, NbrLists nb, const float* nrm, int64_t nrm_stride,
+                          const int32_t* off, NbrLists nb,
                           uint8_t* flags, float* spfh_out, float* fpfh_out, int32_t* j_idx, CloudState* cs,
                           hipStream_t s, bool cleared = false, MatchSet* sets = nullptr,
                           uint64_t* j_scan_status = nullptr);
 // The two halves of features_batch: SPFH (and J) over (off, nb); then the
 // FPFH sum over (off, nb) and the J list.
-kmg_status spfh_batch(const CloudDev* cl, const float* xyz, int64_t stride, const int32_t* kept_cloud,
-                      int64_t m_cap, int H, DevStatus* st, const FeatWs& w, const int32_t* off, NbrLists nb,
-                      const float* nrm, int64_t nrm_stride, uint8_t* flags, float* spfh_out, hipStream_t s,
+kmg_status spfh_batch(const CloudDev* cl, const int32_t* kept_cloud, int64_t m_cap, int H, DevStatus* st,
+                      const FeatWs& w, const int32_t* off, NbrLists nb, float* spfh_out, hipStream_t s,
                       bool cleared = false);
 kmg_status fpfh_batch(int n_clouds, const float* xyz, int64_t stride, int64_t m_cap, int H, DevStatus* st,
                       const FeatWs& w, const int32_t* off, NbrLists nb, uint8_t* flags, float* fpfh_out,
@@ -510,7 +512,7 @@ kmg_status match(const float* dp, const int32_t* rp, int64_t np, const float* dq
 struct Tuning {
     int search_waves = 4;     // waves per block of the radius count and fill passes (2, 4, 8)
     int count_queries = 2;    // queries per wavefront in the count pass (1, 2, 4)
-    int spfh_pair_mean = 24;  // mean list length up to which SPFH takes two points per wavefront
+    int spfh_pair_mean = 24;  // accepted, without effect
     int fpfh_rows = 2;        // SPFH rows per unrolled step of the FPFH sum (1, 2, 4, 8, 16)
     int band_tile = 0;        // accepted, without effect
     int fuse_features = 0;    // 1: SPFH and FPFH in one persistent launch (per-cloud readiness counters)

@@ -549,7 +549,8 @@ __global__ __launch_bounds__(kBlock) void normals_kernel(const CloudDev* __restr
                                                          const int32_t* __restrict__ nbr, int64_t nbr_cap,
                                                          float* __restrict__ nrm, int64_t nrm_stride,
                                                          uint8_t* __restrict__ flags, int32_t* __restrict__ n_normal,
-                                                         DevStatus* st, const int32_t* __restrict__ pad = nullptr,
+                                                         DevStatus* st, float4* __restrict__ rec,
+                                                         const int32_t* __restrict__ pad = nullptr,
                                                          int64_t pad_cap = 0) {
     const int64_t m = clamp_count(st->m_kept, m_cap);
     // list-first form: the lists stay in their pad rows; a list volume beyond
@@ -623,6 +624,10 @@ __global__ __launch_bounds__(kBlock) void normals_kernel(const CloudDev* __restr
         if (e - b < tau_num || nn < tau_num) {
             nrm[q] = nrm[nrm_stride + q] = nrm[2 * nrm_stride + q] = 0.0f;
             flags[q] = 0;
+            if (rec) {
+                rec[2 * q] = make_float4(qx, qy, qz, __int_as_float(0));
+                rec[2 * q + 1] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
             continue;
         }
         const double inv = 1.0 / nn;
@@ -669,7 +674,12 @@ __global__ __launch_bounds__(kBlock) void normals_kernel(const CloudDev* __restr
         nrm[q] = static_cast<float>(n0);
         nrm[nrm_stride + q] = static_cast<float>(n1);
         nrm[2 * nrm_stride + q] = static_cast<float>(n2);
-        flags[q] = (plin < cl[c].tau_lin) ? 1 : 0;
+        const int in_b = (plin < cl[c].tau_lin) ? 1 : 0;
+        flags[q] = static_cast<uint8_t>(in_b);
+        if (rec) {
+            rec[2 * q] = make_float4(qx, qy, qz, __int_as_float(in_b));
+            rec[2 * q + 1] = make_float4(static_cast<float>(n0), static_cast<float>(n1), static_cast<float>(n2), 0.f);
+        }
     }
 }
 
@@ -819,7 +829,7 @@ kmg_status search_lists_first(const CloudDev* cl, const float* xyz, int64_t stri
                               int64_t m_cap, int64_t nbr_cap, DevStatus* st, const SearchWs& w, int32_t* off,
                               int32_t* nbr, int32_t* pad, int64_t pad_cap, int32_t* long_q, float* nrm,
                               int64_t nrm_stride, uint8_t* flags, hipStream_t s, bool inserted,
-                              uint64_t* scan_status) {
+                              uint64_t* scan_status, float4* rec) {
     KMG_TRY(build_grid(cl, xyz, stride, kept_cloud, m_cap, st, w, s, true, inserted, scan_status));
     if (m_cap > 0) {
         StageScope sc(ST_SEARCH_FILL, s);
@@ -844,7 +854,8 @@ kmg_status search_lists_first(const CloudDev* cl, const float* xyz, int64_t stri
     {
         StageScope sc(ST_NORMALS, s);
         normals_kernel<<<grid_cap(m_cap * kNormalLanes, kBlock), kBlock, 0, s>>>(
-            cl, xyz, stride, kept_cloud, m_cap, off, nbr, nbr_cap, nrm, nrm_stride, flags, nullptr, st, pad, pad_cap);
+            cl, xyz, stride, kept_cloud, m_cap, off, nbr, nbr_cap, nrm, nrm_stride, flags, nullptr, st, rec, pad,
+            pad_cap);
         KMG_TRY(launch_status());
     }
     return KMG_OK;
@@ -853,7 +864,7 @@ kmg_status search_lists_first(const CloudDev* cl, const float* xyz, int64_t stri
 kmg_status search_fill_batch(const CloudDev* cl, const float* xyz, int64_t stride, const int32_t* kept_cloud,
                              int64_t m_cap, int64_t nbr_cap, int parts, DevStatus* st, const SearchWs& w,
                              const int32_t* off, int32_t* nbr, float* nrm, int64_t nrm_stride, uint8_t* flags,
-                             int32_t* n_normal, hipStream_t s, int use_rn) {
+                             int32_t* n_normal, hipStream_t s, int use_rn, float4* rec) {
     if (m_cap <= 0) return KMG_OK;
     {
         StageScope sc(ST_SEARCH_FILL, s);
@@ -869,7 +880,7 @@ kmg_status search_fill_batch(const CloudDev* cl, const float* xyz, int64_t strid
     if (parts & kFillNormals) {
         StageScope sc(ST_NORMALS, s);
         normals_kernel<<<grid_cap(m_cap * kNormalLanes, kBlock), kBlock, 0, s>>>(
-            cl, xyz, stride, kept_cloud, m_cap, off, nbr, nbr_cap, nrm, nrm_stride, flags, n_normal, st);
+            cl, xyz, stride, kept_cloud, m_cap, off, nbr, nbr_cap, nrm, nrm_stride, flags, n_normal, st, rec);
         KMG_TRY(launch_status());
     }
     return KMG_OK;

@@ -9,9 +9,15 @@ namespace {
 // Clears the status, writes the cloud's record (block 0) and does the fills of
 // the call (a launch each, they were half of a small call's launches).
 // off (optional): the caller's neighbour lists, whose volume off[m_kept] goes
-// to st->nnz.
+// to st->nnz.  r (optional): the points' records from the caller's arrays.
+struct RecJob {
+    float4* rec;
+    const float* xyz;
+    const float* nrm;
+    const uint8_t* flags;
+};
 __global__ __launch_bounds__(256) void init_single(DevStatus* st, CloudDev* cl, CloudDev v, int64_t n_raw,
-                                                   int64_t m_kept, const int32_t* off, FillJobs fills) {
+                                                   int64_t m_kept, const int32_t* off, FillJobs fills, RecJob r) {
     if (blockIdx.x == 0) {
         const int i = threadIdx.x;
         uint32_t* w = reinterpret_cast<uint32_t*>(st);
@@ -25,6 +31,12 @@ __global__ __launch_bounds__(256) void init_single(DevStatus* st, CloudDev* cl, 
         }
     }
     run_fill_jobs(fills);
+    if (!r.rec) return;
+    for (int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; q < m_kept;
+         q += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+        r.rec[2 * q] = make_float4(r.xyz[q], r.xyz[m_kept + q], r.xyz[2 * m_kept + q], __int_as_float(r.flags[q] & 1));
+        r.rec[2 * q + 1] = make_float4(r.nrm[q], r.nrm[m_kept + q], r.nrm[2 * m_kept + q], 0.f);
+    }
 }
 
 void add_fill(FillJobs& f, void* p, uint64_t v, int64_t n, int32_t bytes) { f.job[f.n_jobs++] = FillJob{p, v, n, bytes}; }
@@ -39,11 +51,11 @@ void add_search_fills(FillJobs& f, const SearchWs& w, int64_t m) {
 }
 
 kmg_status init(DevStatus* st, CloudDev* cl, const CloudDev& v, int64_t n_raw, int64_t m_kept, const FillJobs& fills,
-                hipStream_t s, const int32_t* off = nullptr) {
-    int64_t most = 1;
+                hipStream_t s, const int32_t* off = nullptr, const RecJob& r = RecJob{}) {
+    int64_t most = std::max<int64_t>(r.rec ? m_kept : 1, 1);
     for (int k = 0; k < fills.n_jobs; ++k) most = std::max(most, fills.job[k].n);
     init_single<<<static_cast<unsigned>(std::min<int64_t>((most + 255) / 256, 4096)), 256, 0, s>>>(st, cl, v, n_raw,
-                                                                                                  m_kept, off, fills);
+                                                                                                  m_kept, off, fills, r);
     return launch_status();
 }
 
@@ -237,13 +249,13 @@ kmg_status fpfh(const float* xyz, const float* nrm, uint8_t* flags, const int32_
     add_fill(fills, w.jflag, 0ull, std::max<int64_t>(m, 1), 4);
     add_fill(fills, w.scan_tmp, 0ull, static_cast<int64_t>(scan_temp_elems(m)), 8);
     if (classic) add_search_fills(fills, sw, m);
-    KMG_TRY(init(st, cl, make_cloud(p, nullptr, 0, 0), 0, m, fills, s, off));
+    KMG_TRY(init(st, cl, make_cloud(p, nullptr, 0, 0), 0, m, fills, s, off, RecJob{w.rec, xyz, nrm, flags}));
     if (!classic) {
-        KMG_TRY(features_batch(cl, 1, xyz, m, nullptr, m, H, st, w, off, NbrLists{nbr}, nrm, m, flags, spfh_out,
+        KMG_TRY(features_batch(cl, 1, xyz, m, nullptr, m, H, st, w, off, NbrLists{nbr}, flags, spfh_out,
                                fpfh_out, j_idx, nullptr, s, true, nullptr, look_back_words(w.scan_tmp)));
     } else {
         // SPFH over the lists of search 2; search 3 (r_FPFH again) for the FPFH sum
-        KMG_TRY(spfh_batch(cl, xyz, m, nullptr, m, H, st, w, off, NbrLists{nbr}, nrm, m, flags, spfh_out, s, true));
+        KMG_TRY(spfh_batch(cl, nullptr, m, H, st, w, off, NbrLists{nbr}, spfh_out, s, true));
         KMG_TRY(search_count_batch(cl, xyz, m, nullptr, m, st, sw, off3, s, true, 0, true, false,
                                    look_back_words(sw.scan_tmp)));
         KMG_TRY(fill_counted(cl, xyz, m, nnz3_cap, st, sw, off3, nbr3, nullptr, flags, nullptr, s, 0, false, nullptr,
