@@ -18,6 +18,8 @@
 // eigen-solver in FP64, the linearity test and viewpoint orientation.
 #include <climits>
 
+#include <type_traits>
+
 #include "kmg_device.h"
 
 namespace kmg {
@@ -145,7 +147,31 @@ __device__ __forceinline__ void wave_sort_write(const int32_t* list, int n, int3
     group_sort_write<E, kWave>(list, n, out, lane_id());
 }
 
-constexpr int kCandRounds = 4;  // candidate loads in flight per lane (list fill)
+constexpr int kCandRounds = 4;  // candidate loads in flight per lane
+
+// Positions in pts of candidates t0 + 0, step, 2 step, ...: the cell is the first
+// whose inclusive prefix exceeds t (32 prefixes, INT_MAX past the 27th), the
+// position t + delta[cell].  The searches of a round go side by side, five LDS
+// latencies in all; one after the other, each with its own loop, they were twenty
+// (64 pairs: fill 2.41 -> 2.08 ms; a cloud of 5,000 points: fill 23 -> 19 us for
+// two, count 21 -> 15).
+template <int N>
+__device__ __forceinline__ void candidate_places(const int32_t* incl, const int32_t* delta, int t0, int step,
+                                                 int (&at)[N]) {
+    int c[N];
+#pragma unroll
+    for (int u = 0; u < N; ++u) c[u] = 0;
+#pragma unroll
+    for (int s = 16; s > 0; s >>= 1) {
+        int v[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) v[u] = incl[c[u] + s - 1];
+#pragma unroll
+        for (int u = 0; u < N; ++u) c[u] += v[u] <= t0 + u * step ? s : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) at[u] = t0 + u * step + delta[c[u]];
+}
 constexpr int kNbrRounds = 4;   // neighbour-list entries in flight per lane (normals)
 
 // One wavefront per query, queries visited in cell-sorted order (grid-stride).
@@ -293,7 +319,7 @@ __global__ __launch_bounds__(kWaves* kWave) void radius_count2(const CloudDev* _
     constexpr int G = kWave / kCountGroups;
     constexpr int kPer = (27 + G - 1) / G;  // cells per lane
     __shared__ int32_t s_incl[kWaves][kCountGroups][32];
-    __shared__ int32_t s_start[kWaves][kCountGroups][32];
+    __shared__ int32_t s_delta[kWaves][kCountGroups][32];
     const int wv = threadIdx.x / kWave;
     const int lane = lane_id();
     const int gi = lane / G, gl = lane % G, sh = G * gi;
@@ -322,7 +348,7 @@ __global__ __launch_bounds__(kWaves* kWave) void radius_count2(const CloudDev* _
                 const int64_t cy = cell_coord(qp.y, inv_c) + (cell / 3) % 3 - 1;
                 const int64_t cz = cell_coord(qp.z, inv_c) + cell / 9 - 1;
                 const uint64_t key = pack_key(c, cx, cy, cz);
-            const int h = hash_find(g.keys, g.mask, key, cell_home(key, g.mask));
+                const int h = hash_find(g.keys, g.mask, key, cell_home(key, g.mask));
                 if (h >= 0) {
                     cs[u] = g.start[h];
                     cc[u] = g.count[h];
@@ -343,7 +369,7 @@ __global__ __launch_bounds__(kWaves* kWave) void radius_count2(const CloudDev* _
             const int cell = gl + u * G;
             if (cell < 32) {
                 s_incl[wv][gi][cell] = (cell < 27) ? base_u + incl : INT_MAX;
-                s_start[wv][gi][cell] = cs[u];
+                s_delta[wv][gi][cell] = cs[u] - (base_u + incl - cc[u]);  // first point less the candidates before
             }
             base_u += __shfl(incl, sh + G - 1, kWave);
         }
@@ -354,21 +380,29 @@ __global__ __launch_bounds__(kWaves* kWave) void radius_count2(const CloudDev* _
         for (int d = G; d < kWave; d <<= 1) tmax = max(tmax, __shfl_xor(tmax, d, kWave));
         __builtin_amdgcn_wave_barrier();
         int found = 0;
-        for (int b0 = 0; b0 < tmax; b0 += G) {
-            const int t = b0 + gl;
-            bool in = false;
-            if (t < total) {
-                int lo = 0, hi = 26;  // first cell whose inclusive prefix exceeds t
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (s_incl[wv][gi][mid] > t) hi = mid;
-                    else lo = mid + 1;
-                }
-                const int before = lo ? s_incl[wv][gi][lo - 1] : 0;
-                const float4 sp = g.pts[s_start[wv][gi][lo] + (t - before)];
-                in = in_radius(rt, qp.x, qp.y, qp.z, sp.x, sp.y, sp.z);
+        const auto test = [&](auto n, int b0) {  // n rounds of G candidates from b0 on
+            constexpr int N = decltype(n)::value;
+            int at[N];
+            candidate_places(s_incl[wv][gi], s_delta[wv][gi], b0 + gl, G, at);
+            float4 sp[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+                sp[u] = b0 + u * G + gl < total ? g.pts[at[u]] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const bool in = b0 + u * G + gl < total &&
+                                in_radius(rt, qp.x, qp.y, qp.z, sp[u].x, sp[u].y, sp[u].z);
+                found += __popcll(ballot(in) & gmask);
             }
-            found += __popcll(ballot(in) & gmask);
+        };
+        for (int b0 = 0; b0 < tmax;) {  // a single round where that is all that is left
+            if (tmax - b0 > G) {
+                test(std::integral_constant<int, kCandRounds>{}, b0);
+                b0 += kCandRounds * G;
+            } else {
+                test(std::integral_constant<int, 1>{}, b0);
+                b0 += G;
+            }
         }
         if (act && gl == 0) {
             deg[q] = found;
@@ -399,7 +433,7 @@ __global__ __launch_bounds__(kWaves* kWave) void radius_fill2(const CloudDev* __
                                                               DevStatus* st) {
     constexpr int kHalf = kWave / 2;
     __shared__ int32_t s_incl[kWaves][2][kHalf];
-    __shared__ int32_t s_start[kWaves][2][kHalf];
+    __shared__ int32_t s_delta[kWaves][2][kHalf];
     __shared__ int32_t s_list[kWaves][2][kListSmall];
     const int wv = threadIdx.x / kWave;
     const int lane = lane_id();
@@ -412,10 +446,13 @@ __global__ __launch_bounds__(kWaves* kWave) void radius_fill2(const CloudDev* __
     }
     if (st->err_range || st->err_sync) return;  // no search over a partial grid, no lists at partial offsets
     const int row = kFirst ? pad_stride(nbr_cap, m) : 0;
-    for (int64_t pw = static_cast<int64_t>(blockIdx.x) * kWaves + wv; 2 * pw < m;
-         pw += static_cast<int64_t>(gridDim.x) * kWaves) {
+    const int64_t step = static_cast<int64_t>(gridDim.x) * kWaves;
+    const auto query = [&](int64_t w) { return w < m ? g.pts[w] : make_float4(0.f, 0.f, 0.f, __int_as_float(-1)); };
+    float4 next = query(2 * (static_cast<int64_t>(blockIdx.x) * kWaves + wv) + hf);
+    for (int64_t pw = static_cast<int64_t>(blockIdx.x) * kWaves + wv; 2 * pw < m; pw += step) {
         const int64_t w = 2 * pw + hf;
-        const float4 qp = w < m ? g.pts[w] : make_float4(0.f, 0.f, 0.f, __int_as_float(-1));
+        const float4 qp = next;
+        next = query(w + 2 * step);
         const int q = __float_as_int(qp.w);
         // longer lists are the dense pass's
         const bool act = q >= 0 && q < m && (kFirst || off[q + 1] - off[q] <= kListSmall);
@@ -444,39 +481,39 @@ __global__ __launch_bounds__(kWaves* kWave) void radius_fill2(const CloudDev* __
         const int tmax = max(total, __shfl_xor(total, kHalf, kWave));
         __builtin_amdgcn_wave_barrier();
         s_incl[wv][hf][hl] = (hl < 27) ? incl : INT_MAX;
-        s_start[wv][hf][hl] = cs;
+        s_delta[wv][hf][hl] = cs - (incl - cc);  // first point less the candidates before the cell
         __builtin_amdgcn_wave_barrier();
         // candidates in rounds of kCandRounds x 32: the round's loads are all in
         // flight before the first test, and the tests keep candidate order
         int found = 0;
         const uint32_t below = (1u << hl) - 1u;
-        for (int base = 0; base < tmax; base += kCandRounds * kHalf) {
-            float4 sp[kCandRounds];
+        const auto take = [&](auto n, int base) {  // n rounds of 32 candidates from base on
+            constexpr int N = decltype(n)::value;
+            int at[N];
+            candidate_places(s_incl[wv][hf], s_delta[wv][hf], base + hl, kHalf, at);
+            float4 sp[N];
 #pragma unroll
-            for (int u = 0; u < kCandRounds; ++u) {
-                const int t = base + u * kHalf + hl;
-                sp[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (t < total) {
-                    int lo = 0, hi = 26;  // first cell whose inclusive prefix exceeds t
-                    while (lo < hi) {
-                        const int mid = (lo + hi) >> 1;
-                        if (s_incl[wv][hf][mid] > t) hi = mid;
-                        else lo = mid + 1;
-                    }
-                    const int before = lo ? s_incl[wv][hf][lo - 1] : 0;
-                    sp[u] = g.pts[s_start[wv][hf][lo] + (t - before)];
-                }
-            }
+            for (int u = 0; u < N; ++u)
+                sp[u] = base + u * kHalf + hl < total ? g.pts[at[u]] : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-            for (int u = 0; u < kCandRounds; ++u) {
+            for (int u = 0; u < N; ++u) {
                 const bool in = base + u * kHalf + hl < total &&
                                 in_radius(rt, qp.x, qp.y, qp.z, sp[u].x, sp[u].y, sp[u].z);
                 const uint32_t b = static_cast<uint32_t>(ballot(in) >> (kHalf * hf));
                 if (in) {
-                    const int at = found + __popc(b & below);
-                    if (at < kListSmall) s_list[wv][hf][at] = __float_as_int(sp[u].w);
+                    const int to = found + __popc(b & below);
+                    if (to < kListSmall) s_list[wv][hf][to] = __float_as_int(sp[u].w);
                 }
                 found += __popc(b);
+            }
+        };
+        for (int base = 0; base < tmax;) {  // a single round where that is all that is left
+            if (tmax - base > kHalf) {
+                take(std::integral_constant<int, kCandRounds>{}, base);
+                base += kCandRounds * kHalf;
+            } else {
+                take(std::integral_constant<int, 1>{}, base);
+                base += kHalf;
             }
         }
         __builtin_amdgcn_wave_barrier();
@@ -686,7 +723,10 @@ __global__ __launch_bounds__(kBlock) void normals_kernel(const CloudDev* __restr
 template <int kWaves, int kGroups>
 kmg_status count_as(const CloudDev* cl, Grid g, const int32_t* kept_cloud, int64_t m_cap, int32_t* deg, int use_rn,
                     DevStatus* st, hipStream_t s) {
-    radius_count2<kWaves, kGroups><<<grid_cap((m_cap + kGroups - 1) / kGroups, kWaves), kWaves * kWave, 0, s>>>(
+    // shares small enough for the dispatcher to even out (a cloud of 215,000 points 104 -> 83 us
+    // against 8,192 wavefronts)
+    radius_count2<kWaves, kGroups><<<std::min(grid_for((m_cap + kGroups - 1) / kGroups, kWaves), 128 * kCUs / kWaves),
+                                     kWaves * kWave, 0, s>>>(
         cl, g, kept_cloud, m_cap, deg, use_rn, st);
     return launch_status();
 }
@@ -721,7 +761,10 @@ struct FillOut {
 template <int kWaves, bool kFirst>
 kmg_status fill_as(const CloudDev* cl, Grid g, const int32_t* kept_cloud, int64_t m_cap, const FillOut& o,
                    int use_rn, DevStatus* st, hipStream_t s) {
-    radius_fill2<kWaves, kFirst><<<grid_cap((m_cap + 1) / 2, kWaves), kWaves * kWave, 0, s>>>(
+    // one resident round: the lists in LDS let four wavefronts run per SIMD (a cloud of 215,000
+    // points 190 -> 182 us against two rounds)
+    radius_fill2<kWaves, kFirst><<<std::min(grid_for((m_cap + 1) / 2, kWaves), 16 * kCUs / kWaves), kWaves * kWave, 0,
+                                   s>>>(
         cl, g, kept_cloud, m_cap, o.off, o.nbr, o.nbr_cap, o.deg, o.long_q, use_rn, st);
     return launch_status();
 }
