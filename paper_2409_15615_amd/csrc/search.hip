@@ -28,6 +28,7 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kNormalLanes = 4;  // lanes per point in the normal estimation
+constexpr unsigned kNormalBlocks = 65536;
 
 struct Grid {
     const float4* pts;     // cell-sorted points; w = bit pattern of the kept index
@@ -172,7 +173,7 @@ __device__ __forceinline__ void candidate_places(const int32_t* incl, const int3
 #pragma unroll
     for (int u = 0; u < N; ++u) at[u] = t0 + u * step + delta[c[u]];
 }
-constexpr int kNbrRounds = 4;   // neighbour-list entries in flight per lane (normals)
+constexpr int kNbrRounds = 8;   // neighbour-list entries in flight per lane (normals)
 
 // One wavefront per query, queries visited in cell-sorted order (grid-stride).
 // kFill = false: writes |N(q)| to deg[q].
@@ -579,6 +580,147 @@ __device__ __forceinline__ void jacobi_plane(double& app, double& aqq, double& a
     }
 }
 
+// Moments of the r_normal subset of point q's list, shifted to the query (FP64):
+// a group of kNormalLanes lanes, every lane ending with the totals.
+struct Moments {
+    int nn;
+    double sx, sy, sz, sxx, sxy, sxz, syy, syz, szz;
+};
+__device__ __forceinline__ Moments point_moments(const CloudDev* __restrict__ cl, const float* __restrict__ xyz,
+                                                 int64_t stride, const int32_t* __restrict__ kept_cloud,
+                                                 const int32_t* __restrict__ off, const NbrLists& lists, int row,
+                                                 int64_t q, int sub) {
+    const int c = cloud_of(kept_cloud, q);
+    const RadiusTest rn = cl[c].rn;
+    const float qx = xyz[q], qy = xyz[stride + q], qz = xyz[2 * stride + q];
+    const int b = off[q], e = off[q + 1];
+    const int32_t* src = list_of(lists, row, q, b, e);
+    int nn = 0;
+    double sx = 0, sy = 0, sz = 0, sxx = 0, sxy = 0, sxz = 0, syy = 0, syz = 0, szz = 0;
+    // kNbrRounds list entries per lane and round: their loads are in flight together
+    for (int k0 = b + sub; k0 < e; k0 += kNormalLanes * kNbrRounds) {
+        int id[kNbrRounds];
+#pragma unroll
+        for (int u = 0; u < kNbrRounds; ++u) {
+            const int k = k0 + u * kNormalLanes;
+            id[u] = k < e ? src[k - b] : -1;
+        }
+        float px[kNbrRounds], py[kNbrRounds], pz[kNbrRounds];
+#pragma unroll
+        for (int u = 0; u < kNbrRounds; ++u) {
+            const int s = id[u] < 0 ? 0 : id[u];
+            px[u] = xyz[s];
+            py[u] = xyz[stride + s];
+            pz[u] = xyz[2 * stride + s];
+        }
+#pragma unroll
+        for (int u = 0; u < kNbrRounds; ++u) {
+            if (id[u] < 0 || !in_radius(rn, qx, qy, qz, px[u], py[u], pz[u])) continue;
+            ++nn;
+            const double dx = static_cast<double>(px[u]) - qx, dy = static_cast<double>(py[u]) - qy,
+                         dz = static_cast<double>(pz[u]) - qz;
+            sx += dx;
+            sy += dy;
+            sz += dz;
+            sxx += dx * dx;
+            sxy += dx * dy;
+            sxz += dx * dz;
+            syy += dy * dy;
+            syz += dy * dz;
+            szz += dz * dz;
+        }
+    }
+#pragma unroll
+    for (int d = 1; d < kNormalLanes; d <<= 1) {
+        nn += __shfl_xor(nn, d, kNormalLanes);
+        sx += __shfl_xor(sx, d, kNormalLanes);
+        sy += __shfl_xor(sy, d, kNormalLanes);
+        sz += __shfl_xor(sz, d, kNormalLanes);
+        sxx += __shfl_xor(sxx, d, kNormalLanes);
+        sxy += __shfl_xor(sxy, d, kNormalLanes);
+        sxz += __shfl_xor(sxz, d, kNormalLanes);
+        syy += __shfl_xor(syy, d, kNormalLanes);
+        syz += __shfl_xor(syz, d, kNormalLanes);
+        szz += __shfl_xor(szz, d, kNormalLanes);
+    }
+    return Moments{nn, sx, sy, sz, sxx, sxy, sxz, syy, syz, szz};
+}
+
+// Normal, orientation and flag of point q from its moments (FP64).
+__device__ __forceinline__ void finish_point(const CloudDev* __restrict__ cl, const float* __restrict__ xyz,
+                                             int64_t stride, const int32_t* __restrict__ kept_cloud,
+                                             const int32_t* __restrict__ off, float* __restrict__ nrm,
+                                             int64_t nrm_stride, uint8_t* __restrict__ flags,
+                                             int32_t* __restrict__ n_normal, DevStatus* st, float4* __restrict__ rec,
+                                             int64_t q, int nn, const double (&mom)[9]) {
+    const double sx = mom[0], sy = mom[1], sz = mom[2], sxx = mom[3], sxy = mom[4], sxz = mom[5], syy = mom[6],
+                 syz = mom[7], szz = mom[8];
+    const int c = cloud_of(kept_cloud, q);
+    const float qx = xyz[q], qy = xyz[stride + q], qz = xyz[2 * stride + q];
+    const int b = off[q], e = off[q + 1];
+    if (n_normal) n_normal[q] = nn;
+    const int tau_num = cl[c].tau_num;
+    if (e - b < tau_num || nn < tau_num) {
+        nrm[q] = nrm[nrm_stride + q] = nrm[2 * nrm_stride + q] = 0.0f;
+        flags[q] = 0;
+        if (rec) {
+            rec[2 * q] = make_float4(qx, qy, qz, __int_as_float(0));
+            rec[2 * q + 1] = make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        return;
+    }
+    const double inv = 1.0 / nn;
+    const double mx = sx * inv, my = sy * inv, mz = sz * inv;
+    double a00 = sxx * inv - mx * mx, a01 = sxy * inv - mx * my, a02 = sxz * inv - mx * mz;
+    double a11 = syy * inv - my * my, a12 = syz * inv - my * mz, a22 = szz * inv - mz * mz;
+    double V[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
+    for (int sweep = 0; sweep < 16; ++sweep) {
+        if (a01 == 0.0 && a02 == 0.0 && a12 == 0.0) break;
+        jacobi_plane(a00, a11, a01, a02, a12, V, 0, 1);
+        jacobi_plane(a00, a22, a02, a01, a12, V, 0, 2);
+        jacobi_plane(a11, a22, a12, a01, a02, V, 1, 2);
+    }
+    const double d[3] = {a00, a11, a22};
+    int imax = 0, imin = 0;
+#pragma unroll
+    for (int i = 1; i < 3; ++i) {
+        if (d[i] > d[imax]) imax = i;
+        if (d[i] < d[imin]) imin = i;
+    }
+    if (imax == imin) {  // all eigenvalues equal
+        imax = 0;
+        imin = 2;
+    }
+    const int imid = 3 - imax - imin;
+    const double l1 = d[imax], l2 = d[imid];
+    double n0 = V[0][imin], n1 = V[1][imin], n2 = V[2][imin];
+    const double nl = sqrt(n0 * n0 + n1 * n1 + n2 * n2);
+    n0 /= nl;
+    n1 /= nl;
+    n2 /= nl;
+    const double tx = cl[c].vp[0] - qx, ty = cl[c].vp[1] - qy, tz = cl[c].vp[2] - qz;
+    const double dot = n0 * tx + n1 * ty + n2 * tz;
+    bool flip = dot < 0.0;
+    if (dot == 0.0) flip = (n0 != 0.0) ? (n0 < 0.0) : ((n1 != 0.0) ? (n1 < 0.0) : (n2 < 0.0));
+    if (flip) {
+        n0 = -n0;
+        n1 = -n1;
+        n2 = -n2;
+    }
+    if (fabs(dot) < 1e-12 * sqrt(tx * tx + ty * ty + tz * tz)) atomicAdd(&st->amb_orientation, 1u);
+    const double plin = (l1 - l2) / l1;
+    if (fabs(plin - cl[c].tau_lin) < 1e-12) atomicAdd(&st->amb_linearity, 1u);
+    nrm[q] = static_cast<float>(n0);
+    nrm[nrm_stride + q] = static_cast<float>(n1);
+    nrm[2 * nrm_stride + q] = static_cast<float>(n2);
+    const int in_b = (plin < cl[c].tau_lin) ? 1 : 0;
+    flags[q] = static_cast<uint8_t>(in_b);
+    if (rec) {
+        rec[2 * q] = make_float4(qx, qy, qz, __int_as_float(in_b));
+        rec[2 * q + 1] = make_float4(static_cast<float>(n0), static_cast<float>(n1), static_cast<float>(n2), 0.f);
+    }
+}
+
 __global__ __launch_bounds__(kBlock) void normals_kernel(const CloudDev* __restrict__ cl,
                                                          const float* __restrict__ xyz, int64_t stride,
                                                          const int32_t* __restrict__ kept_cloud, int64_t m_cap,
@@ -596,127 +738,41 @@ __global__ __launch_bounds__(kBlock) void normals_kernel(const CloudDev* __restr
     if (st->err_range || st->nnz > nbr_cap) return;
     const int row = pad ? pad_stride(pad_cap, m) : 0;
     const NbrLists lists{nbr, pad, pad_cap};
-    // kNormalLanes lanes per point: each sums every kNormalLanes-th list entry, then
-    // the group adds up its partial moments (every lane ends with the totals)
-    const int sub = lane_id() % kNormalLanes;
-    const int64_t gs = static_cast<int64_t>(gridDim.x) * (kBlock / kNormalLanes);
-    for (int64_t q = (static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x) / kNormalLanes; q < m; q += gs) {
-        const int c = cloud_of(kept_cloud, q);
-        const RadiusTest rn = cl[c].rn;
-        const float qx = xyz[q], qy = xyz[stride + q], qz = xyz[2 * stride + q];
-        const int b = off[q], e = off[q + 1];
-        const int32_t* src = list_of(lists, row, q, b, e);
-        int nn = 0;
-        // moments of the r_normal subset, shifted to the query (FP64)
-        double sx = 0, sy = 0, sz = 0, sxx = 0, sxy = 0, sxz = 0, syy = 0, syz = 0, szz = 0;
-        // kNbrRounds list entries per lane and round: their loads are in flight together
-        for (int k0 = b + sub; k0 < e; k0 += kNormalLanes * kNbrRounds) {
-            int id[kNbrRounds];
-#pragma unroll
-            for (int u = 0; u < kNbrRounds; ++u) {
-                const int k = k0 + u * kNormalLanes;
-                id[u] = k < e ? src[k - b] : -1;
-            }
-            float px[kNbrRounds], py[kNbrRounds], pz[kNbrRounds];
-#pragma unroll
-            for (int u = 0; u < kNbrRounds; ++u) {
-                const int s = id[u] < 0 ? 0 : id[u];
-                px[u] = xyz[s];
-                py[u] = xyz[stride + s];
-                pz[u] = xyz[2 * stride + s];
-            }
-#pragma unroll
-            for (int u = 0; u < kNbrRounds; ++u) {
-                if (id[u] < 0 || !in_radius(rn, qx, qy, qz, px[u], py[u], pz[u])) continue;
-                ++nn;
-                const double dx = static_cast<double>(px[u]) - qx, dy = static_cast<double>(py[u]) - qy,
-                             dz = static_cast<double>(pz[u]) - qz;
-                sx += dx;
-                sy += dy;
-                sz += dz;
-                sxx += dx * dx;
-                sxy += dx * dy;
-                sxz += dx * dz;
-                syy += dy * dy;
-                syz += dy * dz;
-                szz += dz * dz;
+    // 64 points per block: a group of kNormalLanes lanes sums a point's moments, and one
+    // wavefront then finds all 64 points' eigenvectors (a lane of each group did, with
+    // the others idle, and that chain of FP64 divisions and roots is most of the time:
+    // 64 pairs, 3.6 million points, 1013 -> 712 us, a scan pair 30 -> 24, a cloud of
+    // 215,000 points 70 -> 53)
+    __shared__ double s_mom[9][kWave];
+    __shared__ int s_nn[kWave];
+    const int sub = lane_id() % kNormalLanes, g = static_cast<int>(threadIdx.x) / kNormalLanes;
+    // not always the same wavefront of a block, for these may sit on one SIMD
+    const bool finish = static_cast<int>(threadIdx.x / kWave) == static_cast<int>(blockIdx.x / kXcds % (kBlock / kWave));
+    for (int64_t q0 = static_cast<int64_t>(blockIdx.x) * kWave; q0 < m; q0 += static_cast<int64_t>(gridDim.x) * kWave) {
+        if (q0 + g < m) {  // uniform in the group
+            const Moments t = point_moments(cl, xyz, stride, kept_cloud, off, lists, row, q0 + g, sub);
+            if (sub == 0) {
+                s_nn[g] = t.nn;
+                s_mom[0][g] = t.sx;
+                s_mom[1][g] = t.sy;
+                s_mom[2][g] = t.sz;
+                s_mom[3][g] = t.sxx;
+                s_mom[4][g] = t.sxy;
+                s_mom[5][g] = t.sxz;
+                s_mom[6][g] = t.syy;
+                s_mom[7][g] = t.syz;
+                s_mom[8][g] = t.szz;
             }
         }
-#pragma unroll
-        for (int d = 1; d < kNormalLanes; d <<= 1) {
-            nn += __shfl_xor(nn, d, kNormalLanes);
-            sx += __shfl_xor(sx, d, kNormalLanes);
-            sy += __shfl_xor(sy, d, kNormalLanes);
-            sz += __shfl_xor(sz, d, kNormalLanes);
-            sxx += __shfl_xor(sxx, d, kNormalLanes);
-            sxy += __shfl_xor(sxy, d, kNormalLanes);
-            sxz += __shfl_xor(sxz, d, kNormalLanes);
-            syy += __shfl_xor(syy, d, kNormalLanes);
-            syz += __shfl_xor(syz, d, kNormalLanes);
-            szz += __shfl_xor(szz, d, kNormalLanes);
+        __syncthreads();
+        if (finish && q0 + lane_id() < m) {
+            const int l = lane_id();
+            const int nn = s_nn[l];
+            const double mom[9] = {s_mom[0][l], s_mom[1][l], s_mom[2][l], s_mom[3][l], s_mom[4][l],
+                                   s_mom[5][l], s_mom[6][l], s_mom[7][l], s_mom[8][l]};
+            finish_point(cl, xyz, stride, kept_cloud, off, nrm, nrm_stride, flags, n_normal, st, rec, q0 + l, nn, mom);
         }
-        if (sub != 0) continue;  // the group's first lane finishes the point
-        if (n_normal) n_normal[q] = nn;
-        const int tau_num = cl[c].tau_num;
-        if (e - b < tau_num || nn < tau_num) {
-            nrm[q] = nrm[nrm_stride + q] = nrm[2 * nrm_stride + q] = 0.0f;
-            flags[q] = 0;
-            if (rec) {
-                rec[2 * q] = make_float4(qx, qy, qz, __int_as_float(0));
-                rec[2 * q + 1] = make_float4(0.f, 0.f, 0.f, 0.f);
-            }
-            continue;
-        }
-        const double inv = 1.0 / nn;
-        const double mx = sx * inv, my = sy * inv, mz = sz * inv;
-        double a00 = sxx * inv - mx * mx, a01 = sxy * inv - mx * my, a02 = sxz * inv - mx * mz;
-        double a11 = syy * inv - my * my, a12 = syz * inv - my * mz, a22 = szz * inv - mz * mz;
-        double V[3][3] = {{1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
-        for (int sweep = 0; sweep < 16; ++sweep) {
-            if (a01 == 0.0 && a02 == 0.0 && a12 == 0.0) break;
-            jacobi_plane(a00, a11, a01, a02, a12, V, 0, 1);
-            jacobi_plane(a00, a22, a02, a01, a12, V, 0, 2);
-            jacobi_plane(a11, a22, a12, a01, a02, V, 1, 2);
-        }
-        const double d[3] = {a00, a11, a22};
-        int imax = 0, imin = 0;
-#pragma unroll
-        for (int i = 1; i < 3; ++i) {
-            if (d[i] > d[imax]) imax = i;
-            if (d[i] < d[imin]) imin = i;
-        }
-        if (imax == imin) {  // all eigenvalues equal
-            imax = 0;
-            imin = 2;
-        }
-        const int imid = 3 - imax - imin;
-        const double l1 = d[imax], l2 = d[imid];
-        double n0 = V[0][imin], n1 = V[1][imin], n2 = V[2][imin];
-        const double nl = sqrt(n0 * n0 + n1 * n1 + n2 * n2);
-        n0 /= nl;
-        n1 /= nl;
-        n2 /= nl;
-        const double tx = cl[c].vp[0] - qx, ty = cl[c].vp[1] - qy, tz = cl[c].vp[2] - qz;
-        const double dot = n0 * tx + n1 * ty + n2 * tz;
-        bool flip = dot < 0.0;
-        if (dot == 0.0) flip = (n0 != 0.0) ? (n0 < 0.0) : ((n1 != 0.0) ? (n1 < 0.0) : (n2 < 0.0));
-        if (flip) {
-            n0 = -n0;
-            n1 = -n1;
-            n2 = -n2;
-        }
-        if (fabs(dot) < 1e-12 * sqrt(tx * tx + ty * ty + tz * tz)) atomicAdd(&st->amb_orientation, 1u);
-        const double plin = (l1 - l2) / l1;
-        if (fabs(plin - cl[c].tau_lin) < 1e-12) atomicAdd(&st->amb_linearity, 1u);
-        nrm[q] = static_cast<float>(n0);
-        nrm[nrm_stride + q] = static_cast<float>(n1);
-        nrm[2 * nrm_stride + q] = static_cast<float>(n2);
-        const int in_b = (plin < cl[c].tau_lin) ? 1 : 0;
-        flags[q] = static_cast<uint8_t>(in_b);
-        if (rec) {
-            rec[2 * q] = make_float4(qx, qy, qz, __int_as_float(in_b));
-            rec[2 * q + 1] = make_float4(static_cast<float>(n0), static_cast<float>(n1), static_cast<float>(n2), 0.f);
-        }
+        if (q0 + static_cast<int64_t>(gridDim.x) * kWave < m) __syncthreads();  // uniform; the tables are free again
     }
 }
 
@@ -896,7 +952,7 @@ kmg_status search_lists_first(const CloudDev* cl, const float* xyz, int64_t stri
     }
     {
         StageScope sc(ST_NORMALS, s);
-        normals_kernel<<<grid_cap(m_cap * kNormalLanes, kBlock), kBlock, 0, s>>>(
+        normals_kernel<<<std::min(grid_for(m_cap, kWave), kNormalBlocks), kBlock, 0, s>>>(
             cl, xyz, stride, kept_cloud, m_cap, off, nbr, nbr_cap, nrm, nrm_stride, flags, nullptr, st, rec, pad,
             pad_cap);
         KMG_TRY(launch_status());
@@ -922,7 +978,7 @@ kmg_status search_fill_batch(const CloudDev* cl, const float* xyz, int64_t strid
     }
     if (parts & kFillNormals) {
         StageScope sc(ST_NORMALS, s);
-        normals_kernel<<<grid_cap(m_cap * kNormalLanes, kBlock), kBlock, 0, s>>>(
+        normals_kernel<<<std::min(grid_for(m_cap, kWave), kNormalBlocks), kBlock, 0, s>>>(
             cl, xyz, stride, kept_cloud, m_cap, off, nbr, nbr_cap, nrm, nrm_stride, flags, n_normal, st, rec);
         KMG_TRY(launch_status());
     }
