@@ -38,39 +38,13 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 METRIC = "registration pairs/s (Faster-PFH+matching) @25k pts; p50/p99 latency vs plain"
-PEAK_FP64_MFMA_TFLOPS = 78.6
+PEAK_I8_MFMA_TOPS = 5000.0  # dense
+# Operations of one query-row product in the matching's integer sweep: 64 padded dimensions, four products of
+# signed bytes each (16-bit coordinates).  Chunks that the sweep passes over by their norms count as done.
+SWEEP_OPS = 2 * 64 * 4
+SWEEP_KERNEL = ("sample_tiles + sweep_tiles (integer MFMA products of 16-bit coordinates; the products of chunks "
+                "skipped by their norms count as done), %s")
 PEAK_HBM_GBS = 8000.0
-
-# HBM bytes per launch of the band tile kernel on the LiDAR pair under the launch
-# tuning the autotuner picks for it (both matching directions in one launch,
-# band_tiles<9, 1>, tiles of 16 chunks), from two rocprofv3 --pmc passes (FETCH_SIZE,
-# WRITE_SIZE; KiB per dispatch, mean of the 16 launches of that form), each scaled by what
-# the same counter reads for a streaming add of 256 MiB in and 256 MiB out (FETCH_SIZE
-# 131085.2 KiB -> x2.0, WRITE_SIZE 262144 KiB -> x1.0).  The figures hold for the matcher
-# source with this SHA-256 and those tuning fields only; otherwise the field is reported as
-# null until the counters are taken again.
-TILE_TRAFFIC = {
-    "source": "paper_2409_15615_amd/csrc/match.hip",
-    "sha256": "c19c40ba7b1c6146f86b83e53969efbe83c0ec5e5319a86bd9b15fd011006aeb",
-    "fetch_kib": 67735.5,
-    "fetch_scale": 262144.0 / 131085.2,
-    "write_kib": 11850.6,
-    "write_scale": 262144.0 / 262144.0,
-    "tuning": {"match_form": 1, "band_tile": 16},
-}
-
-
-def tile_traffic_bytes(setting):
-    import hashlib
-
-    if any(setting.get(k) != v for k, v in TILE_TRAFFIC["tuning"].items()):
-        return None
-    path = os.path.join(ROOT, TILE_TRAFFIC["source"])
-    with open(path, "rb") as f:
-        if hashlib.sha256(f.read()).hexdigest() != TILE_TRAFFIC["sha256"]:
-            return None
-    t = TILE_TRAFFIC
-    return 1024.0 * (t["fetch_kib"] * t["fetch_scale"] + t["write_kib"] * t["write_scale"])
 
 
 def pct(xs, q):
@@ -144,8 +118,8 @@ def read_stages(lib, steps):
 
 
 def stage_work(lib, name):
-    """Work count of a stage's last timed launch (query-row distances of the
-    norm-band tiles for match_topk), 0 when the stage counts none."""
+    """Work count of a stage's last timed launch (query-row products of the first
+    phase for match_topk), 0 when the stage counts none."""
     nst = lib.kmg_timing_work(None, 0)
     w = (C.c_int64 * nst)()
     lib.kmg_timing_work(w, nst)
@@ -289,7 +263,7 @@ def run_batch64(args, lib, kmg, torch, synth, dev):
     lib.kmg_timing_enable(1)
     t_batch, lat_batch = timed(batched, max(1, args.steps // 2), sync)
     names, ms, ln = read_stages(lib, args.steps)
-    band_pairs = stage_work(lib, "match_topk")
+    products = stage_work(lib, "match_topk")
     lib.kmg_timing_enable(0)
     n_timed = max(1, args.steps // 2)
     stages = {names[i]: round(ms[i] / n_timed, 4) for i in range(len(names))}
@@ -312,12 +286,10 @@ def run_batch64(args, lib, kmg, torch, synth, dev):
 
     kept = [k for r in res_g for k in r.kept]
     nj = [r.n_j for r in res_g]
-    dim = 3 * pairs[0]["params"].n_bins
-    dense = sum(2.0 * a * b * dim for a, b in nj)  # every query against every row, first direction
-    flops = 2.0 * dim * band_pairs if band_pairs > 0 else dense  # what the band tiles evaluate
+    ops = float(SWEEP_OPS) * products  # the first phase's
     i_topk = names.index("match_topk")
     topk_s = ms[i_topk] / max(1, ln[i_topk]) / 1e3
-    achieved = flops / topk_s / 1e12 if topk_s > 0 else 0.0
+    achieved = ops / topk_s / 1e12 if topk_s > 0 else 0.0
     pfh_ms = sum(stages[n] for n in PFH_STAGES)
     pbytes = pfh_bytes(sum(raw), sum(kept), nnz)
     value = n_pairs * args.steps / t_graph
@@ -358,17 +330,15 @@ def run_batch64(args, lib, kmg, torch, synth, dev):
         },
         "stages_ms_per_step": stages,
         "roofline": {
-            "kernel": "band_tiles (FP64 MFMA distance tiles over the norm bands + top-4 lists), one persistent "
-                      "launch for the first direction of all pairs",
+            "kernel": SWEEP_KERNEL % "the first direction of all pairs",
             "bound": "mfma",
             "achieved": round(achieved, 4),
-            "peak": PEAK_FP64_MFMA_TFLOPS,
-            "unit": "TFLOP/s",
-            "frac": round(achieved / PEAK_FP64_MFMA_TFLOPS, 5),
+            "peak": PEAK_I8_MFMA_TOPS,
+            "unit": "TOP/s",
+            "frac": round(achieved / PEAK_I8_MFMA_TOPS, 5),
             "traffic": None,
             "avg_launch_ms": round(topk_s * 1e3, 4),
-            "flops_per_launch": flops,
-            "band_fraction": round(flops / dense, 4),
+            "ops_per_launch": ops,
         },
         "roofline_faster_pfh": {
             "stages": list(PFH_STAGES),
@@ -506,10 +476,9 @@ def run_c3(args, lib, kmg, torch, synth, dev):
         res[prec] = {"ms_per_match": round(1e3 * t / args.steps, 3),
                      "stages_ms": {names[i]: round(ms[i] / args.steps, 4) for i in range(len(names))
                                    if names[i].startswith("match")},
-                     "uncertified_queries": int(m.n_fallback), "correspondences": int(m.pairs.shape[0]),
-                     "identical_to_fp64_form": bool(same), "band_pairs": work}
-    dense = 2.0 * 1e5 * 1e5 * 33  # every query against every row, first direction
-    flops = 2.0 * 33 * res["fp32"]["band_pairs"] if res["fp32"]["band_pairs"] > 0 else dense
+                     "queries_beyond_four_scores": int(m.n_fallback), "correspondences": int(m.pairs.shape[0]),
+                     "identical_to_fp32_form": bool(same), "products": work}
+    ops = float(SWEEP_OPS) * (res["fp32"]["products"] or 1e10)
     tk = res["fp32"]["stages_ms"]["match_topk"] * 1e-3
     out = {
         "metric": "descriptor matchings/s (100k x 100k mutual NN, exact)",
@@ -527,13 +496,12 @@ def run_c3(args, lib, kmg, torch, synth, dev):
         "config": {"workload": "FPFH rows of two submaps, each four ray-cast scans 8 m apart (128 beams x 3,750 "
                                "azimuths; voxel 0.15 m, r_normal 0.45 m, r_FPFH 0.75 m; 20% target outliers), "
                                "exactly 100,000 J rows per side (seeded subset), "
-                               "mutual NN with FP16 / BF16 candidate tiles + FP64 certificate and re-run; value = "
-                               "FP16 form", "generation_s": round(t_gen, 1), "descriptor_stats": stats},
+                               "mutual NN by the exact integer sweep, which every precision argument takes; value = "
+                               "the call with FP16", "generation_s": round(t_gen, 1), "descriptor_stats": stats},
         "precisions": res,
-        "roofline": {"kernel": "band_tiles, FP64 form, first direction", "bound": "mfma",
-                     "achieved": round(flops / tk / 1e12, 3), "peak": PEAK_FP64_MFMA_TFLOPS, "unit": "TFLOP/s",
-                     "frac": round(flops / tk / 1e12 / PEAK_FP64_MFMA_TFLOPS, 4), "traffic": None,
-                     "band_fraction": round(flops / dense, 4)},
+        "roofline": {"kernel": SWEEP_KERNEL % "first direction (time: both phases)", "bound": "mfma",
+                     "achieved": round(ops / tk / 1e12, 3), "peak": PEAK_I8_MFMA_TOPS, "unit": "TOP/s",
+                     "frac": round(ops / tk / 1e12 / PEAK_I8_MFMA_TOPS, 4), "traffic": None},
     }
     print(json.dumps(out), flush=True)
 
@@ -769,7 +737,6 @@ def main():
         batch.run(args.prec)
 
     tuned = tune_for(kmg, batched, lambda: batch_fingerprint(batch), args, graph_inner=20)
-    match_form = int(kmg.get_tuning()["match_form"])
 
     # plain form
     ws = kmg.Workspace(dev)
@@ -792,7 +759,7 @@ def main():
     ms = (C.c_double * nst)()
     ln = (C.c_int64 * nst)()
     lib.kmg_timing_read(ms, ln, nst)
-    band_pairs = stage_work(lib, "match_topk")
+    products = stage_work(lib, "match_topk")
     lib.kmg_timing_enable(0)
     names = [lib.kmg_stage_name(i).decode() for i in range(nst)]
     stages = {names[i]: round(ms[i] / args.steps, 5) for i in range(nst)}
@@ -867,14 +834,10 @@ def main():
         batched_forms["generation_s"] = round(t_gen, 1)
 
     nj_p, nj_q = res.n_j
-    dim = 3 * p.n_bins
     i_topk = names.index("match_topk")
     topk_avg_s = ms[i_topk] / max(1, ln[i_topk]) / 1e3
-    # every query against every row, in the directions the band tile launch covers
-    dense = 2.0 * nj_p * nj_q * dim * (2 if match_form == 1 else 1)
-    # what the band tiles of that launch evaluate (in form 0 the matching back is its own stage)
-    flops_per_launch = 2.0 * dim * band_pairs if band_pairs > 0 else dense
-    achieved = flops_per_launch / topk_avg_s / 1e12 if topk_avg_s > 0 else 0.0
+    ops_per_launch = float(SWEEP_OPS) * products
+    achieved = ops_per_launch / topk_avg_s / 1e12 if topk_avg_s > 0 else 0.0
 
     value = args.steps / t_graph
     out = {
@@ -919,20 +882,15 @@ def main():
         "stages_ms_per_step": stages,
         "tuning": tuned,
         "roofline": {
-            "kernel": ("band_tiles (FP64 MFMA distance tiles over the norm bands + top-4 epilogue), the "
-                       "persistent launch of the first matching direction (smaller set as queries)")
-                      if match_form == 0 else
-                      ("band_tiles (FP64 MFMA distance tiles over the norm bands + top-4 epilogue), the "
-                       "persistent launch of both matching directions in full"),
+            "kernel": SWEEP_KERNEL % "both directions",
             "bound": "mfma",
             "achieved": round(achieved, 4),
-            "peak": PEAK_FP64_MFMA_TFLOPS,
-            "unit": "TFLOP/s",
-            "frac": round(achieved / PEAK_FP64_MFMA_TFLOPS, 5),
-            "traffic": tile_traffic_bytes(tuned["setting"]),
+            "peak": PEAK_I8_MFMA_TOPS,
+            "unit": "TOP/s",
+            "frac": round(achieved / PEAK_I8_MFMA_TOPS, 5),
+            "traffic": None,
             "avg_launch_ms": round(topk_avg_s * 1e3, 5),
-            "flops_per_launch": flops_per_launch,
-            "band_fraction": round(flops_per_launch / dense, 4),
+            "ops_per_launch": ops_per_launch,
         },
         "roofline_faster_pfh": pfh_roofline(stages, int(src.shape[1]) + int(tgt.shape[1]), sum(res.kept),
                                             batch.nnz()),

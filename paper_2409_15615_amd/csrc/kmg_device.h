@@ -54,18 +54,6 @@ constexpr int kXcds = 8;
 struct XcdItems {
     int64_t first, end, stride;
 };
-// Wavefront index of the launch in the XCD-aware order: the waves of XCD x
-// (blocks b with b % 8 == x) take indices [x W / 8, (x + 1) W / 8) of the W
-// waves, in block order.
-__device__ __forceinline__ int64_t xcd_block_index() {
-    const int64_t G = gridDim.x;
-    const int64_t b = blockIdx.x;
-    return (G % kXcds == 0) ? (b % kXcds) * (G / kXcds) + b / kXcds : b;
-}
-__device__ __forceinline__ int64_t xcd_wave_index() {
-    return xcd_block_index() * (blockDim.x / kWave) + threadIdx.x / kWave;
-}
-
 // The plain split: item i to wavefront i mod (wavefronts of the launch).
 __device__ __forceinline__ XcdItems cyclic_items(int64_t n) {
     return XcdItems{static_cast<int64_t>(global_wave()), n, static_cast<int64_t>(wave_count())};

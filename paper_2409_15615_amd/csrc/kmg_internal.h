@@ -237,7 +237,6 @@ constexpr int64_t kOnePassMaxTiles = 512;
 kmg_status scan_exclusive_onepass(const int32_t* in, int32_t* out, int64_t n, int64_t* total, uint64_t* status,
                                   int32_t* err, hipStream_t s, const int32_t* live = nullptr,
                                   int32_t* list = nullptr);
-kmg_status fill_u8(uint8_t* p, uint8_t v, size_t n, hipStream_t s);
 // Up to kMaxFillJobs fills (4- or 8-byte elements) done by one grid-stride pass.
 struct FillJob {
     void* p;

@@ -193,9 +193,10 @@ __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, M
 // rows of nearly one norm, and a query, whose nearest rows differ from it in norm
 // by no more than in distance, skips most chunks.  Needs neither the centre nor
 // the scale and so runs beside the plan: within the rounding it was a chain of its
-// own of 35 us, here it adds 5 us to the plan's 15.  An order over the whole set would save another third of the
-// sweep and take two launches more.  FP32 serves: the norms only bound, with a
-// margin for their rounding, what may be skipped.
+// own of 35 us, here it adds 5 us to the plan's 15.  Tiles of 2,048 rows and more, or
+// one order over the whole set, leave as many products or more (a LiDAR pair 16% in
+// tiles of 1,024, 20% in one order; rooms 30% and 28%).  FP32 serves: the norms only
+// bound, with a margin for their rounding, what may be skipped.
 __device__ void order_rows(const MatchSet* sets, int n_sets, int dim, const SinglePair& single, int first, int step,
                            const MatchWs& w) {
     constexpr int kPerRound = kSortTile / 8;
@@ -787,14 +788,17 @@ constexpr int kStage = 384;  // hits a wavefront gathers in LDS before it hands 
 // list (row, raw score).  Chunks whose norms no query of a 16-query tile can
 // reach are passed over, without their loads where no tile of the group needs
 // them: a scan pair keeps a sixth to a quarter of the products, indoor rooms a
-// quarter to two fifths (18,000 rows both ways: 150 us -> 101 us; two sets of
+// quarter to two fifths (15,000 rows a side: 150 us -> 101 us; two sets of
 // 100,000: 3.5 ms -> 2.0 ms).  A chunk that all four tiles need runs their products
 // interleaved.  What is left is dense in hits: a lane's four scores go to LDS as
 // they are (one write per lane with a hit; sorting the single hits out on the
 // spot was a quarter of the time, 101 us -> 78 us) and are handed out when the
 // stage is full: ranked per query in LDS, with one global atomic per query.
 // Consecutive tiles sweep the same run of chunks for consecutive groups, so the
-// run is read from cache; loads run a chunk ahead.
+// run is read from cache; loads run a chunk ahead.  What bounds it: for rows that the
+// norms cannot prune, the products; for a LiDAR pair the waits (matrix unit 16%,
+// vector unit 24% busy), which loads two chunks ahead, three wavefronts per SIMD or one
+// or three rounds of tiles only made longer (87 us -> 89 to 98).
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sweep_tiles(
     const SetPlan* __restrict__ plan, int n_sets, int dim, const int32_t* __restrict__ list,
     const PairScale* __restrict__ pp, MatchWs w, const MatchCtl* __restrict__ ctl, const DevStatus* __restrict__ st) {

@@ -176,7 +176,6 @@ kmg_status scan_exclusive_onepass(const int32_t* in, int32_t* out, int64_t n, in
     return launch_status();
 }
 
-kmg_status fill_u8(uint8_t* p, uint8_t v, size_t n, hipStream_t s) { return fill<uint8_t>(p, v, n, s); }
 kmg_status fill_u32(uint32_t* p, uint32_t v, size_t n, hipStream_t s) { return fill<uint32_t>(p, v, n, s); }
 kmg_status fill_u64(uint64_t* p, uint64_t v, size_t n, hipStream_t s) { return fill<uint64_t>(p, v, n, s); }
 
