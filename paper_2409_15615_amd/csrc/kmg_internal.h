@@ -23,7 +23,7 @@ constexpr uint64_t kEmptyKey = ~0ull;
 constexpr int kAxisBits = 18;                                // packed keys: 18 bits per axis
 constexpr int64_t kKeyBias = int64_t(1) << (kAxisBits - 1);  // axis keys in [-2^17, 2^17)
 constexpr int kMaxClouds = 1022;                             // 10 bits of cloud id (1023 is reserved)
-constexpr int kListSmall = 1024;                             // LDS neighbour list of the common fill pass
+constexpr int kListSmall = 928;                              // LDS neighbour list of the common fill pass
 constexpr int kMaxDegree = 8192;                             // largest |N(q)| accepted
 constexpr int kMaxBins = 32;                                 // largest H (3H <= 96 descriptor values)
 constexpr int kMaxMatchDim = 64;                             // longest descriptor the matcher takes

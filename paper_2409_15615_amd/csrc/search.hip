@@ -817,9 +817,11 @@ struct FillOut {
 template <int kWaves, bool kFirst>
 kmg_status fill_as(const CloudDev* cl, Grid g, const int32_t* kept_cloud, int64_t m_cap, const FillOut& o,
                    int use_rn, DevStatus* st, hipStream_t s) {
-    // one resident round: the lists in LDS let four wavefronts run per SIMD (a cloud of 215,000
-    // points 190 -> 182 us against two rounds)
-    radius_fill2<kWaves, kFirst><<<std::min(grid_for((m_cap + 1) / 2, kWaves), 16 * kCUs / kWaves), kWaves * kWave, 0,
+    // One resident round, five wavefronts per SIMD: with the tables, lists of 928 entries take
+    // under a fifth of the LDS per four wavefronts (64 pairs 2.07 -> 1.82 ms, a cloud of 215,000
+    // points 184 -> 173 us against lists of 1,024 with four; 832 entries are no faster, and with
+    // 960 the fifth block no longer fits, so that the grid takes two rounds: 2.92 ms).
+    radius_fill2<kWaves, kFirst><<<std::min(grid_for((m_cap + 1) / 2, kWaves), 20 * kCUs / kWaves), kWaves * kWave, 0,
                                    s>>>(
         cl, g, kept_cloud, m_cap, o.off, o.nbr, o.nbr_cap, o.deg, o.long_q, use_rn, st);
     return launch_status();
