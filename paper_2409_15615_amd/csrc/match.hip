@@ -997,7 +997,7 @@ struct Nearest {
 template <int W>
 __device__ __forceinline__ Nearest score_query(const MatchSet& qs, const MatchSet& ps, const SetPlan& qc,
                                                const SetPlan& pc, int dim, double scale, const MatchWs& w, int64_t slot,
-                                               int m, int cap, int gl) {
+                                               int m, int cap, int gl, int* rows) {
     const uint2* src = w.pool + slot * cap;
     const int own = w.half[slot] + 1;
     const double e = static_cast<double>(w.err[slot]);
@@ -1036,17 +1036,36 @@ __device__ __forceinline__ Nearest score_query(const MatchSet& qs, const MatchSe
             o.b2 = d;
         }
     };
+    // What the bound leaves is gathered first, so that the lanes score it side by side: a
+    // lane's own four entries would run one after another (16 LiDAR pairs 253 -> 221 us, 64
+    // pairs 655 -> 600, 13,000 x 15,400 rows 23.6 -> 18.3; a single LiDAR pair the same).
+    const int lane0 = static_cast<int>(threadIdx.x) % kWave - gl;
+    const uint64_t below = (uint64_t{1} << gl) - 1;
+    const auto score_left = [&]() {
+        int n = 0;
 #pragma unroll
-    for (int u = 0; u < kRegList; ++u)
-        if (static_cast<int>(ent[u].y) >= least) {
-            ++o.scored;
-            take(perm[ent[u].x]);
+        for (int u = 0; u < kRegList; ++u) {
+            const bool left = static_cast<int>(ent[u].y) >= least;
+            const uint64_t who = __ballot(left) >> lane0 & (~uint64_t{0} >> (kWave - W));
+            if (left) rows[n + __popcll(who & below)] = perm[ent[u].x];
+            n += __popcll(who);
         }
-    for (int k = kRegList * W + gl; k < m; k += W) {
-        const uint2 en = src[k];
-        if (static_cast<int>(en.y) < least) continue;
-        ++o.scored;
-        take(perm[en.x]);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (int k = gl; k < n; k += W) {
+            ++o.scored;
+            take(rows[k]);
+        }
+        __builtin_amdgcn_wave_barrier();
+    };
+    score_left();
+    for (int k0 = kRegList * W; k0 < m; k0 += kRegList * W) {
+#pragma unroll
+        for (int u = 0; u < kRegList; ++u) {
+            const int k = k0 + u * W + gl;
+            ent[u] = k < m ? src[k] : make_uint2(0u, static_cast<uint32_t>(kNoRow));
+        }
+        score_left();
     }
     const auto merge = [&]() {
 #pragma unroll
@@ -1091,6 +1110,7 @@ __global__ __launch_bounds__(kBlock, 7) void score_lists(const MatchSet* __restr
     constexpr int kPerBlock = kBlock / kScoreLanes;
     constexpr int kParts = kGroup / kPerBlock;
     __shared__ int s_more;
+    __shared__ int s_rows[kPerBlock][kScoreLanes * kRegList];
     if (st->err_capacity) return;
     const int total = ctl->groups * kParts;
     const int cap = ctl->cap;
@@ -1151,13 +1171,16 @@ __device__ __forceinline__ int exact_segs(int64_t F, int64_t groups, int64_t par
 // from cache; the form for more shares each row among 64 queries:
 // exact FP64 scans for the listed queries: plan[c].n_open entries of set c from
 // fb_list[plan[c].base] on, in groups that never span two sets.  A work item is
-// (group of up to 64 entries, row segment): lane L of every wave holds entry L
-// in registers as FP64, padded with zeros to 4 KS values, the partner rows of
-// the segment stream through LDS as FP64 with the same zero padding (a padded
-// term adds an exact zero), and each wave scores every fourth row, ascending,
-// two rows at a time, with the plain FP64 sum in dimension order.  The four
-// waves merge their (best, index, second) and write them as the segment's
-// partial result.  The block that finishes a group's last segment (counted in
+// (group of up to 64 entries, row segment): the lanes of every wave hold the
+// entries in registers as FP64, padded with zeros to 4 KS values, the partner rows
+// of the segment stream through LDS as FP64 with the same zero padding (a padded
+// term adds an exact zero), and each wave scores its share of the rows, ascending,
+// two at a time, with the plain FP64 sum in dimension order.  FP64 issue bounds it,
+// so a group of up to 8, 16 or 32 entries gives each one 8, 4 or 2 lanes, with
+// rows of their own: a batch's sets have about seven such entries each, and a lane
+// an entry left nine tenths of the wavefront idle (64 pairs 1,020 -> 761 us, 16
+// pairs 244 -> 213, 100,000 rows 273 -> 244).  The lanes and waves of an entry merge
+// their (best, index, second) and write them as the segment's partial result.  The block that finishes a group's last segment (counted in
 // grp_done, which comes in cleared) merges the group's partials in segment
 // order into nn, best and second, and resets the count.
 template <int KS>
@@ -1182,7 +1205,8 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
         const int64_t slot = w.long_list[k];
         const int c = find_set(n_sets, slot, [&](int s) { return static_cast<int64_t>(plan[s].base); });
         const Nearest o = score_query<kWave>(sets[c], sets[c ^ 1], plan[c], plan[c ^ 1], dim, pp[c >> 1].scale, w, slot,
-                                             w.cnt[slot], ctl->cap, L);
+                                             w.cnt[slot], ctl->cap, L,
+                                             reinterpret_cast<int*>(s_x) + wv * kWave * kRegList);
         if (L == 0) {
             const int64_t at = plan[c].base + w.perm[slot];
             w.nn[at] = o.j1 == INT_MAX ? -1 : o.j1;
