@@ -1138,7 +1138,8 @@ __global__ __launch_bounds__(kBlock, 7) void score_lists(const MatchSet* __restr
                 if (gl == 0) w.long_list[atomicAdd(&ctl->n_long, 1)] = slot;
             } else {
                 const Nearest o = score_query<kScoreLanes>(sets[c], sets[c ^ 1], qc, pc, dim, pp[c >> 1].scale, w, slot,
-                                                           found, cap, gl);
+                                                           found, cap, gl,
+                                                           s_rows[threadIdx.x / kScoreLanes]);
                 if (gl == 0) {
                     const int64_t at = qc.base + w.perm[slot];
                     w.nn[at] = o.j1 == INT_MAX ? -1 : o.j1;
@@ -1282,6 +1283,7 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
         }
         return;
     }
+    __syncthreads();  // s_x held the long lists' rows
     for (int i = threadIdx.x; i < kXRows * (kD - dim); i += kBlock)  // the padding, zero for good
         s_x[(i / (kD - dim)) * kD + dim + i % (kD - dim)] = 0.0;
     if (wv == 0) {  // lane L sums sets [kPer L, kPer (L + 1)), then the wave scans the sums
@@ -1324,8 +1326,12 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
             else hi = mid - 1;
         }
         const int c = lo, p = lo ^ 1;
-        // lane L: the group's entry L (dense index e into the partials) and its slot
-        const int local = static_cast<int>(g - s_gpre[c]) * kWave + L;
+        // a lane's entry of the group (dense index e into the partials), its slot and its row of R
+        const int first = static_cast<int>(g - s_gpre[c]) * kWave;
+        const int n_here = s_pre[c + 1] - s_pre[c] - first;  // at least 1
+        const int Q = n_here > 32 ? 64 : n_here > 16 ? 32 : n_here > 8 ? 16 : 8;
+        const int R = kWave / Q, sub = L / Q;
+        const int local = first + (L & (Q - 1));
         const bool have = local < s_pre[c + 1] - s_pre[c];
         const int64_t e = s_pre[c] + local;
         const int64_t slot = have ? w.fb_list[plan[c].base + local] : plan[c].base;
@@ -1377,10 +1383,10 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
                             b2 = acc;
                         }
                     };
-                    for (int r = wv; r < nr; r += 2 * kWaves) {
-                        const bool two = r + kWaves < nr;  // wave-uniform
-                        const double2* xa = reinterpret_cast<const double2*>(s_x + r * kD);
-                        const double2* xb = reinterpret_cast<const double2*>(s_x + (two ? r + kWaves : r) * kD);
+                    for (int rw = wv * R; rw < nr; rw += 2 * kWaves * R) {  // wave-uniform
+                        const int ra = rw + sub, rb = ra + kWaves * R;
+                        const double2* xa = reinterpret_cast<const double2*>(s_x + min(ra, nr - 1) * kD);
+                        const double2* xb = reinterpret_cast<const double2*>(s_x + min(rb, nr - 1) * kD);
                         double a = 0.0, b = 0.0;
 #pragma unroll
                         for (int t = 0; t < kD / 2; ++t) {
@@ -1392,17 +1398,27 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
                             a = a + da1 * da1;
                             b = b + db1 * db1;
                         }
-                        take(a, r0 + r);
-                        if (two) take(b, r0 + r + kWaves);
+                        if (ra < nr) take(a, r0 + ra);
+                        if (rb < nr) take(b, r0 + rb);
                     }
                 }
             }
         }
+        // the lanes of one entry, then the waves
+        const auto merge_rows = [&]() {
+#pragma unroll 1
+            for (int d = Q; d < kWave; d <<= 1) {
+                const double o1 = __shfl_xor(b1, d, kWave), o2 = __shfl_xor(b2, d, kWave);
+                const int oj = __shfl_xor(j1, d, kWave);
+                combine_best(b1, j1, b2, o1, oj, o2);
+            }
+        };
+        merge_rows();
         s_b1[threadIdx.x] = b1;
         s_b2[threadIdx.x] = b2;
         s_j1[threadIdx.x] = j1;
         __syncthreads();
-        if (wv == 0 && have) {
+        if (wv == 0 && have && sub == 0) {
             for (int o = 1; o < kWaves; ++o)
                 combine_best(b1, j1, b2, s_b1[o * kWave + L], s_j1[o * kWave + L], s_b2[o * kWave + L]);
             pb1[sg * F + e] = b1;
@@ -1415,27 +1431,28 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
             if (L == 0) s_last = atomicAdd(&w.grp_done[g], 1) == S - 1;
         }
         __syncthreads();
-        if (s_last) {  // uniform: the group's last segment; the partials by all waves, a quarter each
+        if (s_last) {  // uniform: the group's last segment; the partials dealt to the entry's lanes of all waves
             __threadfence();  // the other segments' partials are visible from here on
             b1 = b2 = INFINITY;
             j1 = INT_MAX;
             if (have) {
                 // sixteen segments' loads in flight: the partials come from beyond the L2
-                for (int k0 = wv; k0 < S; k0 += 16 * kWaves) {
+                for (int k0 = wv * R + sub; k0 < S; k0 += 16 * kWaves * R) {
                     double o1[16], o2[16];
                     int oj[16];
 #pragma unroll
                     for (int u = 0; u < 16; ++u) {
-                        const int64_t at = static_cast<int64_t>(min(k0 + u * kWaves, S - 1)) * F + e;
+                        const int64_t at = static_cast<int64_t>(min(k0 + u * kWaves * R, S - 1)) * F + e;
                         o1[u] = pb1[at];
                         o2[u] = pb2[at];
                         oj[u] = pj1[at];
                     }
 #pragma unroll
                     for (int u = 0; u < 16; ++u)
-                        if (k0 + u * kWaves < S) combine_best(b1, j1, b2, o1[u], oj[u], o2[u]);
+                        if (k0 + u * kWaves * R < S) combine_best(b1, j1, b2, o1[u], oj[u], o2[u]);
                 }
             }
+            merge_rows();
             s_b1[threadIdx.x] = b1;
             s_b2[threadIdx.x] = b2;
             s_j1[threadIdx.x] = j1;
@@ -1443,7 +1460,7 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
             if (wv == 0) {
                 for (int o = 1; o < kWaves; ++o)
                     combine_best(b1, j1, b2, s_b1[o * kWave + L], s_j1[o * kWave + L], s_b2[o * kWave + L]);
-                if (have) {
+                if (have && sub == 0) {
                     const int64_t at = plan[c].base + w.perm[slot];
                     w.nn[at] = (j1 == INT_MAX) ? -1 : j1;
                     w.best[at] = b1;
