@@ -1076,10 +1076,11 @@ __device__ __forceinline__ Nearest score_query(const MatchSet& qs, const MatchSe
         }
     };
     merge();
-    // the partner's rows out of range: farther from the centre than kRange, so farther
-    // from the query than kRange less its own distance from the centre
+    // the partner's rows out of range: as integers farther from the centre than kRange, and
+    // rounding may have lengthened them by as much as it moves any row, so farther from the
+    // query than kRange less that much, less the query's own distance from the centre
     if (pc.n_out > 0) {
-        const double far = kRange - (sqrt(-2.0 * static_cast<double>(own) + 2.0) + e);
+        const double far = kRange - most_err(dim) - (sqrt(-2.0 * static_cast<double>(own) + 2.0) + e);
         const double gap = far * (1.0 - 1e-6) * scale;
         if (!(gap > 0.0 && o.b2 < gap * gap)) {
             if (gl != 0) {  // the merged triple stays on the first lane only
