@@ -152,14 +152,30 @@ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; 
 // as much as a full one; and not a single round, since a run of chunks dense
 // in hits costs several times another and one wavefront then ends long after
 // the rest.
-__device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, MatchCtl* ctl, int* s_scan) {
+// Tiles are numbered in 32 bits, a stride of the grid past the last included: sets
+// for which even the deepest tiles are more (two of 12 million rows, both directions
+// in full) set err_capacity, so that nothing is matched.
+constexpr int64_t kMostTiles = INT32_MAX - static_cast<int64_t>(kTileWaves);
+__device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, MatchCtl* ctl, DevStatus* st,
+                             int* s_scan, int64_t* s_sum) {
     const int groups = (live && n_p > 0) ? ceil_div(nq, kGroup) : 0;
     const int chunks = ceil_div(n_p, kTileRows);
-    int all[2] = {groups, static_cast<int>(min(static_cast<int64_t>(groups) * chunks, static_cast<int64_t>(1) << 40) >> 10)};
-    int tot_all[2];
-    block_scan_k<2>(all, tot_all, s_scan);
+    const int64_t most = block_sum64(static_cast<int64_t>(groups) * ceil_div(chunks, kMaxDepth), s_sum);
+    if (most > kMostTiles) {  // uniform
+        if (live) plan[c].groups = plan[c].nq = plan[c].grp_off = plan[c].s_tile_off = plan[c].tile_off = 0;
+        if (c == 0) {
+            ctl->groups = ctl->s_tiles = ctl->tiles = 0;
+            ctl->depth = ctl->s_segs = 1;
+            st->err_capacity = 1;
+        }
+        return;
+    }
+    const int64_t work = block_sum64(static_cast<int64_t>(groups) * chunks, s_sum);
+    int all[1] = {groups}, tot_all[1];
+    block_scan_k<1>(all, tot_all, s_scan);
     const int all_groups = tot_all[0];
-    int depth = min(max(tot_all[1] / (kRounds * kTileWaves >> 10), kMinDepth), kMaxDepth);
+    int depth = static_cast<int>(min(max(work / (kRounds * kTileWaves), static_cast<int64_t>(kMinDepth)),
+                                     static_cast<int64_t>(kMaxDepth)));
     for (int it = 0; it < 4 && depth < kMaxDepth; ++it) {  // uniform
         int v[1] = {groups * ceil_div(chunks, depth)}, tot[1];
         block_scan_k<1>(v, tot, s_scan);
@@ -384,7 +400,7 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
     const bool rows_only = one_sided && ((c & 1) ? n >= n_p : n > n_p);
     const int nq = (!paired || rows_only) ? 0 : n;
     __syncthreads();
-    plan_queries(c, live, nq, n_p, plan, ctl, s_scan);
+    plan_queries(c, live, nq, n_p, plan, ctl, st, s_scan, s_sum);
     const int64_t work = block_sum64(static_cast<int64_t>(nq) * n_p, s_sum);
     if (c == 0) {
         st->match_products = work;
@@ -401,14 +417,16 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
 }
 
 // The plan of the matching back (the image rows of every set as queries).
-__global__ __launch_bounds__(kPlanThreads) void match_plan_back(int n_sets, SetPlan* plan, MatchCtl* ctl) {
+__global__ __launch_bounds__(kPlanThreads) void match_plan_back(int n_sets, SetPlan* plan, MatchCtl* ctl,
+                                                                DevStatus* st) {
     __shared__ int s_scan[3 * (kPlanThreads / kWave)];
+    __shared__ int64_t s_sum[kPlanThreads / kWave];
     const int c = threadIdx.x;
     const bool live = c < n_sets && (c ^ 1) < n_sets;
     const int n_p = live ? plan[c ^ 1].n : 0;
     const int nq = live ? plan[c].n_img : 0;
     if (live) plan[c].n_open = 0;
-    plan_queries(c, live, nq, n_p, plan, ctl, s_scan);
+    plan_queries(c, live, nq, n_p, plan, ctl, st, s_scan, s_sum);
     if (c == 0) ctl->open = ctl->n_long = 0;
 }
 
@@ -1695,7 +1713,7 @@ kmg_status match_sets(MatchSet* sets, int n_sets, int dim, int64_t products, con
         StageScope sc(ST_MATCH_IMAGE, s);
         image_lists<<<grid_cap(w.slot_cap, kBlock), kBlock, 0, s>>>(w.plan, n_sets, w, w.ctl, st);
         KMG_TRY(launch_status());
-        match_plan_back<<<1, kPlanThreads, 0, s>>>(n_sets, w.plan, w.ctl);
+        match_plan_back<<<1, kPlanThreads, 0, s>>>(n_sets, w.plan, w.ctl, st);
         KMG_TRY(launch_status());
         KMG_TRY(match_queries(sets, n_sets, dim, w.img_list, st, w, s));
     }
