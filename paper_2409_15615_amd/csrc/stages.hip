@@ -71,7 +71,8 @@ kmg_status read_status(DevStatus* st, DevStatus* host, hipStream_t s) {
 
 // The fill after a count pass.  The lists go first, behind the report of the
 // count: while the host reads it the GPU already fills (nothing, when the lists
-// exceed the capacity, their offsets or the supported range).
+// exceed the capacity, their offsets or the supported range).  A call that is refused
+// waits for that launch, which reads the workspace: the caller may use or free it next.
 kmg_status fill_counted(const CloudDev* cl, const float* xyz, int64_t m, int64_t nbr_cap, DevStatus* st,
                         const SearchWs& w, const int32_t* off, int32_t* nbr, float* nrm, uint8_t* flags,
                         int32_t* n_normal, hipStream_t s, int use_rn, bool with_normals, int64_t* nnz_host,
@@ -84,10 +85,19 @@ kmg_status fill_counted(const CloudDev* cl, const float* xyz, int64_t m, int64_t
                               use_rn));
     KMG_TRY(r.wait(&h));
     timer_collect();
-    if (h.err_sync) return KMG_ERR_DEVICE;
-    if (h.err_range || (h.dense & 2) || h.nnz > INT32_MAX) return KMG_ERR_RANGE;
-    if (nnz_host) *nnz_host = h.nnz;
-    if (h.nnz > nbr_cap) return over_capacity;
+    kmg_status refused = KMG_OK;
+    if (h.err_sync) {
+        refused = KMG_ERR_DEVICE;
+    } else if (h.err_range || (h.dense & 2) || h.nnz > INT32_MAX) {
+        refused = KMG_ERR_RANGE;
+    } else {
+        if (nnz_host) *nnz_host = h.nnz;
+        if (h.nnz > nbr_cap) refused = over_capacity;
+    }
+    if (refused != KMG_OK) {
+        KMG_TRY_HIP(hipStreamSynchronize(s));
+        return refused;
+    }
     return search_fill_batch(cl, xyz, m, nullptr, m, cap,
                              ((h.dense & 1) ? kFillDense : 0) | (with_normals ? kFillNormals : 0), st, w, off, nbr, nrm,
                              m, flags, n_normal, s, use_rn);
