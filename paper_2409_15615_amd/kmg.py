@@ -422,7 +422,10 @@ def corr_graph(src_xyz, tgt_xyz, pairs, d1, d2, n_tau=3000, beta=0.45, ws=None):
         _raise("kmg_corr_graph", st)
         break
     n = n_sel.value
-    return GraphOut(sel[:n], off[:n + 1], adj[:nnz.value])
+    adj = adj[:nnz.value]
+    if cap > max(m * 64, 2 * nnz.value):  # the graph must not hold on to a guess far beyond it
+        adj = adj.clone()
+    return GraphOut(sel[:n], off[:n + 1], adj)
 
 
 @dataclass
