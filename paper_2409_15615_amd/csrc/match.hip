@@ -61,6 +61,7 @@ constexpr int kMaxDepth = 128;     // and at most
 constexpr int kMaxSampleSegs = 8;
 constexpr int kCentreRows = 256;   // rows sampled for a pair's centre and scale
 constexpr double kRangeRms = 4.0;
+constexpr float kOrdinary = 16.0f;
 constexpr double kRange = 32600.0;  // largest norm of an integer row
 constexpr int kLimb = 32639;        // largest |q|: 127 * 256 + 127
 constexpr int kMinCap = 16;         // listed rows per query the pool always holds
@@ -132,14 +133,22 @@ __device__ __forceinline__ void block_scan_k(int* v, int* tot, int* smem /* K x 
     __syncthreads();
 }
 
-__device__ __forceinline__ int64_t block_sum64(int64_t v, int64_t* smem) {
-    v = wave_sum(v);
-    if (lane_id() == 0) smem[threadIdx.x / kWave] = v;
+// Block-wide sums of K int64 values per thread in one pass.
+template <int K>
+__device__ __forceinline__ void block_sum64(int64_t* v, int64_t* smem /* K x waves */) {
+    constexpr int kWaves = kPlanThreads / kWave;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        v[k] = wave_sum(v[k]);
+        if (lane_id() == 0) smem[k * kWaves + threadIdx.x / kWave] = v[k];
+    }
     __syncthreads();
-    int64_t t = 0;
-    for (int w = 0; w < kPlanThreads / kWave; ++w) t += smem[w];
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        v[k] = 0;
+        for (int w = 0; w < kWaves; ++w) v[k] += smem[k * kWaves + w];
+    }
     __syncthreads();
-    return t;
 }
 
 __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; }
@@ -160,8 +169,10 @@ __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, M
                              int* s_scan, int64_t* s_sum) {
     const int groups = (live && n_p > 0) ? ceil_div(nq, kGroup) : 0;
     const int chunks = ceil_div(n_p, kTileRows);
-    const int64_t most = block_sum64(static_cast<int64_t>(groups) * ceil_div(chunks, kMaxDepth), s_sum);
-    if (most > kMostTiles) {  // uniform
+    int64_t all[3] = {groups, static_cast<int64_t>(groups) * chunks,
+                      static_cast<int64_t>(groups) * ceil_div(chunks, kMaxDepth)};
+    block_sum64<3>(all, s_sum);
+    if (all[2] > kMostTiles) {  // uniform
         if (live) plan[c].groups = plan[c].nq = plan[c].grp_off = plan[c].s_tile_off = plan[c].tile_off = 0;
         if (c == 0) {
             ctl->groups = ctl->s_tiles = ctl->tiles = 0;
@@ -170,11 +181,8 @@ __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, M
         }
         return;
     }
-    const int64_t work = block_sum64(static_cast<int64_t>(groups) * chunks, s_sum);
-    int all[1] = {groups}, tot_all[1];
-    block_scan_k<1>(all, tot_all, s_scan);
-    const int all_groups = tot_all[0];
-    int depth = static_cast<int>(min(max(work / (kRounds * kTileWaves), static_cast<int64_t>(kMinDepth)),
+    const int all_groups = static_cast<int>(all[0]);
+    int depth = static_cast<int>(min(max(all[1] / (kRounds * kTileWaves), static_cast<int64_t>(kMinDepth)),
                                      static_cast<int64_t>(kMaxDepth)));
     for (int it = 0; it < 4 && depth < kMaxDepth; ++it) {  // uniform
         int v[1] = {groups * ceil_div(chunks, depth)}, tot[1];
@@ -298,7 +306,12 @@ __device__ void order_rows(const MatchSet* sets, int n_sets, int dim, const Sing
 //
 // Centre: the mean of kCentreRows rows at even strides over both sets, in a
 // fixed order (any centre is valid, every bound is stated for the rows as
-// rounded); scale: kRangeRms root mean square norms about it span kRange.
+// rounded); scale: kRangeRms root mean square norms about it span kRange.  Rows
+// with norms beyond kOrdinary times the median of the largest of each four (about
+// the 84% quantile) have no part in either: a single one of a million times the
+// norm among them otherwise put all others within a few units, their lists
+// overflowed and both sets were scanned exactly (13,015 x 15,401 rows: 261 us
+// without such a row, 3,041 with it, now 252).
 __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n_sets, int dim, int one_sided,
                                                            int64_t pool, SetPlan* plan, MatchCtl* ctl, PairScale* pp,
                                                            SinglePair single, MatchWs w, DevStatus* st) {
@@ -312,7 +325,11 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
     if (blockIdx.x > 0) {
         constexpr int kGroups = kPlanThreads / kMaxMatchDim;  // 16 row groups of 64 dimensions
         constexpr int kPer = kCentreRows / kGroups;
+        static_assert(kMaxMatchDim == kWave, "a row per wavefront");
         __shared__ double s_part[kPlanThreads];
+        __shared__ float s_norm[kCentreRows / 4];
+        static_assert(kCentreRows / 4 == kWave, "a lane per four rows");
+        __shared__ int s_rows[kGroups];
         const int pair = static_cast<int>(blockIdx.x) - 1;
         const MatchSet a = by_value ? single.a : sets[2 * pair];
         const MatchSet b = by_value ? single.b : sets[2 * pair + 1];
@@ -321,38 +338,80 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
         const int ns = static_cast<int>(nt < kCentreRows ? nt : kCentreRows);
         const int d = threadIdx.x % kMaxMatchDim, g = threadIdx.x / kMaxMatchDim;
         double x[kPer];
-        double sum = 0.0;
+        float n2[kPer];
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const int k = g + u * kGroups;
             x[u] = 0.0;
             if (d < dim && k < ns) {
-                const int r = static_cast<int>(static_cast<int64_t>(k) * nt / ns);
+                // k nt / ns, without the division
+                const int r = ns < kCentreRows ? k : static_cast<int>(static_cast<int64_t>(k) * nt / kCentreRows);
                 x[u] = r < na ? set_row(a, r, dim)[d] : set_row(b, r - na, dim)[d];
             }
-            sum += x[u];
+            n2[u] = static_cast<float>(x[u]) * static_cast<float>(x[u]);
         }
+        // a wavefront holds its rows whole: their norms (not a number: the largest of all).  The
+        // lanes halve the rows that they go on with at each step, lane d ending with row d / 4.
+        static_assert(kPer == 16 && kGroups == 16, "four steps, and 16 wavefronts");
+#pragma unroll
+        for (int l = 32, n = kPer / 2; n > 0; l >>= 1, n >>= 1) {
+#pragma unroll
+            for (int u = 0; u < n; ++u) {
+                const float give = d & l ? n2[u] : n2[u + n];
+                n2[u] = (d & l ? n2[u + n] : n2[u]) + __shfl_xor(give, l, kWave);
+            }
+        }
+        n2[0] += __shfl_xor(n2[0], 2, kWave);
+        n2[0] += __shfl_xor(n2[0], 1, kWave);
+        const bool row = g + d / 4 * kGroups < ns;
+        const float norm = n2[0] >= 0.0f ? sqrtf(n2[0]) : INFINITY;
+        float most = row ? norm : 0.0f;
+#pragma unroll
+        for (int l = 4; l < 16; l <<= 1) most = fmaxf(most, __shfl_xor(most, l, kWave));
+        if (d % 16 == 0) s_norm[4 * g + d / 16] = row ? most : INFINITY;  // four rows' largest; the first is there if any is
+        __syncthreads();
+        {
+            // their median, to the twelve leading bits (rounded up); counting who lies below whom took 3 us
+            constexpr int kBits = 12;
+            const uint32_t key = __float_as_uint(s_norm[d]) >> (31 - kBits);
+            const int fours = __popcll(ballot(d / 4 + 4 * kGroups * (d % 4) < ns));
+            uint32_t at = 0;
+#pragma unroll
+            for (int k = kBits - 1; k >= 0; --k)
+                if (__popcll(ballot(key < (at | 1u << k))) <= max(fours - 1, 0) / 2) at |= 1u << k;
+            constexpr uint32_t kInf = 0x7f800000u;
+            most = kOrdinary * __uint_as_float(min((at + 1) << (31 - kBits), kInf));
+        }
+        const uint64_t use = ballot(row && norm <= most);  // bit 4 u: row u counts
+        if (d == 0) s_rows[g] = __popcll(use) / 4;
+        double sum = 0.0;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u)
+            if (use >> (4 * u) & 1) sum += x[u];
         s_part[threadIdx.x] = sum;
         __syncthreads();
+        int rows = 0;
         double mu = 0.0;
-        for (int q = 0; q < kGroups; ++q) mu += s_part[q * kMaxMatchDim + d];
-        mu = ns > 0 ? mu / ns : 0.0;
+        for (int q = 0; q < kGroups; ++q) {
+            rows += s_rows[q];
+            mu += s_part[q * kMaxMatchDim + d];
+        }
+        mu = rows > 0 ? mu / rows : 0.0;
         __syncthreads();
         double sq = 0.0;
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const double v = x[u] - mu;
-            if (d < dim && g + u * kGroups < ns) sq += v * v;
+            if (d < dim && (use >> (4 * u) & 1)) sq += v * v;
         }
-        s_part[threadIdx.x] = sq;
+        sq = wave_sum(sq);
+        if (d == 0) s_part[g] = sq;
         __syncthreads();
-        for (int w = kPlanThreads / 2; w > 0; w >>= 1) {
-            if (static_cast<int>(threadIdx.x) < w) s_part[threadIdx.x] += s_part[threadIdx.x + w];
-            __syncthreads();
-        }
         if (g == 0) pp[pair].mu[d] = d < dim ? mu : 0.0;
         if (threadIdx.x == 0) {
-            const double rms = ns > 0 ? sqrt(s_part[0] / ns) : 0.0;
+            double all = 0.0;
+            for (int q = 0; q < kGroups; ++q) all += s_part[q];
+            const double rms = rows > 0 ? sqrt(all / rows) : 0.0;
             double s = rms * (kRangeRms / kRange);
             if (!(s > 1e-30) || !(s < 1e30)) s = 1.0;  // equal rows, or nothing that can be scaled
             pp[pair].scale = s;
@@ -361,7 +420,7 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
         return;
     }
     __shared__ int s_scan[3 * (kPlanThreads / kWave)];
-    __shared__ int64_t s_sum[kPlanThreads / kWave];
+    __shared__ int64_t s_sum[3 * (kPlanThreads / kWave)];
     const int c = threadIdx.x;
     if (by_value) {
         for (int k = c; k < static_cast<int>(sizeof(DevStatus) / 4); k += kPlanThreads)
@@ -401,9 +460,10 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
     const int nq = (!paired || rows_only) ? 0 : n;
     __syncthreads();
     plan_queries(c, live, nq, n_p, plan, ctl, st, s_scan, s_sum);
-    const int64_t work = block_sum64(static_cast<int64_t>(nq) * n_p, s_sum);
+    int64_t work[1] = {static_cast<int64_t>(nq) * n_p};
+    block_sum64<1>(work, s_sum);
     if (c == 0) {
-        st->match_products = work;
+        st->match_products = work[0];
         ctl->slots = tot[0] * kTileRows;
         ctl->emit_tiles = tot[1];
         // whole 128-byte lines, an odd number of them: with lists a power of two apart the first
@@ -420,7 +480,7 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
 __global__ __launch_bounds__(kPlanThreads) void match_plan_back(int n_sets, SetPlan* plan, MatchCtl* ctl,
                                                                 DevStatus* st) {
     __shared__ int s_scan[3 * (kPlanThreads / kWave)];
-    __shared__ int64_t s_sum[kPlanThreads / kWave];
+    __shared__ int64_t s_sum[3 * (kPlanThreads / kWave)];
     const int c = threadIdx.x;
     const bool live = c < n_sets && (c ^ 1) < n_sets;
     const int n_p = live ? plan[c ^ 1].n : 0;
