@@ -91,13 +91,13 @@ struct SetPlan {
     int32_t n_out;       // rows out of the integer range
     int32_t n_open;      // queries of the phase listed for the exact scan
     int32_t n_img;       // one-sided form: rows listed for the matching back
-    int32_t pad[2];
+    int32_t s_segs;      // segments of the sample per group
+    int32_t pad;
 };
 
 // Counts of the matching's passes, on the device.
 struct MatchCtl {
     int32_t slots, groups, s_tiles, tiles;
-    int32_t s_segs;      // sample segments per group (partials per query)
     int32_t depth;       // chunks per tile of the sweep
     int32_t cap;         // listed rows per query
     int32_t open;        // queries listed for the exact scan
@@ -448,7 +448,7 @@ struct MatchWs {
     float2* c_norm;        // per chunk: least and largest norm
     int32_t* perm;         // per slot: the row (a set's slots are in norm order within 1,024-row tiles)
     int32_t* inv;          // per row: its place in the set's slots
-    int2* s_best;          // best and second raw score of every query over a sample segment
+    int2* s_best;          // per tile of the sample: best and second raw score of its queries
     float* err;            // per slot: rounding error in units of the scale (< 0: not in the sweep)
     int32_t* cnt;          // per slot: listed rows
     uint2* pool;           // the lists: ctl->cap entries (row, raw score) per slot

@@ -58,7 +58,8 @@ constexpr int kTileWaves = kTileBlocks * kWavesPerBlock;
 constexpr int kRounds = 2;         // tiles per resident wavefront of the sweep
 constexpr int kMinDepth = 4;       // chunks per tile, at least
 constexpr int kMaxDepth = 128;     // and at most
-constexpr int kMaxSampleSegs = 8;
+constexpr int kMaxSampleSegs = 32;
+constexpr int kPartRounds = 8;     // partials of the sample in flight per query
 constexpr int kCentreRows = 256;   // rows sampled for a pair's centre and scale
 constexpr double kRangeRms = 4.0;
 constexpr float kOrdinary = 16.0f;
@@ -144,9 +145,11 @@ __device__ __forceinline__ void block_sum64(int64_t* v, int64_t* smem /* K x wav
     }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < K; ++k) {
-        v[k] = 0;
-        for (int w = 0; w < kWaves; ++w) v[k] += smem[k * kWaves + w];
+    for (int k = 0; k < K; ++k) v[k] = 0;
+#pragma unroll 4
+    for (int w = 0; w < kWaves; ++w) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] += smem[k * kWaves + w];
     }
     __syncthreads();
 }
@@ -161,6 +164,11 @@ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; 
 // as much as a full one; and not a single round, since a run of chunks dense
 // in hits costs several times another and one wavefront then ends long after
 // the rest.
+// The sample of a set is split in segments of whole sort tiles, in proportion to its
+// partner's tiles and about one per resident wavefront over all sets, so that a few
+// queries against many rows are dealt out too: with one number of segments for all
+// groups, 100,000 rows were left to eight wavefronts beside 200 queries (the call
+// 595 us, now 208).
 // Tiles are numbered in 32 bits, a stride of the grid past the last included: sets
 // for which even the deepest tiles are more (two of 12 million rows, both directions
 // in full) set err_capacity, so that nothing is matched.
@@ -169,20 +177,20 @@ __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, M
                              int* s_scan, int64_t* s_sum) {
     const int groups = (live && n_p > 0) ? ceil_div(nq, kGroup) : 0;
     const int chunks = ceil_div(n_p, kTileRows);
-    int64_t all[3] = {groups, static_cast<int64_t>(groups) * chunks,
+    const int s_tiles = max(ceil_div(chunks, kTileChunks), 1);
+    int64_t all[3] = {static_cast<int64_t>(groups) * chunks, static_cast<int64_t>(groups) * s_tiles,
                       static_cast<int64_t>(groups) * ceil_div(chunks, kMaxDepth)};
     block_sum64<3>(all, s_sum);
     if (all[2] > kMostTiles) {  // uniform
         if (live) plan[c].groups = plan[c].nq = plan[c].grp_off = plan[c].s_tile_off = plan[c].tile_off = 0;
         if (c == 0) {
             ctl->groups = ctl->s_tiles = ctl->tiles = 0;
-            ctl->depth = ctl->s_segs = 1;
+            ctl->depth = 1;
             st->err_capacity = 1;
         }
         return;
     }
-    const int all_groups = static_cast<int>(all[0]);
-    int depth = static_cast<int>(min(max(all[1] / (kRounds * kTileWaves), static_cast<int64_t>(kMinDepth)),
+    int depth = static_cast<int>(min(max(all[0] / (kRounds * kTileWaves), static_cast<int64_t>(kMinDepth)),
                                      static_cast<int64_t>(kMaxDepth)));
     for (int it = 0; it < 4 && depth < kMaxDepth; ++it) {  // uniform
         int v[1] = {groups * ceil_div(chunks, depth)}, tot[1];
@@ -191,9 +199,9 @@ __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, M
         const int over = static_cast<int>(static_cast<int64_t>(depth) * tot[0] / (kRounds * kTileWaves));
         depth = min(max(over, depth + 1), kMaxDepth);
     }
-    const int want_s = all_groups > 0 ? kTileWaves / all_groups : 1;
-    const int s_segs = min(max(want_s, 1), kMaxSampleSegs);
-    int v[3] = {groups, groups * min(s_segs, max(ceil_div(chunks, kTileChunks), 1)), groups * ceil_div(chunks, depth)};
+    const int64_t share = s_tiles * static_cast<int64_t>(kTileWaves) / max(all[1], static_cast<int64_t>(1));
+    const int s_segs = max(static_cast<int>(min(share, static_cast<int64_t>(min(s_tiles, kMaxSampleSegs)))), 1);
+    int v[3] = {groups, groups * s_segs, groups * ceil_div(chunks, depth)};
     int tot[3];
     block_scan_k<3>(v, tot, s_scan);
     if (live) {
@@ -202,13 +210,13 @@ __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, M
         plan[c].grp_off = v[0];
         plan[c].s_tile_off = v[1];
         plan[c].tile_off = v[2];
+        plan[c].s_segs = s_segs;
     }
     if (c == 0) {
         ctl->groups = tot[0];
         ctl->s_tiles = tot[1];
         ctl->tiles = tot[2];
         ctl->depth = depth;
-        ctl->s_segs = s_segs;
     }
 }
 
@@ -748,7 +756,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         const int c = find_set(n_sets, tu, [&](int s) { return static_cast<int64_t>(plan[s].s_tile_off); });
         const SetPlan qc = plan[c], pc = plan[c ^ 1];
         const int chunks = ceil_div(pc.n, kTileRows), tiles = max(ceil_div(chunks, kTileChunks), 1);
-        const int segs = min(ctl->s_segs, tiles);
+        const int segs = qc.s_segs;
         const int stride = sample_stride(pc.n);
         const int local = tu - qc.s_tile_off;
         const int g = local % qc.groups, sg = local / qc.groups;
@@ -854,8 +862,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 m1[t] = max(m1[t], o1);
             }
             if (lane < 16)
-                w.s_best[(static_cast<int64_t>(qc.grp_off + g) * ctl->s_segs + sg) * kGroup + t * kTileCols + lane] =
-                    make_int2(m1[t], m2[t]);
+                w.s_best[static_cast<int64_t>(tu) * kGroup + t * kTileCols + lane] = make_int2(m1[t], m2[t]);
         }
     }
 }
@@ -901,23 +908,26 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         const int c0 = sg * depth, c1 = min(c0 + depth, chunks);
         const RowBuf b = row_buf(w.rows, w.half, pc.base, chunks);
         const QueryRegs q = load_queries(qc, list, g, w.rows, lane);
-        const int s_segs = min(ctl->s_segs, ceil_div(chunks, kTileChunks));
         // query `lane` of the group: its slot and the least raw score of a row that it may need
         // (the sample's partials, all in flight; the chain per tile column took 13 us)
         const int iq = g * kGroup + lane;
         const int slot_l = list ? list[qc.base + min(iq, qc.nq - 1)] : qc.base + min(iq, qc.nq - 1);
         const float err = w.err[slot_l];
         const int own = w.half[slot_l] + 1;  // minus the query's half norm
-        const int2* src = w.s_best + static_cast<int64_t>(qc.grp_off + g) * ctl->s_segs * kGroup + lane;
-        int2 part[kMaxSampleSegs];
-#pragma unroll
-        for (int k = 0; k < kMaxSampleSegs; ++k) part[k] = src[min(k, s_segs - 1) * kGroup];
+        const int2* src = w.s_best + static_cast<int64_t>(qc.s_tile_off + g) * kGroup + lane;
+        const int64_t seg_step = static_cast<int64_t>(qc.groups) * kGroup;
         int m1 = kNoRow, m2 = kNoRow;
+#pragma unroll 1
+        for (int k0 = 0; k0 < qc.s_segs; k0 += kPartRounds) {
+            int2 part[kPartRounds];
 #pragma unroll
-        for (int k = 0; k < kMaxSampleSegs; ++k) {
-            if (k >= s_segs) break;
-            m2 = max(min(m1, part[k].x), max(m2, part[k].y));
-            m1 = max(m1, part[k].x);
+            for (int k = 0; k < kPartRounds; ++k) part[k] = src[min(k0 + k, qc.s_segs - 1) * seg_step];
+#pragma unroll
+            for (int k = 0; k < kPartRounds; ++k) {
+                if (k0 + k >= qc.s_segs) break;
+                m2 = max(min(m1, part[k].x), max(m2, part[k].y));
+                m1 = max(m1, part[k].x);
+            }
         }
         const bool act = iq < qc.nq && err >= 0.0f;
         const int w2 = m2 == kNoRow ? m2 : m2 + own;
@@ -1703,8 +1713,8 @@ MatchWs carve_match(Carver& c, int n_sets, int64_t q_cap, int dim) {
     w.c_norm = c.take<float2>(static_cast<size_t>(w.slot_cap / kTileRows + 1));
     w.perm = c.take<int32_t>(static_cast<size_t>(w.slot_cap));
     w.inv = c.take<int32_t>(static_cast<size_t>(w.slot_cap));
-    // s_segs <= max(1, kTileWaves / groups): at most kTileWaves groups of partials, or one each
-    w.s_best = c.take<int2>(static_cast<size_t>(std::max<int64_t>(grp_cap, kTileWaves)) * kGroup);
+    // at most kTileWaves segments of the sample, and one more for each group
+    w.s_best = c.take<int2>(static_cast<size_t>(grp_cap + kTileWaves) * kGroup);
     w.err = c.take<float>(static_cast<size_t>(w.slot_cap));
     w.cnt = c.take<int32_t>(static_cast<size_t>(w.slot_cap));
     // listed rows: kMinCap per slot whatever the size, up to kMaxCap from 128 MB more
