@@ -315,11 +315,11 @@ __device__ void order_rows(const MatchSet* sets, int n_sets, int dim, const Sing
 // Centre: the mean of kCentreRows rows at even strides over both sets, in a
 // fixed order (any centre is valid, every bound is stated for the rows as
 // rounded); scale: kRangeRms root mean square norms about it span kRange.  Rows
-// with norms beyond kOrdinary times the median of the largest of each four (about
-// the 84% quantile) have no part in either: a single one of a million times the
-// norm among them otherwise put all others within a few units, their lists
-// overflowed and both sets were scanned exactly (13,015 x 15,401 rows: 261 us
-// without such a row, 3,041 with it, now 252).
+// with norms beyond kOrdinary times the upper quartile of the 16 that a wavefront
+// reads have no part in either: a single one of a million times the norm among the 256
+// otherwise put all others within a few units, their lists overflowed and both sets
+// were scanned exactly (13,015 x 15,401 rows: 261 us without such a row, 3,041 with
+// it, now 252).  A quantile of all 256 took two barriers and 2 us more.
 __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n_sets, int dim, int one_sided,
                                                            int64_t pool, SetPlan* plan, MatchCtl* ctl, PairScale* pp,
                                                            SinglePair single, MatchWs w, DevStatus* st) {
@@ -335,8 +335,6 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
         constexpr int kPer = kCentreRows / kGroups;
         static_assert(kMaxMatchDim == kWave, "a row per wavefront");
         __shared__ double s_part[kPlanThreads];
-        __shared__ float s_norm[kCentreRows / 4];
-        static_assert(kCentreRows / 4 == kWave, "a lane per four rows");
         __shared__ int s_rows[kGroups];
         const int pair = static_cast<int>(blockIdx.x) - 1;
         const MatchSet a = by_value ? single.a : sets[2 * pair];
@@ -373,23 +371,16 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
         n2[0] += __shfl_xor(n2[0], 1, kWave);
         const bool row = g + d / 4 * kGroups < ns;
         const float norm = n2[0] >= 0.0f ? sqrtf(n2[0]) : INFINITY;
-        float most = row ? norm : 0.0f;
+        // the upper quartile of the wavefront's rows, to the twelve leading bits (rounded up)
+        constexpr int kBits = 12;
+        constexpr uint32_t kInf = 0x7f800000u;
+        const uint32_t key = (row ? __float_as_uint(norm) : ~0u) >> (31 - kBits);
+        const int rank = max(__popcll(ballot(row)) - 4, 0) * 3 / 4;  // four lanes a row
+        uint32_t at = 0;
 #pragma unroll
-        for (int l = 4; l < 16; l <<= 1) most = fmaxf(most, __shfl_xor(most, l, kWave));
-        if (d % 16 == 0) s_norm[4 * g + d / 16] = row ? most : INFINITY;  // four rows' largest; the first is there if any is
-        __syncthreads();
-        {
-            // their median, to the twelve leading bits (rounded up); counting who lies below whom took 3 us
-            constexpr int kBits = 12;
-            const uint32_t key = __float_as_uint(s_norm[d]) >> (31 - kBits);
-            const int fours = __popcll(ballot(d / 4 + 4 * kGroups * (d % 4) < ns));
-            uint32_t at = 0;
-#pragma unroll
-            for (int k = kBits - 1; k >= 0; --k)
-                if (__popcll(ballot(key < (at | 1u << k))) <= max(fours - 1, 0) / 2) at |= 1u << k;
-            constexpr uint32_t kInf = 0x7f800000u;
-            most = kOrdinary * __uint_as_float(min((at + 1) << (31 - kBits), kInf));
-        }
+        for (int k = kBits - 1; k >= 0; --k)
+            if (__popcll(ballot(key < (at | 1u << k))) <= rank) at |= 1u << k;
+        const float most = kOrdinary * __uint_as_float(min((at + 1) << (31 - kBits), kInf));
         const uint64_t use = ballot(row && norm <= most);  // bit 4 u: row u counts
         if (d == 0) s_rows[g] = __popcll(use) / 4;
         double sum = 0.0;
@@ -1269,9 +1260,17 @@ __device__ __forceinline__ int exact_segs(int64_t F, int64_t groups, int64_t par
 // so a group of up to 8, 16 or 32 entries gives each one 8, 4 or 2 lanes, with
 // rows of their own: a batch's sets have about seven such entries each, and a lane
 // an entry left nine tenths of the wavefront idle (64 pairs 1,020 -> 761 us, 16
-// pairs 244 -> 213, 100,000 rows 273 -> 244).  The lanes and waves of an entry merge
-// their (best, index, second) and write them as the segment's partial result.  The block that finishes a group's last segment (counted in
-// grp_done, which comes in cleared) merges the group's partials in segment
+// pairs 244 -> 213, 100,000 rows 273 -> 244).
+// A group whose entries are all there for an overflowed list takes the rows in norm
+// order and passes over the tiles that none of them can reach by their norms, as the
+// sweep does (a cluster of three tenths of 13,015 x 15,401 rows, closer together than
+// the integers resolve: 1,170 -> 800 us for the call); the groups of a segment go to
+// neighbouring blocks, so that a block's next item is of another segment (where the
+// cluster lies in the order made some of them long: scan of six tenths 1,320 -> 1,180
+// us).  Another group reads every row, as they lie.
+// The lanes and waves of an entry merge their (best, index, second) and write them as
+// the segment's partial result.  The block that finishes a group's last segment
+// (counted in grp_done, which comes in cleared) merges the group's partials in segment
 // order into nn, best and second, and resets the count.
 template <int KS>
 __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict__ sets, SetPlan* plan, int n_sets,
@@ -1282,6 +1281,7 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
     constexpr int kXRows = KS <= 9 ? 128 : 64;   // partner rows per LDS tile
     __shared__ __attribute__((aligned(16))) double s_x[kXRows * kD];
     __shared__ const float* s_row[kXRows];
+    __shared__ int s_id[kXRows];
     __shared__ double s_b1[kBlock], s_b2[kBlock];
     __shared__ int s_j1[kBlock];
     __shared__ int s_last;
@@ -1406,8 +1406,8 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
     int32_t* pj1 = reinterpret_cast<int32_t*>(part + 2 * F * S);
     const int64_t items = groups * S;
     for (int64_t item = blockIdx.x; item < items; item += gridDim.x) {
-        const int64_t g = item / S;
-        const int sg = static_cast<int>(item % S);
+        const int sg = static_cast<int>(item / groups);
+        const int64_t g = item - sg * groups;
         int lo = 0, hi = n_sets - 1;  // the group's set: the last whose first group is <= g
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -1424,6 +1424,7 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
         const bool have = local < s_pre[c + 1] - s_pre[c];
         const int64_t e = s_pre[c] + local;
         const int64_t slot = have ? w.fb_list[plan[c].base + local] : plan[c].base;
+        const float err = w.err[slot], nu = w.nu[slot];
         double y[kD];
         {
             const float* yr = set_row(sets[c], w.perm[slot], dim);
@@ -1433,19 +1434,60 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
                 y[t] = t < dim ? v : 0.0;
             }
         }
+        // the norms that the entries of a group may need, when all are there for their lists: what
+        // the first of the rows on them say
+        float from = -INFINITY, upto = INFINITY;
+        if (!ballot(have && err < 0.0f)) {  // uniform in the block
+            int v[kMinCap], m1 = kNoRow, m2 = kNoRow;
+#pragma unroll
+            for (int k = 0; k < kMinCap; ++k) v[k] = static_cast<int>(w.pool[slot * ctl->cap + k].y);
+#pragma unroll
+            for (int k = 0; k < kMinCap; ++k) {
+                m2 = med3(m1, m2, v[k]);
+                m1 = max(m1, v[k]);
+            }
+            const float reach = reach_of(m2 == kNoRow ? m2 : m2 + w.half[slot] + 1,
+                                         static_cast<double>(err) + most_err(dim), pp[c >> 1].scale);
+            from = have ? nu * (1.0f - kNormSlack) - reach : INFINITY;
+            upto = have ? nu * (1.0f + kNormSlack) + reach : -INFINITY;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                from = fminf(from, __shfl_xor(from, d, kWave));
+                upto = fmaxf(upto, __shfl_xor(upto, d, kWave));
+            }
+        }
         double b1 = INFINITY, b2 = INFINITY;
         int j1 = INT_MAX;
         {
-            const int np = plan[p].n;
-            const int len = (np + S - 1) / S;
+            const int np = plan[p].n, base = plan[p].base;
+            const bool bounded = from > -INFINITY;  // uniform in the block, and over a group's segments
+            int len = (np + S - 1) / S;
+            if (bounded) len = (len + kTileRows - 1) / kTileRows * kTileRows;  // whole chunks
             const int r_begin = min(np, sg * len), r_end = min(np, r_begin + len);
+            // rows in norm order where some can be passed over, else as they lie
+            const auto row_at = [&](int r) {
+                const int at = min(r + static_cast<int>(threadIdx.x) % kXRows, np - 1);
+                return bounded ? w.perm[base + at] : at;
+            };
+            const auto norms_at = [&](int r) {
+                const int at = min(r + L % (kXRows / kTileRows) * kTileRows, np - 1);
+                return bounded ? w.c_norm[(base + at) / kTileRows] : make_float2(0.f, 0.f);
+            };
+            int next = row_at(r_begin);
+            float2 next_norms = norms_at(r_begin);
             for (int r0 = r_begin; r0 < r_end; r0 += kXRows) {
-                const int nr = min(kXRows, r_end - r0);
+                const int nr = min(kXRows, r_end - r0), j = next;
+                const float2 cn = next_norms;
+                next = row_at(r0 + kXRows);  // a tile ahead: the rows' addresses hang on it
+                next_norms = norms_at(r0 + kXRows);
+                if (bounded && !ballot(cn.x <= upto && cn.y >= from)) continue;  // none of the rows is needed
                 __syncthreads();
                 // the tile's rows: their addresses first, then all values by all threads,
                 // eight loads in flight per thread
-                if (static_cast<int>(threadIdx.x) < nr)
-                    s_row[threadIdx.x] = set_row(sets[p], r0 + static_cast<int>(threadIdx.x), dim);
+                if (static_cast<int>(threadIdx.x) < nr) {
+                    s_id[threadIdx.x] = j;
+                    s_row[threadIdx.x] = set_row(sets[p], j, dim);
+                }
                 __syncthreads();
                 const int n_el = nr * dim;
                 for (int e0 = static_cast<int>(threadIdx.x); e0 < n_el; e0 += 8 * kBlock) {
@@ -1463,8 +1505,10 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
                 }
                 __syncthreads();
                 {
-                    const auto take = [&](double acc, int j) {
-                        if (acc < b1) {
+                    const auto take = [&](double acc, int at) {
+                        if (!(acc <= b2)) return;
+                        const int j = s_id[at];
+                        if (acc < b1 || (acc == b1 && j < j1)) {
                             b2 = b1;
                             b1 = acc;
                             j1 = j;
@@ -1487,8 +1531,8 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
                             a = a + da1 * da1;
                             b = b + db1 * db1;
                         }
-                        if (ra < nr) take(a, r0 + ra);
-                        if (rb < nr) take(b, r0 + rb);
+                        if (ra < nr) take(a, ra);
+                        if (rb < nr) take(b, rb);
                     }
                 }
             }
