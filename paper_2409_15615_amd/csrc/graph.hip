@@ -207,6 +207,8 @@ enum : int { kSettled = 0, kAll = 1, kDue = 2 };  // what the next sweep is to d
 constexpr int kHSweeps = 48;  // sweeps launched at most; the block peel finishes graphs that need more
 constexpr int kHChunk = 8;    // sweeps between two looks of the host at the convergence flag
 constexpr int kHRegs = 32;    // neighbour values held in registers per lane (deg <= 2048)
+constexpr int kHFew = 4;      // and of short rows (deg <= 256): the checks of 32 were most of a sweep over them
+                              // (16,000 vertices of 8 neighbours: 13 us a sweep, now 7)
 static_assert(kHSweeps % kHChunk == 0, "whole chunks");
 
 __global__ __launch_bounds__(kBlock) void kcore_hinit(const int32_t* __restrict__ off, int32_t n,
@@ -218,6 +220,62 @@ __global__ __launch_bounds__(kBlock) void kcore_hinit(const int32_t* __restrict_
         due[v] = 0;
     }
     for (int i = blockIdx.x * kBlock + threadIdx.x; i <= kHSweeps; i += gridDim.x * kBlock) flag[i] = i == 0 ? kAll : kSettled;
+}
+
+// The largest x <= hi that as many of a row's values reach, by their counts.
+template <class F>
+__device__ __forceinline__ int h_index(int hi, F count_ge) {
+    int lo = count_ge(hi);
+    if (lo >= hi) return hi;
+    --hi;  // below hi as many values reach lo at least; count_ge(hi + 1) < hi + 1
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (count_ge(mid) >= mid) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// A row of at most 64 R neighbours (adj[b ..], deg of them) of vertex v, whose value
+// is cap: its new value, and where that is less, the neighbours of whose count v was
+// one are due.
+template <int R>
+__device__ __forceinline__ int sweep_row(const int32_t* __restrict__ adj, int32_t n, int32_t* h, int32_t* due, int v,
+                                         int b, int deg, int cap, int next, int32_t* __restrict__ info) {
+    const int lane = lane_id();
+    int val[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int t = r * kWave + lane;
+        val[r] = -1;
+        if (r * kWave < deg) val[r] = t < deg ? adj[b + t] : -1;  // uniform
+    }
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        if (r * kWave >= deg) continue;  // uniform
+        const int u = val[r];
+        const bool in = u >= 0 && u < n;
+        bad = bad || (!in && r * kWave + lane < deg);  // not a vertex: reported, never followed
+        const int w = h[in ? u : v];
+        val[r] = in ? w : -1;
+    }
+    if (bad) info[2] = 1;
+    const int lo = h_index(min(cap, deg), [&](int x) {
+        int c = 0;
+#pragma unroll
+        for (int r = 0; r < R; r += 4)
+            if (r * kWave < deg)  // uniform
+                c += __popcll(ballot(val[r] >= x)) + __popcll(ballot(val[r + 1] >= x)) +
+                     __popcll(ballot(val[r + 2] >= x)) + __popcll(ballot(val[r + 3] >= x));
+        return c;
+    });
+    if (lo < cap) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (r * kWave < deg && val[r] > lo && val[r] <= cap) due[adj[b + r * kWave + lane]] = next;
+    }
+    return lo;
 }
 
 __global__ __launch_bounds__(kBlock) void kcore_hsweep(const int32_t* __restrict__ off,
@@ -233,39 +291,14 @@ __global__ __launch_bounds__(kBlock) void kcore_hsweep(const int32_t* __restrict
         const int b = off[v], deg = off[v + 1] - b;
         if (todo == kSettled) return;  // looked at beside the row's own loads
         if (cap == 0 || (todo == kDue && now < sweep)) continue;
-        int hi = min(cap, deg);
-        int lo = 0;
-        int val[kHRegs];
-        const bool in_regs = deg <= kHRegs * kWave;
-        if (in_regs) {
-#pragma unroll
-            for (int r = 0; r < kHRegs; ++r) {
-                const int t = r * kWave + lane;
-                val[r] = -1;
-                if (r * kWave < deg) val[r] = t < deg ? adj[b + t] : -1;  // uniform
-            }
-            bool bad = false;
-#pragma unroll
-            for (int r = 0; r < kHRegs; ++r) {
-                if (r * kWave >= deg) continue;  // uniform
-                const int u = val[r];
-                const bool in = u >= 0 && u < n;
-                bad = bad || (!in && r * kWave + lane < deg);  // not a vertex: reported, never followed
-                const int w = h[in ? u : v];
-                val[r] = in ? w : -1;
-            }
-            if (bad) info[2] = 1;
-        }
-        // count of neighbour values >= x (from registers, or re-read for long rows)
-        auto count_ge = [&](int x) {
-            int c = 0;
-            if (in_regs) {
-#pragma unroll
-                for (int r = 0; r < kHRegs; r += 4)
-                    if (r * kWave < deg)  // uniform
-                        c += __popcll(ballot(val[r] >= x)) + __popcll(ballot(val[r + 1] >= x)) +
-                             __popcll(ballot(val[r + 2] >= x)) + __popcll(ballot(val[r + 3] >= x));
-            } else {
+        int lo;
+        if (deg <= kHFew * kWave) {  // uniform
+            lo = sweep_row<kHFew>(adj, n, h, due, v, b, deg, cap, sweep + 1, info);
+        } else if (deg <= kHRegs * kWave) {
+            lo = sweep_row<kHRegs>(adj, n, h, due, v, b, deg, cap, sweep + 1, info);
+        } else {  // re-read for each step of the search
+            lo = h_index(min(cap, deg), [&](int x) {
+                int c = 0;
                 for (int t0 = 0; t0 < deg; t0 += kWave) {
                     const int t = t0 + lane;
                     int w = -1;
@@ -276,35 +309,18 @@ __global__ __launch_bounds__(kBlock) void kcore_hsweep(const int32_t* __restrict
                     }
                     c += __popcll(ballot(w >= x));
                 }
-            }
-            return c;
-        };
-        const int at_hi = count_ge(hi);
-        if (at_hi >= hi) {
-            lo = hi;
-        } else {
-            lo = at_hi;  // below hi as many values reach at_hi at least
-            --hi;        // invariant: count_ge(lo) >= lo, count_ge(hi + 1) < hi + 1
-            while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (count_ge(mid) >= mid) lo = mid;
-                else hi = mid - 1;
-            }
+                return c;
+            });
+            if (lo < cap)
+                for (int t = lane; t < deg; t += kWave) {
+                    const int u = adj[b + t];
+                    if (u >= 0 && u < n && h[u] > lo && h[u] <= cap) due[u] = sweep + 1;
+                }
         }
         if (lo < cap) {
             if (lane == 0) {
                 h[v] = lo;
                 due[v] = sweep + 1;
-            }
-            if (in_regs) {
-#pragma unroll
-                for (int r = 0; r < kHRegs; ++r)
-                    if (r * kWave < deg && val[r] > lo && val[r] <= cap) due[adj[b + r * kWave + lane]] = sweep + 1;
-            } else {
-                for (int t = lane; t < deg; t += kWave) {
-                    const int u = adj[b + t];
-                    if (u >= 0 && u < n && h[u] > lo && h[u] <= cap) due[u] = sweep + 1;
-                }
             }
             changed = true;
         }
