@@ -251,8 +251,11 @@ __device__ void order_rows(const MatchSet* sets, int n_sets, int dim, const Sing
         const int e0 = (tile - s_tile0[c]) * kSortTile, cnt = min(kSortTile, s_n[c] - e0);
         const int64_t base = s_base[c] + e0;
         const MatchSet set = by_value ? (c ? single.b : single.a) : sets[c];
+        // what there is to sort (500 pairs of clouds of 200 points: the launch 92 us with 1,024, 77)
+        int size = kWave;
+        while (size < cnt) size <<= 1;
 #pragma unroll 4
-        for (int u = 0; u < kSortTile / kPerRound; ++u) {
+        for (int u = 0; u < (size + kPerRound - 1) / kPerRound; ++u) {
             const int r = u * kPerRound + t / 8;
             float x2 = 0.0f;
             if (r < cnt) {
@@ -277,7 +280,7 @@ __device__ void order_rows(const MatchSet* sets, int n_sets, int dim, const Sing
         // bitonic, a key per thread: partners closer than a wavefront trade through shuffles
         uint32_t key = s_key[t];
 #pragma unroll 1
-        for (int k = 2; k <= kSortTile; k <<= 1) {
+        for (int k = 2; k <= size; k <<= 1) {
 #pragma unroll 1
             for (int d = k >> 1; d > 0; d >>= 1) {
                 uint32_t o;
