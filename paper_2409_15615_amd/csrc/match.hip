@@ -173,14 +173,16 @@ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; 
 // for which even the deepest tiles are more (two of 12 million rows, both directions
 // in full) set err_capacity, so that nothing is matched.
 constexpr int64_t kMostTiles = INT32_MAX - static_cast<int64_t>(kTileWaves);
-__device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, MatchCtl* ctl, DevStatus* st,
-                             int* s_scan, int64_t* s_sum) {
+// Returns the query-row products.
+__device__ int64_t plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, MatchCtl* ctl, DevStatus* st,
+                                int* s_scan, int64_t* s_sum) {
     const int groups = (live && n_p > 0) ? ceil_div(nq, kGroup) : 0;
     const int chunks = ceil_div(n_p, kTileRows);
     const int s_tiles = max(ceil_div(chunks, kTileChunks), 1);
-    int64_t all[3] = {static_cast<int64_t>(groups) * chunks, static_cast<int64_t>(groups) * s_tiles,
-                      static_cast<int64_t>(groups) * ceil_div(chunks, kMaxDepth)};
-    block_sum64<3>(all, s_sum);
+    int64_t all[4] = {static_cast<int64_t>(groups) * chunks, static_cast<int64_t>(groups) * s_tiles,
+                      static_cast<int64_t>(groups) * ceil_div(chunks, kMaxDepth),
+                      live ? static_cast<int64_t>(nq) * n_p : 0};
+    block_sum64<4>(all, s_sum);
     if (all[2] > kMostTiles) {  // uniform
         if (live) plan[c].groups = plan[c].nq = plan[c].grp_off = plan[c].s_tile_off = plan[c].tile_off = 0;
         if (c == 0) {
@@ -188,7 +190,7 @@ __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, M
             ctl->depth = 1;
             st->err_capacity = 1;
         }
-        return;
+        return 0;
     }
     int depth = static_cast<int>(min(max(all[0] / (kRounds * kTileWaves), static_cast<int64_t>(kMinDepth)),
                                      static_cast<int64_t>(kMaxDepth)));
@@ -199,8 +201,10 @@ __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, M
         const int over = static_cast<int>(static_cast<int64_t>(depth) * tot[0] / (kRounds * kTileWaves));
         depth = min(max(over, depth + 1), kMaxDepth);
     }
-    const int64_t share = s_tiles * static_cast<int64_t>(kTileWaves) / max(all[1], static_cast<int64_t>(1));
-    const int s_segs = max(static_cast<int>(min(share, static_cast<int64_t>(min(s_tiles, kMaxSampleSegs)))), 1);
+    // (a set has at most 2^14 sort tiles)
+    const uint32_t share = static_cast<uint32_t>(s_tiles) * kTileWaves /
+                           static_cast<uint32_t>(min(max(all[1], static_cast<int64_t>(1)), static_cast<int64_t>(INT32_MAX)));
+    const int s_segs = max(min(static_cast<int>(share), min(s_tiles, kMaxSampleSegs)), 1);
     int v[3] = {groups, groups * s_segs, groups * ceil_div(chunks, depth)};
     int tot[3];
     block_scan_k<3>(v, tot, s_scan);
@@ -218,6 +222,7 @@ __device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, M
         ctl->tiles = tot[2];
         ctl->depth = depth;
     }
+    return all[3];
 }
 
 // The rows of each sort tile (1,024 rows of a set) in order of their norm about
@@ -338,6 +343,7 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
         constexpr int kPer = kCentreRows / kGroups;
         static_assert(kMaxMatchDim == kWave, "a row per wavefront");
         __shared__ double s_part[kPlanThreads];
+        __shared__ double s_sq[kGroups];
         __shared__ int s_rows[kGroups];
         const int pair = static_cast<int>(blockIdx.x) - 1;
         const MatchSet a = by_value ? single.a : sets[2 * pair];
@@ -399,7 +405,6 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
             mu += s_part[q * kMaxMatchDim + d];
         }
         mu = rows > 0 ? mu / rows : 0.0;
-        __syncthreads();
         double sq = 0.0;
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
@@ -407,12 +412,12 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
             if (d < dim && (use >> (4 * u) & 1)) sq += v * v;
         }
         sq = wave_sum(sq);
-        if (d == 0) s_part[g] = sq;
+        if (d == 0) s_sq[g] = sq;
         __syncthreads();
         if (g == 0) pp[pair].mu[d] = d < dim ? mu : 0.0;
         if (threadIdx.x == 0) {
             double all = 0.0;
-            for (int q = 0; q < kGroups; ++q) all += s_part[q];
+            for (int q = 0; q < kGroups; ++q) all += s_sq[q];
             const double rms = rows > 0 ? sqrt(all / rows) : 0.0;
             double s = rms * (kRangeRms / kRange);
             if (!(s > 1e-30) || !(s < 1e30)) s = 1.0;  // equal rows, or nothing that can be scaled
@@ -422,7 +427,7 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
         return;
     }
     __shared__ int s_scan[3 * (kPlanThreads / kWave)];
-    __shared__ int64_t s_sum[3 * (kPlanThreads / kWave)];
+    __shared__ int64_t s_sum[4 * (kPlanThreads / kWave)];
     const int c = threadIdx.x;
     if (by_value) {
         for (int k = c; k < static_cast<int>(sizeof(DevStatus) / 4); k += kPlanThreads)
@@ -461,11 +466,9 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
     const bool rows_only = one_sided && ((c & 1) ? n >= n_p : n > n_p);
     const int nq = (!paired || rows_only) ? 0 : n;
     __syncthreads();
-    plan_queries(c, live, nq, n_p, plan, ctl, st, s_scan, s_sum);
-    int64_t work[1] = {static_cast<int64_t>(nq) * n_p};
-    block_sum64<1>(work, s_sum);
+    const int64_t products = plan_queries(c, live, nq, n_p, plan, ctl, st, s_scan, s_sum);
     if (c == 0) {
-        st->match_products = work[0];
+        st->match_products = products;
         ctl->slots = tot[0] * kTileRows;
         ctl->emit_tiles = tot[1];
         // whole 128-byte lines, an odd number of them: with lists a power of two apart the first
@@ -482,7 +485,7 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
 __global__ __launch_bounds__(kPlanThreads) void match_plan_back(int n_sets, SetPlan* plan, MatchCtl* ctl,
                                                                 DevStatus* st) {
     __shared__ int s_scan[3 * (kPlanThreads / kWave)];
-    __shared__ int64_t s_sum[3 * (kPlanThreads / kWave)];
+    __shared__ int64_t s_sum[4 * (kPlanThreads / kWave)];
     const int c = threadIdx.x;
     const bool live = c < n_sets && (c ^ 1) < n_sets;
     const int n_p = live ? plan[c ^ 1].n : 0;
