@@ -126,10 +126,12 @@ int32_t kmg_version(void);
  * the first matching phase, match_image the whole matching back) and
  * returns the number of stages; kmg_stage_name(i) names stage i (static
  * storage).  kmg_timing_work copies up to n per-stage work counts of the
- * stage's last timed launch (for match_topk: query-row products of the
- * matching's first phase; 0 where a stage counts none, -1 if the count could not be read) and returns the number of stages;
- * it reads device memory of the last call's workspace, which must still be
- * allocated.
+ * stage's last timed launch (for match_topk and match_image: query-row
+ * products that the sample and the sweep of the first matching phase, or of the
+ * matching back, evaluated, 256 to a tile of 16 queries and 16 rows; 0 where a
+ * stage counts none, -1 if the count could not be read) and returns the number
+ * of stages; it reads device memory of the last call's workspace, which must
+ * still be allocated.
  */
 int32_t kmg_timing_enable(int32_t on);
 int32_t kmg_timing_read(double* ms, int64_t* launches, int32_t n);

@@ -129,7 +129,7 @@ struct DevStatus {
     uint32_t feat_fp64;       // pair features recomputed in FP64
     uint32_t feat_edge;       // FP64 features within 1e-9 of a bin edge
     int32_t err_sync;         // a bounded wait inside a kernel gave up (never expected)
-    int64_t match_products;   // query-row products of the matching's first phase
+    int64_t match_products[2]; // query-row products evaluated by the matching's phases (while timing is on)
 };
 
 // Linear workspace allocator; with base == nullptr it only measures.
@@ -202,6 +202,7 @@ int timer_enable(int on);
 int timer_read(double* ms, int64_t* launches, int n);
 // The open stage's work units live in *dev (a device counter read back by timer_work).
 void timer_note_work(const int64_t* dev);
+bool timer_on();
 int timer_work(int64_t* work, int n);
 const char* stage_name(int stage);
 

@@ -173,16 +173,14 @@ __device__ __forceinline__ int ceil_div(int a, int b) { return (a + b - 1) / b; 
 // for which even the deepest tiles are more (two of 12 million rows, both directions
 // in full) set err_capacity, so that nothing is matched.
 constexpr int64_t kMostTiles = INT32_MAX - static_cast<int64_t>(kTileWaves);
-// Returns the query-row products.
-__device__ int64_t plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, MatchCtl* ctl, DevStatus* st,
-                                int* s_scan, int64_t* s_sum) {
+__device__ void plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan, MatchCtl* ctl, DevStatus* st,
+                             int* s_scan, int64_t* s_sum) {
     const int groups = (live && n_p > 0) ? ceil_div(nq, kGroup) : 0;
     const int chunks = ceil_div(n_p, kTileRows);
     const int s_tiles = max(ceil_div(chunks, kTileChunks), 1);
-    int64_t all[4] = {static_cast<int64_t>(groups) * chunks, static_cast<int64_t>(groups) * s_tiles,
-                      static_cast<int64_t>(groups) * ceil_div(chunks, kMaxDepth),
-                      live ? static_cast<int64_t>(nq) * n_p : 0};
-    block_sum64<4>(all, s_sum);
+    int64_t all[3] = {static_cast<int64_t>(groups) * chunks, static_cast<int64_t>(groups) * s_tiles,
+                      static_cast<int64_t>(groups) * ceil_div(chunks, kMaxDepth)};
+    block_sum64<3>(all, s_sum);
     if (all[2] > kMostTiles) {  // uniform
         if (live) plan[c].groups = plan[c].nq = plan[c].grp_off = plan[c].s_tile_off = plan[c].tile_off = 0;
         if (c == 0) {
@@ -190,7 +188,7 @@ __device__ int64_t plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan
             ctl->depth = 1;
             st->err_capacity = 1;
         }
-        return 0;
+        return;
     }
     int depth = static_cast<int>(min(max(all[0] / (kRounds * kTileWaves), static_cast<int64_t>(kMinDepth)),
                                      static_cast<int64_t>(kMaxDepth)));
@@ -222,7 +220,6 @@ __device__ int64_t plan_queries(int c, bool live, int nq, int n_p, SetPlan* plan
         ctl->tiles = tot[2];
         ctl->depth = depth;
     }
-    return all[3];
 }
 
 // The rows of each sort tile (1,024 rows of a set) in order of their norm about
@@ -427,7 +424,7 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
         return;
     }
     __shared__ int s_scan[3 * (kPlanThreads / kWave)];
-    __shared__ int64_t s_sum[4 * (kPlanThreads / kWave)];
+    __shared__ int64_t s_sum[3 * (kPlanThreads / kWave)];
     const int c = threadIdx.x;
     if (by_value) {
         for (int k = c; k < static_cast<int>(sizeof(DevStatus) / 4); k += kPlanThreads)
@@ -466,9 +463,9 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
     const bool rows_only = one_sided && ((c & 1) ? n >= n_p : n > n_p);
     const int nq = (!paired || rows_only) ? 0 : n;
     __syncthreads();
-    const int64_t products = plan_queries(c, live, nq, n_p, plan, ctl, st, s_scan, s_sum);
+    plan_queries(c, live, nq, n_p, plan, ctl, st, s_scan, s_sum);
     if (c == 0) {
-        st->match_products = products;
+        st->match_products[0] = st->match_products[1] = 0;
         ctl->slots = tot[0] * kTileRows;
         ctl->emit_tiles = tot[1];
         // whole 128-byte lines, an odd number of them: with lists a power of two apart the first
@@ -485,7 +482,7 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
 __global__ __launch_bounds__(kPlanThreads) void match_plan_back(int n_sets, SetPlan* plan, MatchCtl* ctl,
                                                                 DevStatus* st) {
     __shared__ int s_scan[3 * (kPlanThreads / kWave)];
-    __shared__ int64_t s_sum[4 * (kPlanThreads / kWave)];
+    __shared__ int64_t s_sum[3 * (kPlanThreads / kWave)];
     const int c = threadIdx.x;
     const bool live = c < n_sets && (c ^ 1) < n_sets;
     const int n_p = live ? plan[c ^ 1].n : 0;
@@ -740,14 +737,25 @@ __device__ __forceinline__ int first_tile(int n_sets, int wv) {
     return j / kTileRun * (kXcds * kTileRun) + b % kXcds * kTileRun + j % kTileRun;
 }
 
+// The 16 x 16 products that a wavefront evaluated, where they are counted (kCount: per-stage
+// timing is on; counted always they were 1% of the call for 100,000 rows).
+__device__ __forceinline__ void count_work(int64_t* work, int done) {
+    if (done && lane_id() == 0)
+        atomicAdd(reinterpret_cast<unsigned long long*>(work),
+                  static_cast<unsigned long long>(done) * (kTileRows * kTileCols));
+}
+
 // Best and second best raw score of every query over a segment of the sample
 // (whole sort tiles).  Of each sort tile the chunks in the group's own norm range
 // go first; what they find limits the norms at which the rest can matter.
+template <bool kCount>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sample_tiles(
     const SetPlan* __restrict__ plan, int n_sets, int dim, const int32_t* __restrict__ list,
-    const PairScale* __restrict__ pp, MatchWs w, const MatchCtl* __restrict__ ctl, const DevStatus* __restrict__ st) {
+    const PairScale* __restrict__ pp, MatchWs w, const MatchCtl* __restrict__ ctl, const DevStatus* __restrict__ st,
+    int64_t* work) {
     const int lane = lane_id();
     const int total = st->err_capacity ? 0 : ctl->s_tiles;
+    int done = 0;  // 16 x 16 products
     for (int tile = first_tile(n_sets, static_cast<int>(threadIdx.x / kWave)); tile < total; tile += kTileWaves) {
         const int tu = __builtin_amdgcn_readfirstlane(tile);
         const int c = find_set(n_sets, tu, [&](int s) { return static_cast<int64_t>(plan[s].s_tile_off); });
@@ -813,7 +821,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         for (int tl = t0; tl < t1; ++tl) {
             bool have;
             const float2 cn = chunk_norms(tl, have);
-            for_chunks(b, tl * kTileChunks, near_of(cn, have), lane, see);
+            const uint64_t near = near_of(cn, have);
+            if (kCount) done += kTilesPerWave * __popcll(near);
+            for_chunks(b, tl * kTileChunks, near, lane, see);
         }
         for (int tl = t0; tl < t1; ++tl) {
             bool have;
@@ -835,7 +845,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 const float reach = least == INT_MAX ? 0.0f : reach_of(least, 2.0 * most_err(dim), scale);
                 need[t] = ballot(have && cn.x <= hi[t] + reach && cn.y >= lo[t] - reach);
             }
-            const uint64_t rest = ((need[0] | need[1]) | (need[2] | need[3])) & ~near_of(cn, have);
+            const uint64_t near = near_of(cn, have);
+            const uint64_t rest = ((need[0] | need[1]) | (need[2] | need[3])) & ~near;
+#pragma unroll
+            for (int t = 0; t < kTilesPerWave; ++t)
+                if (kCount) done += __popcll(need[t] & ~near);
             for_chunks(b, tl * kTileChunks, rest, lane, [&](const ChunkRegs& a, int k) {
 #pragma unroll
                 for (int t = 0; t < kTilesPerWave; ++t) {
@@ -862,6 +876,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 w.s_best[static_cast<int64_t>(tu) * kGroup + t * kTileCols + lane] = make_int2(m1[t], m2[t]);
         }
     }
+    if (kCount) count_work(work, done);
 }
 
 constexpr int kStage = 384;  // hits a wavefront gathers in LDS before it hands them out
@@ -881,9 +896,11 @@ constexpr int kStage = 384;  // hits a wavefront gathers in LDS before it hands 
 // norms cannot prune, the products; for a LiDAR pair the waits (matrix unit 16%,
 // vector unit 24% busy), which loads two chunks ahead, three wavefronts per SIMD or one
 // or three rounds of tiles only made longer (87 us -> 89 to 98).
+template <bool kCount>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sweep_tiles(
     const SetPlan* __restrict__ plan, int n_sets, int dim, const int32_t* __restrict__ list,
-    const PairScale* __restrict__ pp, MatchWs w, const MatchCtl* __restrict__ ctl, const DevStatus* __restrict__ st) {
+    const PairScale* __restrict__ pp, MatchWs w, const MatchCtl* __restrict__ ctl, const DevStatus* __restrict__ st,
+    int64_t* work) {
     __shared__ i32x4 s_hit[kWavesPerBlock][kStage];     // a lane's four scores,
     __shared__ uint32_t s_at[kWavesPerBlock][kStage];   // their first row and column,
     __shared__ uint16_t s_rank[kWavesPerBlock][kStage]; // and the place of the first in its list
@@ -895,6 +912,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const int total = st->err_capacity ? 0 : ctl->tiles;
     const int cap = ctl->cap, depth = ctl->depth;
     const double e_rows = most_err(dim);
+    int done = 0;
     for (int tile = first_tile(n_sets, wv); tile < total; tile += kTileWaves) {
         const int tu = __builtin_amdgcn_readfirstlane(tile);
         const int c = find_set(n_sets, tu, [&](int s) { return static_cast<int64_t>(plan[s].tile_off); });
@@ -990,6 +1008,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 }
             }
             const uint64_t all = (need[0] & need[1]) & (need[2] & need[3]);
+#pragma unroll
+            for (int t = 0; t < kTilesPerWave; ++t)
+                if (kCount) done += __popcll(need[t]);
             for_chunks(b, k0, (need[0] | need[1]) | (need[2] | need[3]), lane, [&](const ChunkRegs& a, int k) {
                 i32x4 s[kTilesPerWave];
                 uint64_t has[kTilesPerWave];
@@ -1026,6 +1047,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         }
         if (n_hit) hand_out();
     }
+    if (kCount) count_work(work, done);
 }
 
 // ------------------------------------------------------ exact re-scoring --
@@ -1794,11 +1816,14 @@ kmg_status match_queries(const MatchSet* sets, int n_sets, int dim, const int32_
                          const MatchWs& w, hipStream_t s) {
     {
         StageScope sc(ST_MATCH_TOPK, s);
-        sample_tiles<<<kTileBlocks, kBlock, 0, s>>>(w.plan, n_sets, dim, list, w.pp, w, w.ctl, st);
+        int64_t* const work = &st->match_products[list ? 1 : 0];
+        const auto sample = timer_on() ? &sample_tiles<true> : &sample_tiles<false>;
+        const auto sweep = timer_on() ? &sweep_tiles<true> : &sweep_tiles<false>;
+        sample<<<kTileBlocks, kBlock, 0, s>>>(w.plan, n_sets, dim, list, w.pp, w, w.ctl, st, work);
         KMG_TRY(launch_status());
-        sweep_tiles<<<kTileBlocks, kBlock, 0, s>>>(w.plan, n_sets, dim, list, w.pp, w, w.ctl, st);
+        sweep<<<kTileBlocks, kBlock, 0, s>>>(w.plan, n_sets, dim, list, w.pp, w, w.ctl, st, work);
         KMG_TRY(launch_status());
-        timer_note_work(&st->match_products);
+        timer_note_work(work);
     }
     StageScope sc(ST_MATCH_RESCORE, s);
     score_lists<<<grid_cap((w.q_cap / kGroup + n_sets) * (kGroup * kScoreLanes / kBlock), 1), kBlock, 0, s>>>(sets, w.plan, n_sets, dim, list, w.pp, w,

@@ -76,6 +76,8 @@ int timer_enable(int on) {
     return 0;
 }
 
+bool timer_on() { return g_timer.enabled; }
+
 void timer_note_work(const int64_t* dev) {
     TimerState& t = g_timer;
     if (!t.enabled || !t.open) return;
