@@ -24,12 +24,11 @@ import torch
 
 from . import kmg
 
+# (spfh_pair_mean and band_tile are accepted by the library without effect, and not tried)
 SPACE = {
     "search_waves": (2, 4, 8),
     "count_queries": (1, 2, 4),
-    "spfh_pair_mean": (0, 16, 24, 32, 8192),
     "fpfh_rows": (1, 2, 4, 8, 16),
-    "band_tile": (0, 8, 12, 16, 20, 24, 32, 48, 64),
     "fuse_features": (0, 1),
     "xcd_split": (0, 1, 2, 3),
     "match_form": (0, 1),
