@@ -76,9 +76,13 @@ __device__ __forceinline__ float atan2_screen(float y, float x) {
 // 1 / ||d0||.  Returns false when a decision is too close to call in FP32: a
 // short frame axis (||d x u|| < 0.2), a near-degenerate f1 argument (|(w.n_b,
 // u.n_b)| < 0.2), or a scaled feature within 2e-4 of an integer; and for what
-// is not a number.  The FP32 error of the scaled features is below 3e-5 outside
-// those cases (hardware reciprocal roots, 1e-7 relative; f1 2e-6 + 7e-7 times
-// H / 2 pi).
+// is not a number.  The FP32 error of the scaled features outside those cases, with
+// u = 2^-24, unit normals and hardware reciprocal roots within an ulp: d is off by at
+// most 5.5 u, d x u by 8 u, which over its least length of 0.2 is 2.4e-6, v by 2.7e-6
+// and w by 2.9e-6; v . n_b so by 2.9e-6, (w . n_b, u . n_b) by 3.1e-6, which over its
+// least length of 0.2 is an angle of 1.6e-5 with the polynomial's 7e-7.  Times H / 2 or
+// H / 2 pi, at most 32 bins, and with the last roundings: below 5e-5 and 9e-5 (the most
+// seen in 24 million frames, half of them near those limits: 7e-6 and 1.1e-5).
 __device__ __forceinline__ bool bins_f32_roles(V3f d0, float rdl, V3f nq, V3f nk, bool qa, int H, int bins[3]) {
     const V3f u = qa ? nq : nk;
     const V3f nb = qa ? nk : nq;
