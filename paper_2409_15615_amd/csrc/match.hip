@@ -63,6 +63,7 @@ constexpr int kPartRounds = 8;     // partials of the sample in flight per query
 constexpr int kCentreRows = 256;   // rows sampled for a pair's centre and scale
 constexpr double kRangeRms = 4.0;
 constexpr float kOrdinary = 16.0f;
+constexpr double kSkew = 8.0;
 constexpr double kRange = 32600.0;  // largest norm of an integer row
 constexpr int kLimb = 32639;        // largest |q|: 127 * 256 + 127
 constexpr int kMinCap = 16;         // listed rows per query the pool always holds
@@ -313,18 +314,52 @@ __device__ void order_rows(const MatchSet* sets, int n_sets, int dim, const Sing
     }
 }
 
+// Of the 16 rows that a wavefront holds (lane d: dimension d), those with norms of at
+// most kOrdinary times their upper quartile: bit 4 u for row u.  row: the lane's row, d / 4,
+// is there.
+__device__ __forceinline__ uint64_t ordinary_rows(const double* x, bool row) {
+    constexpr int kPer = kWave / 4;
+    const int d = lane_id();
+    float n2[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) n2[u] = static_cast<float>(x[u]) * static_cast<float>(x[u]);
+    // the lanes halve the rows that they go on with at each step, lane d ending with row d / 4
+#pragma unroll
+    for (int l = 32, n = kPer / 2; n > 0; l >>= 1, n >>= 1) {
+#pragma unroll
+        for (int u = 0; u < n; ++u) {
+            const float give = d & l ? n2[u] : n2[u + n];
+            n2[u] = (d & l ? n2[u + n] : n2[u]) + __shfl_xor(give, l, kWave);
+        }
+    }
+    n2[0] += __shfl_xor(n2[0], 2, kWave);
+    n2[0] += __shfl_xor(n2[0], 1, kWave);
+    const float norm = n2[0] >= 0.0f ? sqrtf(n2[0]) : INFINITY;  // not a number: the largest of all
+    // the quartile, to the twelve leading bits (rounded up)
+    constexpr int kBits = 12;
+    constexpr uint32_t kInf = 0x7f800000u;
+    const uint32_t key = (row ? __float_as_uint(norm) : ~0u) >> (31 - kBits);
+    const int rank = max(__popcll(ballot(row)) - 4, 0) * 3 / 4;  // four lanes a row
+    uint32_t at = 0;
+#pragma unroll
+    for (int k = kBits - 1; k >= 0; --k)
+        if (__popcll(ballot(key < (at | 1u << k))) <= rank) at |= 1u << k;
+    const float most = kOrdinary * __uint_as_float(min((at + 1) << (31 - kBits), kInf));
+    return ballot(row && norm <= most);
+}
+
 // One launch: block 0 plans, block 1 + i finds the centre and the scale of
 // pair i, the rest order the rows.  With `single` the two sets come by value (and are written, with the
 // output record, for the kernels that follow); the status is then cleared too.
 //
 // Centre: the mean of kCentreRows rows at even strides over both sets, in a
 // fixed order (any centre is valid, every bound is stated for the rows as
-// rounded); scale: kRangeRms root mean square norms about it span kRange.  Rows
-// with norms beyond kOrdinary times the upper quartile of the 16 that a wavefront
-// reads have no part in either: a single one of a million times the norm among the 256
-// otherwise put all others within a few units, their lists overflowed and both sets
-// were scanned exactly (13,015 x 15,401 rows: 261 us without such a row, 3,041 with
-// it, now 252).  A quantile of all 256 took two barriers and 2 us more.
+// rounded); scale: kRangeRms root mean square norms about it span kRange.  Where the
+// squares of the sixteen wavefronts' rows differ (their mean beyond kSkew times the
+// least), rows of extraordinary norm have no part in either: a single one of a million
+// times the norm among the 256 otherwise put all others within a few units, their lists
+// overflowed and both sets were scanned exactly (13,015 x 15,401 rows: 261 us without
+// such a row, 3,041 with it, now 252).  Looked for in every call, they cost 1 to 2.5 us.
 __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n_sets, int dim, int one_sided,
                                                            int64_t pool, SetPlan* plan, MatchCtl* ctl, PairScale* pp,
                                                            SinglePair single, MatchWs w, DevStatus* st) {
@@ -350,7 +385,6 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
         const int ns = static_cast<int>(nt < kCentreRows ? nt : kCentreRows);
         const int d = threadIdx.x % kMaxMatchDim, g = threadIdx.x / kMaxMatchDim;
         double x[kPer];
-        float n2[kPer];
 #pragma unroll
         for (int u = 0; u < kPer; ++u) {
             const int k = g + u * kGroups;
@@ -360,61 +394,47 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
                 const int r = ns < kCentreRows ? k : static_cast<int>(static_cast<int64_t>(k) * nt / kCentreRows);
                 x[u] = r < na ? set_row(a, r, dim)[d] : set_row(b, r - na, dim)[d];
             }
-            n2[u] = static_cast<float>(x[u]) * static_cast<float>(x[u]);
         }
-        // a wavefront holds its rows whole: their norms (not a number: the largest of all).  The
-        // lanes halve the rows that they go on with at each step, lane d ending with row d / 4.
-        static_assert(kPer == 16 && kGroups == 16, "four steps, and 16 wavefronts");
-#pragma unroll
-        for (int l = 32, n = kPer / 2; n > 0; l >>= 1, n >>= 1) {
-#pragma unroll
-            for (int u = 0; u < n; ++u) {
-                const float give = d & l ? n2[u] : n2[u + n];
-                n2[u] = (d & l ? n2[u + n] : n2[u]) + __shfl_xor(give, l, kWave);
-            }
-        }
-        n2[0] += __shfl_xor(n2[0], 2, kWave);
-        n2[0] += __shfl_xor(n2[0], 1, kWave);
         const bool row = g + d / 4 * kGroups < ns;
-        const float norm = n2[0] >= 0.0f ? sqrtf(n2[0]) : INFINITY;
-        // the upper quartile of the wavefront's rows, to the twelve leading bits (rounded up)
-        constexpr int kBits = 12;
-        constexpr uint32_t kInf = 0x7f800000u;
-        const uint32_t key = (row ? __float_as_uint(norm) : ~0u) >> (31 - kBits);
-        const int rank = max(__popcll(ballot(row)) - 4, 0) * 3 / 4;  // four lanes a row
-        uint32_t at = 0;
+        uint64_t use = ballot(row);  // bit 4 u: row u of the wavefront counts
+        double mu, all;
+        int rows;
+#pragma unroll 1
+        for (int pass = 0;; ++pass) {
+            if (d == 0) s_rows[g] = __popcll(use) / 4;
+            double sum = 0.0;
 #pragma unroll
-        for (int k = kBits - 1; k >= 0; --k)
-            if (__popcll(ballot(key < (at | 1u << k))) <= rank) at |= 1u << k;
-        const float most = kOrdinary * __uint_as_float(min((at + 1) << (31 - kBits), kInf));
-        const uint64_t use = ballot(row && norm <= most);  // bit 4 u: row u counts
-        if (d == 0) s_rows[g] = __popcll(use) / 4;
-        double sum = 0.0;
+            for (int u = 0; u < kPer; ++u)
+                if (use >> (4 * u) & 1) sum += x[u];
+            s_part[threadIdx.x] = sum;
+            __syncthreads();
+            rows = 0;
+            mu = 0.0;
+            for (int q = 0; q < kGroups; ++q) {
+                rows += s_rows[q];
+                mu += s_part[q * kMaxMatchDim + d];
+            }
+            mu = rows > 0 ? mu / rows : 0.0;
+            double sq = 0.0;
 #pragma unroll
-        for (int u = 0; u < kPer; ++u)
-            if (use >> (4 * u) & 1) sum += x[u];
-        s_part[threadIdx.x] = sum;
-        __syncthreads();
-        int rows = 0;
-        double mu = 0.0;
-        for (int q = 0; q < kGroups; ++q) {
-            rows += s_rows[q];
-            mu += s_part[q * kMaxMatchDim + d];
+            for (int u = 0; u < kPer; ++u) {
+                const double v = x[u] - mu;
+                if (d < dim && (use >> (4 * u) & 1)) sq += v * v;
+            }
+            sq = wave_sum(sq);
+            if (d == 0) s_sq[g] = sq;
+            __syncthreads();
+            all = 0.0;
+            double least = INFINITY;
+            for (int q = 0; q < kGroups; ++q) {
+                all += s_sq[q];
+                if (q < ns) least = fmin(least, s_sq[q]);
+            }
+            if (pass > 0 || all <= kSkew * kGroups * least) break;  // uniform; what is not a number goes on
+            use = ordinary_rows(x, row);
         }
-        mu = rows > 0 ? mu / rows : 0.0;
-        double sq = 0.0;
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const double v = x[u] - mu;
-            if (d < dim && (use >> (4 * u) & 1)) sq += v * v;
-        }
-        sq = wave_sum(sq);
-        if (d == 0) s_sq[g] = sq;
-        __syncthreads();
         if (g == 0) pp[pair].mu[d] = d < dim ? mu : 0.0;
         if (threadIdx.x == 0) {
-            double all = 0.0;
-            for (int q = 0; q < kGroups; ++q) all += s_sq[q];
             const double rms = rows > 0 ? sqrt(all / rows) : 0.0;
             double s = rms * (kRangeRms / kRange);
             if (!(s > 1e-30) || !(s < 1e30)) s = 1.0;  // equal rows, or nothing that can be scaled
@@ -1265,6 +1285,9 @@ __global__ __launch_bounds__(kBlock, 7) void score_lists(const MatchSet* __restr
 
 constexpr int kFewOpen = 16;  // up to here the exact scans run a wavefront per query and segment
 constexpr int kXSegMax = 256;  // row segments per group of the exact scan
+// Rows of a segment from which a bound on the norms is looked for: it costs 3 us, as much
+// as a tile of 128 rows (two pairs of 1,849 raw points a cloud: 41 us, with it 44).
+constexpr int kBoundRows = 512;
 
 // Row segments of the exact scan of F listed queries in `groups` groups:
 // enough items for the chip, as many as the partial buffer holds.
@@ -1465,7 +1488,9 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
         // the norms that the entries of a group may need, when all are there for their lists: what
         // the first of the rows on them say
         float from = -INFINITY, upto = INFINITY;
-        if (!ballot(have && err < 0.0f)) {  // uniform in the block
+        const int np = plan[p].n;
+        int len = (np + S - 1) / S;
+        if (len >= kBoundRows && !ballot(have && err < 0.0f)) {  // uniform in the block, and over the group's segments
             int v[kMinCap], m1 = kNoRow, m2 = kNoRow;
 #pragma unroll
             for (int k = 0; k < kMinCap; ++k) v[k] = static_cast<int>(w.pool[slot * ctl->cap + k].y);
@@ -1487,9 +1512,8 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
         double b1 = INFINITY, b2 = INFINITY;
         int j1 = INT_MAX;
         {
-            const int np = plan[p].n, base = plan[p].base;
-            const bool bounded = from > -INFINITY;  // uniform in the block, and over a group's segments
-            int len = (np + S - 1) / S;
+            const int base = plan[p].base;
+            const bool bounded = from > -INFINITY;
             if (bounded) len = (len + kTileRows - 1) / kTileRows * kTileRows;  // whole chunks
             const int r_begin = min(np, sg * len), r_end = min(np, r_begin + len);
             // rows in norm order where some can be passed over, else as they lie
