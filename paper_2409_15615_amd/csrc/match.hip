@@ -1155,7 +1155,7 @@ __device__ __forceinline__ Nearest score_query(const MatchSet& qs, const MatchSe
     Nearest o{INFINITY, INFINITY, INT_MAX, 0};
     const auto take = [&](int j) {
         const double d = exact_d2(set_row(ps, j, dim), y, dim);
-        if (d < o.b1 || (d == o.b1 && j < o.j1)) {
+        if (d < o.b1 || (d == o.b1 && j < o.j1 && d < INFINITY)) {  // an infinite distance is none
             o.b2 = o.b1;
             o.b1 = d;
             o.j1 = j;
@@ -1560,7 +1560,7 @@ __global__ __launch_bounds__(kBlock) void score_rest(const MatchSet* __restrict_
                     const auto take = [&](double acc, int at) {
                         if (!(acc <= b2)) return;
                         const int j = s_id[at];
-                        if (acc < b1 || (acc == b1 && j < j1)) {
+                        if (acc < b1 || (acc == b1 && j < j1 && acc < INFINITY)) {  // an infinite distance is none
                             b2 = b1;
                             b1 = acc;
                             j1 = j;
