@@ -129,7 +129,6 @@ struct DevStatus {
     uint32_t feat_fp64;       // pair features recomputed in FP64
     uint32_t feat_edge;       // FP64 features within 1e-9 of a bin edge
     int32_t err_sync;         // a bounded wait inside a kernel gave up (never expected)
-    int64_t match_products[2]; // query-row products evaluated by the matching's phases (while timing is on)
 };
 
 // Linear workspace allocator; with base == nullptr it only measures.
@@ -200,8 +199,9 @@ void timer_end(int stage, hipStream_t s);
 void timer_collect();  // call after the stream has been synchronised
 int timer_enable(int on);
 int timer_read(double* ms, int64_t* launches, int n);
-// The open stage's work units live in *dev (a device counter read back by timer_work).
-void timer_note_work(const int64_t* dev);
+// The open stage's work units are the sum of dev[0 .. n) (device counters read back by timer_work).
+constexpr int kMaxWorkCounters = 512;
+void timer_note_work(const int64_t* dev, int n);
 bool timer_on();
 int timer_work(int64_t* work, int n);
 const char* stage_name(int stage);
@@ -464,6 +464,7 @@ struct MatchWs {
     int32_t* fb_part;      // queries decided on more than four exact scores, partial counts per set
     int32_t* grp_done;     // exact scan: finished segments per 64-entry group
     uint64_t* emit_status; // look-back words of the mutual test
+    int64_t* work;         // per phase kMaxWorkCounters counters of products (counted while timing is on)
     int64_t q_cap, slot_cap, pool_cap, part_cap;
     int32_t n_sets;
 };

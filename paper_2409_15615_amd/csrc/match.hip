@@ -485,7 +485,6 @@ __global__ __launch_bounds__(kPlanThreads) void match_plan(MatchSet* sets, int n
     __syncthreads();
     plan_queries(c, live, nq, n_p, plan, ctl, st, s_scan, s_sum);
     if (c == 0) {
-        st->match_products[0] = st->match_products[1] = 0;
         ctl->slots = tot[0] * kTileRows;
         ctl->emit_tiles = tot[1];
         // whole 128-byte lines, an odd number of them: with lists a power of two apart the first
@@ -543,6 +542,7 @@ __global__ __launch_bounds__(kBlock) void match_round(const MatchSet* __restrict
     for (int64_t k = tid; k <= ctl->emit_tiles; k += gs) w.emit_status[k] = 0ull;
     for (int64_t k = tid; k < slots / kWave + n_sets + 1; k += gs) w.grp_done[k] = 0;
     for (int64_t k = tid; k < n_sets * kFbParts; k += gs) w.fb_part[k] = 0;
+    for (int64_t k = tid; k < 2 * kMaxWorkCounters; k += gs) w.work[k] = 0;
     const int j = threadIdx.x & 7;
     for (int64_t slot = tid / 8; slot < slots; slot += gs / 8) {
         const int c = find_set(n_sets, slot, [&](int s) { return static_cast<int64_t>(plan[s].base); });
@@ -758,10 +758,12 @@ __device__ __forceinline__ int first_tile(int n_sets, int wv) {
 }
 
 // The 16 x 16 products that a wavefront evaluated, where they are counted (kCount: per-stage
-// timing is on; counted always they were 1% of the call for 100,000 rows).
+// timing is on; counted always they were 1% of the call for 100,000 rows), into counters a
+// line each (all into one, the sample pass of a LiDAR pair took 62 us instead of 36).
 __device__ __forceinline__ void count_work(int64_t* work, int done) {
+    constexpr int kApart = 8;
     if (done && lane_id() == 0)
-        atomicAdd(reinterpret_cast<unsigned long long*>(work),
+        atomicAdd(reinterpret_cast<unsigned long long*>(work) + global_wave() % (kMaxWorkCounters / kApart) * kApart,
                   static_cast<unsigned long long>(done) * (kTileRows * kTileCols));
 }
 
@@ -1829,6 +1831,7 @@ MatchWs carve_match(Carver& c, int n_sets, int64_t q_cap, int dim) {
     w.fb_part = c.take<int32_t>(static_cast<size_t>(n_sets) * kFbParts);
     w.grp_done = c.take<int32_t>(static_cast<size_t>(w.slot_cap / kWave + n_sets + 2));
     w.emit_status = c.take<uint64_t>(static_cast<size_t>(w.q_cap / kEmitTile + n_sets + 2));
+    w.work = c.take<int64_t>(2 * kMaxWorkCounters);
     return w;
 }
 
@@ -1840,14 +1843,14 @@ kmg_status match_queries(const MatchSet* sets, int n_sets, int dim, const int32_
                          const MatchWs& w, hipStream_t s) {
     {
         StageScope sc(ST_MATCH_TOPK, s);
-        int64_t* const work = &st->match_products[list ? 1 : 0];
+        int64_t* const work = w.work + (list ? kMaxWorkCounters : 0);
         const auto sample = timer_on() ? &sample_tiles<true> : &sample_tiles<false>;
         const auto sweep = timer_on() ? &sweep_tiles<true> : &sweep_tiles<false>;
         sample<<<kTileBlocks, kBlock, 0, s>>>(w.plan, n_sets, dim, list, w.pp, w, w.ctl, st, work);
         KMG_TRY(launch_status());
         sweep<<<kTileBlocks, kBlock, 0, s>>>(w.plan, n_sets, dim, list, w.pp, w, w.ctl, st, work);
         KMG_TRY(launch_status());
-        timer_note_work(work);
+        timer_note_work(work, kMaxWorkCounters);
     }
     StageScope sc(ST_MATCH_RESCORE, s);
     score_lists<<<grid_cap((w.q_cap / kGroup + n_sets) * (kGroup * kScoreLanes / kBlock), 1), kBlock, 0, s>>>(sets, w.plan, n_sets, dim, list, w.pp, w,

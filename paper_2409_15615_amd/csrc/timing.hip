@@ -21,6 +21,7 @@ struct TimerState {
     double ms[kStageCount] = {};
     int64_t launches[kStageCount] = {};
     const int64_t* work[kStageCount] = {};  // device counters of the stages' last timed launches
+    int n_work[kStageCount] = {};
 };
 
 TimerState g_timer;
@@ -78,19 +79,24 @@ int timer_enable(int on) {
 
 bool timer_on() { return g_timer.enabled; }
 
-void timer_note_work(const int64_t* dev) {
+void timer_note_work(const int64_t* dev, int n) {
     TimerState& t = g_timer;
     if (!t.enabled || !t.open) return;
     t.work[t.stage_of[t.used]] = dev;
+    t.n_work[t.stage_of[t.used]] = n < kMaxWorkCounters ? n : kMaxWorkCounters;
 }
 
 int timer_work(int64_t* work, int n) {
     timer_collect();
     const int k = n < kStageCount ? n : kStageCount;
     for (int i = 0; i < k; ++i) {
-        int64_t v = 0;
-        if (g_timer.work[i] && hipMemcpy(&v, g_timer.work[i], sizeof(v), hipMemcpyDeviceToHost) != hipSuccess) v = -1;
-        if (work) work[i] = v;
+        int64_t v[kMaxWorkCounters], sum = 0;
+        const int c = g_timer.n_work[i];
+        if (g_timer.work[i]) {
+            if (hipMemcpy(v, g_timer.work[i], c * sizeof(v[0]), hipMemcpyDeviceToHost) != hipSuccess) sum = -1;
+            else for (int j = 0; j < c; ++j) sum += v[j];
+        }
+        if (work) work[i] = sum;
     }
     return kStageCount;
 }
