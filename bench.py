@@ -67,7 +67,7 @@ def timed(fn, steps, sync):
 
 def batch_fingerprint(batch):
     """Digests of a batch's results for the autotuner's invariance check: pair counts,
-    sizes and statuses (counts without column 5, the exact re-scans, a work statistic
+    sizes and statuses (counts without column 5, queries beyond four exact scores, a work statistic
     that depends on the matching form), correspondences, d1, d2."""
     import hashlib
 
